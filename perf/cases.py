@@ -259,3 +259,47 @@ def tolerance(case):
     if case["kind"] in ("prune", "refresh", "search"):
         return "exact"
     return {"rel": 5e-6 if case.get("fp32") else 8e-4}
+
+
+def _masked64(W, V, M):
+    """V:N:M pruning of W in fp64: per V x M block the four columns of largest L1 norm, per row the two
+    largest magnitudes among them, ties to the lower index."""
+    out, inn = W.shape
+    R, B = -(-out // V), -(-inn // M)
+    P = torch.zeros((R * V, B * M), dtype=torch.float64, device=W.device)
+    P[:out, :inn] = W.double()
+    P = P.reshape(R, V, B, M)
+    norms = P.abs().sum(1)                                                          # [R, B, M], exact
+    cols = torch.sort(norms, dim=-1, descending=True, stable=True).indices[..., :4].sort(-1).values
+    cols = cols[:, None].expand(R, V, B, 4)
+    kept = P.gather(3, cols)
+    two = torch.sort(kept.abs(), dim=-1, descending=True, stable=True).indices[..., :2]
+    D = torch.zeros_like(P).scatter_(3, cols.gather(3, two), kept.gather(3, two))
+    return D.reshape(R * V, B * M)[:out, :inn]
+
+
+def exact(case, seed):
+    """Products in fp64.  What is defined to the bit (pruning, merging, the search) has no rounding to measure."""
+    g = _generator(seed)
+    if case["kind"] == "layer":
+        W = _masked64(_weight(g, case["out"], case["in"]), case["V"], case["M"])
+        x = _activations(g, case["tokens"], case["in"]).double()
+        bias = torch.randn(case["out"], generator=g, device=DEV).to(torch.float16) if case["bias"] else None
+        perm = {p: torch.randperm(n, generator=g, device=DEV) if case[p] else None
+                for p, n in (("perm_in", case["in"]), ("perm_out", case["out"]))}
+        y = (x if perm["perm_in"] is None else x[:, perm["perm_in"]]) @ W.t()
+        if bias is not None:
+            y += bias.double()
+        if perm["perm_out"] is None:
+            return y
+        z = torch.empty_like(y)
+        z[:, perm["perm_out"]] = y
+        return z
+    if case["kind"] != "block":
+        return None
+    layers = _layers(case)
+    W = [_masked64(_weight(g, o, i), case["V"], case["M"]) for _, o, i, _ in layers]
+    widths = {x: i for _, _, i, x in layers}
+    xs = [_activations(g, case["tokens"], widths[k]).double() for k in range(len(widths))]
+    bias = [torch.randn(o, generator=g, device=DEV).to(torch.float16) if case["bias"] else None for _, o, _, _ in layers]
+    return [xs[x] @ w.t() if b is None else xs[x] @ w.t() + b.double() for (_, _, _, x), w, b in zip(layers, W, bias)]
