@@ -107,6 +107,11 @@ int launch_decompress(const void* values, const void* meta, const void* colidx, 
 int launch_spmm_generic(const void* X, int64_t T, int64_t ldx, const void* values, const void* meta,
                         const void* colidx, const Dims& d, void* Y, int64_t ldy, int y_dtype,
                         const Fused& f, hipStream_t st);
+// Products on the canonical triple for layers without a packed copy and for unaligned X (vnm_spmm_plain.hip)
+bool spmm_plain_applicable(int64_t T, const void* colidx, const Dims& d);
+int launch_spmm_plain(const void* X, int64_t T, int64_t ldx, const void* values, const void* meta,
+                      const void* colidx, const Dims& d, void* Y, int64_t ldy, int y_dtype,
+                      const Fused& f, hipStream_t st);
 // perm_in (or null): image row c of K step s holds X[:, perm_in[8 M s + c]]
 int launch_stage_x(const void* X, int64_t T, int64_t ldx, const Dims& d, const int* perm_in, void* Xs,
                    hipStream_t st);

@@ -25,6 +25,8 @@ int launch_prune_fast_scored(const void*, int64_t, const void*, int64_t, const D
 int launch_prune_scored(const void*, int64_t, const void*, int64_t, const Dims&, void*, void*, void*, void*, hipStream_t) STUB
 int launch_ria_scores(const void*, int64_t, int64_t, int64_t, const void*, void*, int64_t, void*, hipStream_t) STUB
 int launch_spmm_generic(const void*, int64_t, int64_t, const void*, const void*, const void*, const Dims&, void*, int64_t, int, const Fused&, hipStream_t) STUB
+bool spmm_plain_applicable(int64_t, const void*, const Dims&) { return true; }
+int launch_spmm_plain(const void*, int64_t, int64_t, const void*, const void*, const void*, const Dims&, void*, int64_t, int, const Fused&, hipStream_t) STUB
 int launch_spmm_resident(const void*, int64_t, int64_t, const void*, const Dims&, void*, int64_t, int, const Fused&, hipStream_t) STUB
 int launch_spmm_skinny(const void*, int64_t, int64_t, const void*, const Dims&, void*, int64_t, int, void*, int64_t, const Fused&, hipStream_t) STUB
 int launch_stage_x(const void*, int64_t, int64_t, const Dims&, const int*, void*, hipStream_t) STUB
