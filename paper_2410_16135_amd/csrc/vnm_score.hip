@@ -6,6 +6,7 @@
 // most 2^40 each, summed in 64 bits), every later step is a single IEEE fp64 operation -- convert,
 // divide, divide, add, multiply -- and the result is rounded once to fp32.  In the pruning kernel
 // the column L1 norms of the scores are added in fp64 one row after the other, a fixed order.
+#include <type_traits>
 #include "vnm_internal.h"
 
 namespace vnm {
@@ -16,121 +17,153 @@ __device__ __forceinline__ unsigned long long sc_fp16_units(unsigned short h) {
   return e ? ((unsigned long long)(1024u + m) << (e - 1)) : (unsigned long long)m;
 }
 
-// Column sums: a workgroup owns 64 columns and walks all rows.  Thread (c, q) owns 8 adjacent columns
-// (one 16-byte load per row: with 8 such threads a row of the strip is one 128-byte line) and the rows
-// q, q + 32, ...; the 32 partial sums of a column meet in LDS and one thread stores their total, so
-// every sum is written once, by one thread, without atomics.  `vec` = rows are 16-byte aligned;
-// otherwise 2-byte loads.
-__global__ void __launch_bounds__(256)
-abs_colsum_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, int64_t ldw, int vec,
-                  unsigned long long* __restrict__ colsum) {
-  __shared__ unsigned long long part[32][8][8];
-  const int c = threadIdx.x & 7, q = threadIdx.x >> 3;
-  const int64_t col = ((int64_t)blockIdx.x * 8 + c) * 8;
-  const int nc = col >= in ? 0 : (int)((in - col) < 8 ? (in - col) : 8);
-  unsigned long long acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (nc > 0) {
-    if (vec && nc == 8) {
-      constexpr int kU = 4;                                   // rows in flight per thread
-      for (int64_t row = q; row < out; row += 32 * kU) {
-        uint4 v[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          const int64_t rr = row + 32 * u;
-          v[u] = rr < out ? *(const uint4*)(W + rr * ldw + col) : make_uint4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          const unsigned d[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            acc[2 * e] += sc_fp16_units((unsigned short)(d[e] & 0xFFFFu));
-            acc[2 * e + 1] += sc_fp16_units((unsigned short)(d[e] >> 16));
-          }
-        }
-      }
-    } else {
-      for (int64_t row = q; row < out; row += 32) {
-        const unsigned short* p = W + row * ldw + col;
-        for (int e = 0; e < nc; ++e) acc[e] += sc_fp16_units(p[e]);
-      }
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) part[q][c][e] = acc[e];
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const int cc = threadIdx.x >> 3, e = threadIdx.x & 7;
-    const int64_t gc = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    unsigned long long t = 0;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) t += part[k][cc][e];
-    if (gc < in) colsum[gc] = t;
-  }
+__global__ void __launch_bounds__(256) zero_u64_kernel(unsigned long long* p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) p[i] = 0;
 }
 
-// Row sums: one wave per row, lanes stride over the row 8 columns at a time, one reduction at the end.
+// Column and row sums in one pass over W.  A workgroup owns 128 rows x 256 columns; thread (q, c) owns 8
+// adjacent columns (one 16-byte load per row) and the rows q, q + 8, ....  Its partial sums meet those of
+// the other threads in LDS and leave as one 64-bit integer atomic per row and column of the tile: integer
+// sums do not depend on their order.  Bound by the read of W.  (Before: one workgroup per 64 columns
+// walked all rows, 34 us on 4096 x 4096 with 64 workgroups on 256 compute units, and a second kernel read
+// W again for the row sums, 10 us.)  `vec` = rows are 16-byte aligned; otherwise 2-byte loads.
+constexpr int kSumRows = 128, kSumCols = 256;
+
 __global__ void __launch_bounds__(256)
-abs_rowsum_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, int64_t ldw, int vec,
-                  unsigned long long* __restrict__ rowsum) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= out) return;                                    // uniform over the wave
-  const unsigned short* p = W + row * ldw;
-  unsigned long long acc = 0;
-  for (int64_t c = (int64_t)lane * 8; c < in; c += 512) {
-    if (vec && c + 8 <= in) {
-      const uint4 v = *(const uint4*)(p + c);
-      const unsigned d[4] = {v.x, v.y, v.z, v.w};
+abs_sums_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, int64_t ldw, int vec,
+                unsigned long long* __restrict__ colsum, unsigned long long* __restrict__ rowsum) {
+  __shared__ unsigned long long rpart[kSumRows][33];
+  __shared__ unsigned long long cpart[8][kSumCols];
+  const int c = threadIdx.x & 31, q = threadIdx.x >> 5;
+  const int64_t col = (int64_t)blockIdx.x * kSumCols + c * 8;
+  const int64_t row0 = (int64_t)blockIdx.y * kSumRows + q;
+  const int nc = col >= in ? 0 : (int)((in - col) < 8 ? (in - col) : 8);
+  constexpr int kU = kSumRows / 8;
+  unsigned long long acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (vec && nc == 8) {
+    // all 16 rows in flight: rows beyond the last repeat it and count as zero
+    uint4 v[kU];
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        acc += sc_fp16_units((unsigned short)(d[e] & 0xFFFFu)) + sc_fp16_units((unsigned short)(d[e] >> 16));
-    } else {
-      for (int64_t e = c; e < in && e < c + 8; ++e) acc += sc_fp16_units(p[e]);
+    for (int u = 0; u < kU; ++u) {
+      const int64_t rr = row0 + 8 * u;
+      v[u] = *(const uint4*)(W + (rr < out ? rr : out - 1) * ldw + col);
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const bool ok = row0 + 8 * u < out;
+      const unsigned d[4] = {ok ? v[u].x : 0u, ok ? v[u].y : 0u, ok ? v[u].z : 0u, ok ? v[u].w : 0u};
+      unsigned long long s = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned long long a = sc_fp16_units((unsigned short)(d[e] & 0xFFFFu)), b = sc_fp16_units((unsigned short)(d[e] >> 16));
+        acc[2 * e] += a; acc[2 * e + 1] += b;
+        s += a + b;
+      }
+      rpart[q + 8 * u][c] = s;
+    }
+  } else {
+    for (int u = 0; u < kU; ++u) {
+      const int64_t rr = row0 + 8 * u;
+      unsigned long long s = 0;
+      if (rr < out)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (e < nc) { const unsigned long long a = sc_fp16_units(W[rr * ldw + col + e]); acc[e] += a; s += a; }
+      rpart[q + 8 * u][c] = s;
     }
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned lo = __shfl_xor((unsigned)acc, o), hi = __shfl_xor((unsigned)(acc >> 32), o);
-    acc += ((unsigned long long)hi << 32) | lo;
-  }
-  if (lane == 0) rowsum[row] = acc;
+  for (int e = 0; e < 8; ++e) cpart[q][c * 8 + e] = acc[e];
+  __syncthreads();
+  const int64_t gc = (int64_t)blockIdx.x * kSumCols + threadIdx.x;
+  unsigned long long t = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) t += cpart[k][threadIdx.x];
+  if (gc < in && t) atomicAdd(colsum + gc, t);
+  // two threads per row
+  const int lr = threadIdx.x >> 1, h = (threadIdx.x & 1) * 16;
+  unsigned long long s = 0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) s += rpart[lr][h + k];
+  const unsigned lo = __shfl_xor((unsigned)s, 1), hi = __shfl_xor((unsigned)(s >> 32), 1);
+  s += ((unsigned long long)hi << 32) | lo;
+  const int64_t gr = (int64_t)blockIdx.y * kSumRows + lr;
+  if (h == 0 && gr < out && s) atomicAdd(rowsum + gr, s);
+}
+
+// a / b rounded to nearest, from y = 1 / b rounded to nearest: q0 = a y is within 1.5 ulp, one correction
+// makes q1 a faithful quotient, and for a faithful quotient the second one gives the correctly rounded result
+// (Markstein's theorem; no overflow or underflow here: a is 0 or an integer up to 2^41, b one up to 2^63).
+// Five operations per element; the division by itself takes about fifteen, two of them per element
+// (53 us on 4096 x 4096, of which the memory traffic needs a third).
+__device__ __forceinline__ double sc_div(double a, double b, double y) {
+  const double q0 = a * y;
+  const double q1 = fma(fma(-b, q0, a), y, q0);
+  return fma(fma(-b, q1, a), y, q1);
 }
 
 // Scores: thread t owns 4 adjacent columns (`vec`: one 8-byte load of W and one 16-byte store of S per
-// row) and walks the rows blockIdx.y, blockIdx.y + gridDim.y, ...
+// row) of 16 rows; the reciprocals are taken once per column and thread and once per row and workgroup.
+constexpr int kScoreRows = 16;
+
 __global__ void __launch_bounds__(256)
 ria_score_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, int64_t ldw,
                  const unsigned long long* __restrict__ colsum, const unsigned long long* __restrict__ rowsum,
                  const float* __restrict__ act, float* __restrict__ S, int64_t lds, int vec) {
+  __shared__ double rsum[kScoreRows], rrec[kScoreRows];
   const int64_t col = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (col >= in) return;
-  const int nc = (int)((in - col) < 4 ? (in - col) : 4);
-  unsigned long long cs[4] = {0, 0, 0, 0};
-  double cd[4] = {0, 0, 0, 0}, ad[4] = {0, 0, 0, 0};
-  for (int e = 0; e < nc; ++e) { cs[e] = colsum[col + e]; cd[e] = (double)cs[e]; ad[e] = (double)act[col + e]; }
-  for (int64_t row = blockIdx.y; row < out; row += gridDim.y) {
-    const unsigned long long rs = rowsum[row];
-    const double rd = (double)rs;
-    unsigned short h[4] = {0, 0, 0, 0};
-    if (vec && nc == 4) {
-      const uint2 v = *(const uint2*)(W + row * ldw + col);
-      h[0] = (unsigned short)(v.x & 0xFFFFu); h[1] = (unsigned short)(v.x >> 16);
-      h[2] = (unsigned short)(v.y & 0xFFFFu); h[3] = (unsigned short)(v.y >> 16);
-    } else {
-      for (int e = 0; e < nc; ++e) h[e] = W[row * ldw + col + e];
-    }
-    float sc[4];
+  const int nc = col >= in ? 0 : (int)((in - col) < 4 ? (in - col) : 4);
+  double cd[4], cy[4], ad[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const double a = (double)sc_fp16_units(h[e]);
-      const double q_col = cs[e] ? a / cd[e] : 0.0;
-      const double q_row = rs ? a / rd : 0.0;
-      const double sum = q_col + q_row;
-      sc[e] = (float)(sum * ad[e]);
+  for (int e = 0; e < 4; ++e) {
+    cd[e] = e < nc ? (double)colsum[col + e] : 0.0;
+    ad[e] = e < nc ? (double)act[col + e] : 0.0;
+    cy[e] = cd[e] > 0.0 ? 1.0 / cd[e] : 0.0;          // a zero sum: every quotient of its terms is 0
+  }
+  for (int64_t row0 = (int64_t)blockIdx.y * kScoreRows; row0 < out; row0 += (int64_t)gridDim.y * kScoreRows) {
+    const int nr = (int)(out - row0 < kScoreRows ? out - row0 : kScoreRows);
+    __syncthreads();
+    if ((int)threadIdx.x < nr) {
+      const double rd = (double)rowsum[row0 + threadIdx.x];
+      rsum[threadIdx.x] = rd;
+      rrec[threadIdx.x] = rd > 0.0 ? 1.0 / rd : 0.0;
     }
-    if (vec && nc == 4) *(float4*)(S + row * lds + col) = make_float4(sc[0], sc[1], sc[2], sc[3]);
-    else for (int e = 0; e < nc; ++e) S[row * lds + col + e] = sc[e];
+    __syncthreads();
+    if (nc == 0) continue;
+    auto scores = [&](int v, const unsigned short* h, float* sc) {
+      const double rd = rsum[v], ry = rrec[v];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double a = (double)sc_fp16_units(h[e]);
+        const double sum = sc_div(a, cd[e], cy[e]) + sc_div(a, rd, ry);
+        sc[e] = (float)(sum * ad[e]);
+      }
+    };
+    if (vec && nc == 4) {
+      uint2 w[kScoreRows];
+#pragma unroll
+      for (int v = 0; v < kScoreRows; ++v) w[v] = *(const uint2*)(W + (row0 + (v < nr ? v : nr - 1)) * ldw + col);
+#pragma unroll
+      for (int v = 0; v < kScoreRows; ++v) {
+        if (v >= nr) break;
+        const unsigned short h[4] = {(unsigned short)(w[v].x & 0xFFFFu), (unsigned short)(w[v].x >> 16),
+                                     (unsigned short)(w[v].y & 0xFFFFu), (unsigned short)(w[v].y >> 16)};
+        float sc[4];
+        scores(v, h, sc);
+        *(float4*)(S + (row0 + v) * lds + col) = make_float4(sc[0], sc[1], sc[2], sc[3]);
+      }
+    } else {
+      for (int v = 0; v < nr; ++v) {
+        unsigned short h[4] = {0, 0, 0, 0};
+        float sc[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) if (e < nc) h[e] = W[(row0 + v) * ldw + col + e];
+        scores(v, h, sc);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) if (e < nc) S[(row0 + v) * lds + col + e] = sc[e];
+      }
+    }
   }
 }
 
@@ -140,12 +173,15 @@ int launch_ria_scores(const void* W, int64_t out, int64_t in, int64_t ldw, const
   unsigned long long* colsum = (unsigned long long*)workspace;
   unsigned long long* rowsum = colsum + in;
   const int vec = (ldw % 8 == 0) && (((uintptr_t)W & 15) == 0);
-  hipLaunchKernelGGL(abs_colsum_kernel, dim3((unsigned)((in + 63) / 64)), dim3(256), 0, st, (const unsigned short*)W, out, in,
-                     ldw, vec, colsum);
-  hipLaunchKernelGGL(abs_rowsum_kernel, dim3((unsigned)((out + 3) / 4)), dim3(256), 0, st, (const unsigned short*)W,
-                     out, in, ldw, vec, rowsum);
+  hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((in + out + 255) / 256)), dim3(256), 0, st, colsum, in + out);
+  for (int64_t o0 = 0; o0 < out; o0 += 65535ll * kSumRows) {      // grid.y limit
+    const int64_t rows = out - o0 < 65535ll * kSumRows ? out - o0 : 65535ll * kSumRows;
+    hipLaunchKernelGGL(abs_sums_kernel, dim3((unsigned)((in + kSumCols - 1) / kSumCols), (unsigned)((rows + kSumRows - 1) / kSumRows)),
+                       dim3(256), 0, st, (const unsigned short*)W + o0 * ldw, rows, in, ldw, vec, colsum, rowsum + o0);
+  }
   const int vec_s = (ldw % 4 == 0) && (((uintptr_t)W & 7) == 0) && (lds % 4 == 0) && (((uintptr_t)S & 15) == 0);
-  hipLaunchKernelGGL(ria_score_kernel, dim3((unsigned)((in + 1023) / 1024), (unsigned)(out < 65535 ? out : 65535)), dim3(256), 0, st,
+  const int64_t gy = (out + kScoreRows - 1) / kScoreRows;
+  hipLaunchKernelGGL(ria_score_kernel, dim3((unsigned)((in + 1023) / 1024), (unsigned)(gy < 65535 ? gy : 65535)), dim3(256), 0, st,
                      (const unsigned short*)W, out, in, ldw, colsum, rowsum, (const float*)act, (float*)S, lds, vec_s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "ria score kernels"); return VNM_ERR_HIP; }
@@ -299,6 +335,54 @@ lora_merge_kernel(const unsigned short* __restrict__ W, int64_t ldw, const float
   for (int v = 0; v < kMergeRows; ++v)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[v][e] = 0.f;
+  // whole tiles with aligned rows: W and four rows of A at a time are requested before the first use (one row
+  // per trip left a memory round trip exposed per k: 28 us on 4096 x 4096 at r = 16)
+  if (vec && avec && n == 8 && rows == kMergeRows) {
+    uint4 w4[kMergeRows];
+#pragma unroll
+    for (int v = 0; v < kMergeRows; ++v) w4[v] = *(const uint4*)(W + (o0 + v) * ldw + i0);
+    auto steps = [&](int k, auto count) {
+#pragma clang fp contract(off)
+      constexpr int K = decltype(count)::value;
+      float4 a0[K], a1[K];
+#pragma unroll
+      for (int u = 0; u < K; ++u) {
+        a0[u] = *(const float4*)(A + (int64_t)(k + u) * lda + i0);
+        a1[u] = *(const float4*)(A + (int64_t)(k + u) * lda + i0 + 4);
+      }
+#pragma unroll
+      for (int u = 0; u < K; ++u) {
+        const float a[8] = {a0[u].x, a0[u].y, a0[u].z, a0[u].w, a1[u].x, a1[u].y, a1[u].z, a1[u].w};
+#pragma unroll
+        for (int v = 0; v < kMergeRows; ++v) {
+          const float b = B[(o0 + v) * ldb + k + u];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) { const float p = b * a[e]; acc[v][e] = acc[v][e] + p; }
+        }
+      }
+    };
+    int k = 0;
+    for (; k + 4 <= r; k += 4) steps(k, std::integral_constant<int, 4>{});
+    for (; k < r; ++k) steps(k, std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int v = 0; v < kMergeRows; ++v) {
+      const unsigned d[4] = {w4[v].x, w4[v].y, w4[v].z, w4[v].w};
+      unsigned m[4];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const unsigned short hb = (unsigned short)(d[e / 2] >> (16 * (e & 1)));
+        _Float16 h;
+        __builtin_memcpy(&h, &hb, 2);
+        const float sp = scale * acc[v][e];
+        const _Float16 res = (_Float16)(sp + (float)h);
+        unsigned short rb;
+        __builtin_memcpy(&rb, &res, 2);
+        m[e / 2] = (e & 1) ? (m[e / 2] | ((unsigned)rb << 16)) : rb;
+      }
+      *(uint4*)(Wm + (o0 + v) * ldm + i0) = make_uint4(m[0], m[1], m[2], m[3]);
+    }
+    return;
+  }
   for (int k = 0; k < r; ++k) {
     float a[8];
     if (n == 8 && avec) {
