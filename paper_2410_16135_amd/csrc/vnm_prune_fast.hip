@@ -406,7 +406,7 @@ int launch_prune_fast_scored(const void* W, int64_t ldw, const void* S, int64_t 
   a.R = d.R; a.B = d.B; a.S = d.S;
   a.Sc = (const float*)S; a.lds_s = lds_s;
   int k = 8;
-  while (k > 1 && prune_fast_lds(d.V, d.M, k, true) > 64 * 1024) k >>= 1;     // two workgroups per CU at least
+  while (k > 1 && prune_fast_lds(d.V, d.M, k, true) > 40 * 1024) k >>= 1;     // four workgroups per CU
   a.KSW = k;
   const int chunks = a.KSW * d.M;
   a.G = 256 / chunks < d.V ? 256 / chunks : d.V;

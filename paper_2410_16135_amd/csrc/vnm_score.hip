@@ -118,7 +118,7 @@ ria_score_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, 
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     cd[e] = e < nc ? (double)colsum[col + e] : 0.0;
-    ad[e] = e < nc ? (double)act[col + e] : 0.0;
+    ad[e] = e < nc ? (double)act[col + e] * 0x1p136 : 0.0;
     cy[e] = cd[e] > 0.0 ? 1.0 / cd[e] : 0.0;          // a zero sum: every quotient of its terms is 0
   }
   for (int64_t row0 = (int64_t)blockIdx.y * kScoreRows; row0 < out; row0 += (int64_t)gridDim.y * kScoreRows) {
@@ -135,7 +135,9 @@ ria_score_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, 
       const double rd = rsum[v], ry = rrec[v];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const double a = (double)sc_fp16_units(h[e]);
+        // the 15 magnitude bits read as fp32 are the magnitude times 2^-112 (subnormals and the top exponent
+        // included): units times 2^-136, a scale that act takes back exactly
+        const double a = (double)__uint_as_float((unsigned)(h[e] & 0x7FFFu) << 13);
         const double sum = sc_div(a, cd[e], cy[e]) + sc_div(a, rd, ry);
         sc[e] = (float)(sum * ad[e]);
       }
