@@ -149,7 +149,7 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 // Nothing but the two waits stands between the fourth and the fifth MFMA: the barrier brings the
 // two waves of a SIMD to the same point of the step, so whatever is issued next to it is issued by
 // both while the matrix pipe has nothing queued (measured: 800 -> 775 clocks per step).
-#define VNM_ASM_STEP(CW0, CW1, CIDX, NPC, LW0, LW1, LIDX, LPC, COPY_A, COPY_B, VMWSTR)             \
+#define VNM_ASM_STEP(CW0, CW1, CIDX, NPC, LW0, LW1, LIDX, LPC, COPY_A, COPY_B, VMWSTR, NEXT_IMG)   \
       "s_waitcnt lgkmcnt(4)\n s_nop 0\n"                                                          \
       "v_smfmac_f32_32x32x32_f16 %[a00], v[" CW0 "], v[192:199], v" CIDX "\n"                     \
       "global_load_dwordx4 v[" LW0 "], %[voff16], s[80:81]\n"                                     \
@@ -179,7 +179,7 @@ typedef float f16v __attribute__((ext_vector_type(16)));
       VNM_ASM_READ2(0, 196, 188, 198, 189)                                                        \
       COPY_B                                                                                      \
       "s_add_u32 %[wr], %[wr], %[img]\n s_cmp_eq_u32 %[wr], %[lend]\n s_cselect_b32 %[wr], %[lbeg], %[wr]\n" \
-      "s_add_u32 s86, s86, %[img]\n s_addc_u32 s87, s87, 0\n"                                     \
+      NEXT_IMG                                                                                    \
       "s_waitcnt lgkmcnt(4)\n s_nop 0\n"                                                          \
       "v_smfmac_f32_32x32x32_f16 %[a03], v[" CW0 "], v[216:223], v" CIDX "\n"                     \
       VNM_ASM_READ2(64, 200, 186, 202, 187)                                                       \
@@ -203,9 +203,9 @@ typedef float f16v __attribute__((ext_vector_type(16)));
       VNM_ASM_READ4(0, 192, 194, 196, 198)                                                        \
       VNM_ASM_READ4(64, 200, 202, 204, 206)                                                       \
       "1:\n"                                                                                \
-      VNM_ASM_STEP("224:227", "228:231", "232", "243", "244:247", "248:251", "252", "253", COPY_A, COPY_B, VMWSTR) \
-      VNM_ASM_STEP("234:237", "238:241", "242", "253", "224:227", "228:231", "232", "233", COPY_A, COPY_B, VMWSTR) \
-      VNM_ASM_STEP("244:247", "248:251", "252", "233", "234:237", "238:241", "242", "243", COPY_A, COPY_B, VMWSTR) \
+      VNM_ASM_STEP("224:227", "228:231", "232", "243", "244:247", "248:251", "252", "253", COPY_A, COPY_B, VMWSTR, VNM_ASM_NEXT_IMG) \
+      VNM_ASM_STEP("234:237", "238:241", "242", "253", "224:227", "228:231", "232", "233", COPY_A, COPY_B, VMWSTR, VNM_ASM_NEXT_IMG) \
+      VNM_ASM_STEP("244:247", "248:251", "252", "233", "234:237", "238:241", "242", "243", COPY_A, COPY_B, VMWSTR, VNM_ASM_NEXT_IMG) \
       "s_branch 1b\n"                                                                             \
       "9:\n"                                                                                      \
       "s_waitcnt vmcnt(0) lgkmcnt(0)\n"                                                           \
@@ -220,6 +220,63 @@ typedef float f16v __attribute__((ext_vector_type(16)));
         [woff] "s"(l_woff), [clamp] "s"(l_clamp), [pitch] "s"(l_pitch), [img] "s"(l_img),         \
         [lbeg] "s"(l_lbeg), [lend] "s"(l_lend)                                                    \
       : "memory", "scc", "m0",                                                                    \
+        "v186", "v187", "v188", "v189", "v190", "v191",                                           \
+        "v192", "v193", "v194", "v195", "v196", "v197", "v198", "v199", "v200", "v201", "v202", "v203", \
+        "v204", "v205", "v206", "v207", "v208", "v209", "v210", "v211", "v212", "v213", "v214", "v215", \
+        "v216", "v217", "v218", "v219", "v220", "v221", "v222", "v223", "v224", "v225", "v226", "v227", \
+        "v228", "v229", "v230", "v231", "v232", "v233", "v234", "v235", "v236", "v237", "v238", "v239", \
+        "v240", "v241", "v242", "v243", "v244", "v245", "v246", "v247", "v248", "v249", "v250", "v251", \
+        "v252", "v253",                                                                           \
+        "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89")
+
+// The same loop with six A register sets and a ring of six images: operands are requested five steps
+// ahead instead of two and three, for launches that do not fill the chip (see launch_spmm_smfmac).
+// Sets 3-5:
+//   v[148:151] v[152:155] v156 v157, v[158:161] v[162:165] v166 v167, v[168:171] v[172:175] v176 v177
+// The image pointer stops at the workgroup's last image (five images would reach past the three that
+// the staged buffer carries as slack); what is copied again there is never used.
+#define VNM_ASM_NEXT_IMG "s_add_u32 s86, s86, %[img]\n s_addc_u32 s87, s87, 0\n"
+#define VNM_ASM_NEXT_IMG_DEEP                                                                     \
+      "s_cmp_ge_u32 %[n], 7\n s_cselect_b32 %[tci], %[img], 0\n"                                  \
+      "s_add_u32 s86, s86, %[tci]\n s_addc_u32 s87, s87, 0\n"
+#define VNM_ASM_LOOP_DEEP(COPY_A, COPY_B, VMWSTR)                                                 \
+  asm volatile(                                                                                   \
+      "s_mov_b32 s80, %[pa_lo]\n s_mov_b32 s81, %[pa_hi]\n"                                       \
+      "s_mov_b32 s82, %[pi_lo]\n s_mov_b32 s83, %[pi_hi]\n"                                       \
+      "s_mov_b32 s84, %[pc_lo]\n s_mov_b32 s85, %[pc_hi]\n"                                       \
+      "s_mov_b32 s86, %[xs_lo]\n s_mov_b32 s87, %[xs_hi]\n"                                       \
+      VNM_ASM_LOAD_A("224:227", "228:231", "232", "233") \
+      VNM_ASM_LOAD_A("234:237", "238:241", "242", "243") \
+      VNM_ASM_LOAD_A("244:247", "248:251", "252", "253") \
+      VNM_ASM_LOAD_A("148:151", "152:155", "156", "157") \
+      VNM_ASM_LOAD_A("158:161", "162:165", "166", "167") \
+      "s_waitcnt vmcnt(0) lgkmcnt(0)\n"                                                           \
+      "s_barrier\n"                                                                               \
+      VNM_ASM_ADDR("233")                                                                         \
+      VNM_ASM_READ4(0, 192, 194, 196, 198)                                                        \
+      VNM_ASM_READ4(64, 200, 202, 204, 206)                                                       \
+      "1:\n"                                                                                \
+      VNM_ASM_STEP("224:227", "228:231", "232", "243", "168:171", "172:175", "176", "177", COPY_A, COPY_B, VMWSTR, VNM_ASM_NEXT_IMG_DEEP) \
+      VNM_ASM_STEP("234:237", "238:241", "242", "253", "224:227", "228:231", "232", "233", COPY_A, COPY_B, VMWSTR, VNM_ASM_NEXT_IMG_DEEP) \
+      VNM_ASM_STEP("244:247", "248:251", "252", "157", "234:237", "238:241", "242", "243", COPY_A, COPY_B, VMWSTR, VNM_ASM_NEXT_IMG_DEEP) \
+      VNM_ASM_STEP("148:151", "152:155", "156", "167", "244:247", "248:251", "252", "253", COPY_A, COPY_B, VMWSTR, VNM_ASM_NEXT_IMG_DEEP) \
+      VNM_ASM_STEP("158:161", "162:165", "166", "177", "148:151", "152:155", "156", "157", COPY_A, COPY_B, VMWSTR, VNM_ASM_NEXT_IMG_DEEP) \
+      VNM_ASM_STEP("168:171", "172:175", "176", "233", "158:161", "162:165", "166", "167", COPY_A, COPY_B, VMWSTR, VNM_ASM_NEXT_IMG_DEEP) \
+      "s_branch 1b\n"                                                                             \
+      "9:\n"                                                                                      \
+      "s_waitcnt vmcnt(0) lgkmcnt(0)\n"                                                           \
+      "s_barrier\n"                                                                               \
+      VNM_ASM_MFMA_DRAIN                                                                          \
+      : [a00] "+v"(acc[0][0]), [a01] "+v"(acc[0][1]), [a02] "+v"(acc[0][2]), [a03] "+v"(acc[0][3]), \
+        [a10] "+v"(acc[1][0]), [a11] "+v"(acc[1][1]), [a12] "+v"(acc[1][2]), [a13] "+v"(acc[1][3]), \
+        [rd] "+&s"(l_rd), [wr] "+&s"(l_wr), [n] "+&s"(l_n), [tci] "=&s"(l_tci)                    \
+      : [pa_lo] "s"(l_pa_lo), [pa_hi] "s"(l_pa_hi), [pi_lo] "s"(l_pi_lo), [pi_hi] "s"(l_pi_hi),   \
+        [pc_lo] "s"(l_pc_lo), [pc_hi] "s"(l_pc_hi), [xs_lo] "s"(l_xs_lo), [xs_hi] "s"(l_xs_hi),   \
+        [voff16] "v"(l_voff16), [voffi] "v"(l_voffi), [voffp] "v"(l_voffp), [vtok] "v"(l_vtok),   \
+        [woff] "s"(l_woff), [clamp] "s"(l_clamp), [pitch] "s"(l_pitch), [img] "s"(l_img),         \
+        [lbeg] "s"(l_lbeg), [lend] "s"(l_lend)                                                    \
+      : "memory", "scc", "m0",                                                                    \
+        "v148", "v149", "v150", "v151", "v152", "v153", "v154", "v155", "v156", "v157", "v158", "v159", "v160", "v161", "v162", "v163", "v164", "v165", "v166", "v167", "v168", "v169", "v170", "v171", "v172", "v173", "v174", "v175", "v176", "v177", \
         "v186", "v187", "v188", "v189", "v190", "v191",                                           \
         "v192", "v193", "v194", "v195", "v196", "v197", "v198", "v199", "v200", "v201", "v202", "v203", \
         "v204", "v205", "v206", "v207", "v208", "v209", "v210", "v211", "v212", "v213", "v214", "v215", \
@@ -367,6 +424,7 @@ struct SpmmArgs {
   int64_t ks_steps, z_stride;
   // fused epilogue (null = none): bias per weight row, destination channel per weight row
   const _Float16* bias; const int* perm_out;
+  int tiles_per_xcd; // 1: the token tiles of one (row group, K piece) run on one XCD, see launch_spmm_smfmac
 };
 
 // One K step = 8 column blocks = 8*M raw input columns = 32 compacted K = one staged image.
@@ -388,11 +446,24 @@ spmm_smfmac_kernel(const SpmmArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave / WT, wt = wave % WT;
-  const int64_t r = (int64_t)blockIdx.y * WR + wr;
+  // Workgroup n of the launch runs on XCD n mod 8, each with an L2 of its own.  With tiles_per_xcd the
+  // workgroups of one XCD take consecutive (K piece, row group, token tile) triples, tiles fastest.
+  unsigned tile_id = blockIdx.x, group_id = blockIdx.y, piece_id = blockIdx.z;
+  if (a.tiles_per_xcd) {
+    const unsigned n = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    const unsigned total = gridDim.x * gridDim.y * gridDim.z, xcd = n & 7, each = total >> 3, rest = total & 7;
+    const unsigned id = xcd * each + (xcd < rest ? xcd : rest) + (n >> 3);
+    const unsigned pair = id / gridDim.x;
+    // (a division is done on the vector unit: back to scalars)
+    tile_id = __builtin_amdgcn_readfirstlane(id - pair * gridDim.x);
+    group_id = __builtin_amdgcn_readfirstlane(pair % gridDim.y);
+    piece_id = __builtin_amdgcn_readfirstlane(pair / gridDim.y);
+  }
+  const int64_t r = (int64_t)group_id * WR + wr;
   const bool r_valid = r < a.R;
   const int64_t rr = r_valid ? r : a.R - 1;      // out-of-range waves compute a valid row block, store nothing
-  const int64_t t0 = (int64_t)blockIdx.x * kTokTile;
-  const int64_t s0 = (int64_t)blockIdx.z * a.ks_steps;
+  const int64_t t0 = (int64_t)tile_id * kTokTile;
+  const int64_t s0 = (int64_t)piece_id * a.ks_steps;
   const int64_t S = (a.S - s0) < a.ks_steps ? (a.S - s0) : a.ks_steps;   // steps of this workgroup
   const int64_t rs0 = rr * a.S + s0;                                      // its first (row block, step)
   const int img = a.image_bytes;
@@ -412,7 +483,7 @@ spmm_smfmac_kernel(const SpmmArgs a) {
   const unsigned lds0 = (unsigned)(size_t)(VNM_LDS(unsigned char))smem;
   const unsigned tokoff = (unsigned)((wt * TW + tg * 16 + q * 4) * 2);
 
-  const unsigned char* xs_tile = a.Xs + ((int64_t)blockIdx.x * a.S + s0) * img;
+  const unsigned char* xs_tile = a.Xs + ((int64_t)tile_id * a.S + s0) * img;
   // copy this wave's share of image s into ring slot `slot`; chunks beyond the image are clamped to
   // its last chunk (an idempotent duplicate) so that every wave issues the same number of copies
   auto copy_image = [&](int64_t s, int slot) {
@@ -452,19 +523,21 @@ spmm_smfmac_kernel(const SpmmArgs a) {
       unsigned l_n = (unsigned)n_steady;
       // VMW = operations that may stay in flight at a step's wait: the 4 loads of A(s+2) issued at
       // its start and, with a ring of 4, the NCW copies issued after the previous step's barrier
-      // (with a ring of 3 those copies are image s+1 itself and must have landed)
-#define VNM_GO(W, N, VM3, VM4)                                                    \
+      // (with a ring of 3 those copies are image s+1 itself and must have landed); with the ring of 6 image
+      // s+1 was requested before the loads of four steps and the copies of three
+#define VNM_GO(W, N, VM3, VM4, VM6)                                               \
       if constexpr (NW == W && NCW == N && !DUAL) {                              \
-        if constexpr (NBUF == 4) VNM_ASM_LOOP_V64(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM4);  \
+        if constexpr (NBUF == 6) VNM_ASM_LOOP_DEEP(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM6);  \
+        else if constexpr (NBUF == 4) VNM_ASM_LOOP_V64(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM4);  \
         else VNM_ASM_LOOP_V64(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM3);         \
       }                                                                          \
       if constexpr (NW == W && NCW == N && DUAL) {                               \
         if constexpr (NBUF == 4) VNM_ASM_LOOP_D(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM4);    \
         else VNM_ASM_LOOP_D(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM3);           \
       }
-      VNM_GO(4, 3, "4", "7") VNM_GO(4, 4, "4", "8") VNM_GO(4, 5, "4", "9") VNM_GO(4, 6, "4", "10")
-      VNM_GO(4, 7, "4", "11") VNM_GO(4, 8, "4", "12") VNM_GO(4, 9, "4", "13") VNM_GO(4, 10, "4", "14")
-      VNM_GO(8, 2, "4", "6") VNM_GO(8, 3, "4", "7") VNM_GO(8, 4, "4", "8") VNM_GO(8, 5, "4", "9")
+      VNM_GO(4, 3, "4", "7", "25") VNM_GO(4, 4, "4", "8", "28") VNM_GO(4, 5, "4", "9", "31") VNM_GO(4, 6, "4", "10", "34")
+      VNM_GO(4, 7, "4", "11", "37") VNM_GO(4, 8, "4", "12", "40") VNM_GO(4, 9, "4", "13", "43") VNM_GO(4, 10, "4", "14", "46")
+      VNM_GO(8, 2, "4", "6", "22") VNM_GO(8, 3, "4", "7", "25") VNM_GO(8, 4, "4", "8", "28") VNM_GO(8, 5, "4", "9", "31")
 #undef VNM_GO
     }
   }
@@ -514,7 +587,7 @@ spmm_smfmac_kernel(const SpmmArgs a) {
     constexpr int LPT = V / 8;                            // lanes per token row (16 bytes each)
     constexpr int TPI = 64 / LPT;                         // token rows per wave-wide store
     const int ch = lane % LPT, tl = lane / LPT;
-    _Float16* Yh = (_Float16*)a.Y + (int64_t)blockIdx.z * a.z_stride;
+    _Float16* Yh = (_Float16*)a.Y + (int64_t)piece_id * a.z_stride;
 #pragma unroll
     for (int it = 0; it < TW / TPI; ++it) {
       const int tk = it * TPI + tl;
@@ -588,8 +661,8 @@ spmm_smfmac_kernel(const SpmmArgs a) {
         const int64_t o = r * V + i * 32 + 8 * jq + 4 * hB;
         const float v0 = acc[i][j][4 * jq], v1 = acc[i][j][4 * jq + 1], v2 = acc[i][j][4 * jq + 2],
                     v3 = acc[i][j][4 * jq + 3];
-        if (a.y_fp32) store4((float*)a.Y + (int64_t)blockIdx.z * a.z_stride + tok * a.ldy + o, o, v0, v1, v2, v3);
-        else store4((_Float16*)a.Y + (int64_t)blockIdx.z * a.z_stride + tok * a.ldy + o, o, v0, v1, v2, v3);
+        if (a.y_fp32) store4((float*)a.Y + (int64_t)piece_id * a.z_stride + tok * a.ldy + o, o, v0, v1, v2, v3);
+        else store4((_Float16*)a.Y + (int64_t)piece_id * a.z_stride + tok * a.ldy + o, o, v0, v1, v2, v3);
       }
     }
   }
@@ -637,6 +710,23 @@ static int launch_v64_w4(const SpmmArgs& a, hipStream_t st) {
   }
   return VNM_ERR_UNSUPPORTED;
 }
+// the deep loop (ring of 6, M <= 9)
+static int launch_deep(const SpmmArgs& a, bool wide, hipStream_t st) {
+  if (wide) {
+    switch ((a.image_bytes / 1024 + 7) / 8) {
+      case 2: return launch_cfg<64, 128, 8, 1, 2, 6, false>(a, st);
+      case 3: return launch_cfg<64, 128, 8, 1, 3, 6, false>(a, st);
+    }
+    return VNM_ERR_UNSUPPORTED;
+  }
+  switch ((a.image_bytes / 1024 + 3) / 4) {
+    case 3: return launch_cfg<64, 128, 4, 1, 3, 6, false>(a, st);
+    case 4: return launch_cfg<64, 128, 4, 1, 4, 6, false>(a, st);
+    case 5: return launch_cfg<64, 128, 4, 1, 5, 6, false>(a, st);
+    case 6: return launch_cfg<64, 128, 4, 1, 6, 6, false>(a, st);
+  }
+  return VNM_ERR_UNSUPPORTED;
+}
 template <int NBUF, bool DUAL>
 static int launch_v64_w8(const SpmmArgs& a, hipStream_t st) {
   const int ncw = (a.image_bytes / 1024 + 7) / 8;
@@ -671,6 +761,64 @@ splitk_reduce_kernel(const float* __restrict__ part, int KS, int64_t T, int64_t 
   if (bias) acc += (float)bias[o];
   const int64_t dst = perm_out ? (int64_t)perm_out[o] : o;
   if (dst >= 0 && dst < out) Y[t * ldy + dst] = (OutT)acc;
+}
+
+// The same sums, 4 adjacent channels of one token per thread: 16-byte loads, no division (grid x runs over a row).
+// Bound by reading the parts: 700 tokens x 4096 channels in two parts 8.9 -> 5.8 us.
+template <typename OutT>
+__global__ void __launch_bounds__(256)
+splitk_reduce4_kernel(const float* __restrict__ part, int KS, int64_t T, int64_t out, OutT* __restrict__ Y, int64_t ldy, int vec_store,
+                      const _Float16* __restrict__ bias, const int* __restrict__ perm_out) {
+  typedef OutT o4 __attribute__((ext_vector_type(4)));
+  const int64_t o = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (o >= out) return;
+  const int64_t zs = T * out;
+  for (int64_t t = blockIdx.y; t < T; t += gridDim.y) {
+    const float* p = part + t * out + o;
+    f4 acc = 0.f;
+    int z = 0;
+    for (; z + 4 <= KS; z += 4) {
+      const f4 a0 = *(const f4*)(p + (int64_t)z * zs), a1 = *(const f4*)(p + (int64_t)(z + 1) * zs),
+               a2 = *(const f4*)(p + (int64_t)(z + 2) * zs), a3 = *(const f4*)(p + (int64_t)(z + 3) * zs);
+      acc += (a0 + a1) + (a2 + a3);
+    }
+    if (z + 2 <= KS) {
+      const f4 a0 = *(const f4*)(p + (int64_t)z * zs), a1 = *(const f4*)(p + (int64_t)(z + 1) * zs);
+      acc += a0;
+      acc += a1;
+      z += 2;
+    }
+    if (z < KS) acc += *(const f4*)(p + (int64_t)z * zs);
+    if (bias)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] += (float)bias[o + e];
+    if (vec_store && !perm_out) {
+      o4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = (OutT)acc[e];
+      *(o4*)(Y + t * ldy + o) = v;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t dst = perm_out ? (int64_t)perm_out[o + e] : o + e;
+        if (dst >= 0 && dst < out) Y[t * ldy + dst] = (OutT)acc[e];
+      }
+    }
+  }
+}
+
+// Below 2^19 results the launch is what counts, and one result per thread spreads it wider: a 4096 / 11008 block at
+// 24 tokens (three reductions) 73.7 us with that kernel, 74.2 with the other.
+template <typename OutT>
+static void launch_reduce(const float* part, int KS, int64_t T, int64_t out, OutT* Y, int64_t ldy, const Fused& f, hipStream_t st) {
+  if (out % 4 == 0 && ((uintptr_t)part & 15) == 0 && T * out >= (1 << 19)) {
+    const int vec_store = ldy % 4 == 0 && ((uintptr_t)Y % (4 * sizeof(OutT))) == 0;
+    const dim3 grid((unsigned)((out / 4 + 255) / 256), (unsigned)(T < 65535 ? T : 65535));
+    hipLaunchKernelGGL(splitk_reduce4_kernel<OutT>, grid, dim3(256), 0, st, part, KS, T, out, Y, ldy, vec_store, f.bias, f.perm_out);
+  } else {
+    hipLaunchKernelGGL(splitk_reduce_kernel<OutT>, dim3((unsigned)((T * out + 255) / 256)), dim3(256), 0, st, part, KS, T, out, Y,
+                       ldy, f.bias, f.perm_out);
+  }
 }
 
 constexpr int64_t kSplitKMaxTokens = 2048;
@@ -718,10 +866,12 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
     // up to 256 tokens: about 200 workgroups measured best.  Beyond that the partial products (ks x T x
     // out floats written, then read by the reduction) weigh in: about 256 workgroups while fewer than
     // half the CUs would have one, and a split in two only where the K loop is long enough to pay
-    // for the reduction (measured: 276 K steps gain 19 %, 103 steps lose 10 %)
+    // for the reduction.  At exactly half the CUs a split in two fills them without a second generation:
+    // 4096 x 4096 at 1024 tokens, 103 steps, 43.2 -> 36.5 us; 2048 x 5504 at 2048 tokens, 138 steps, 52.7 -> 41.4;
+    // 64 steps gain nothing (33.8 against 34.6).  Above, pieces share CUs: 192 pairs of 103 steps 43.4 against 51.0.
     int64_t ks = 1;
     if (T <= 256) ks = (200 + base / 2) / base;
-    else if (base < 128) ks = 256 / base;
+    else if (base < 128 || (base == 128 && d.S >= 96)) ks = 256 / base;
     else if (d.S >= 192) ks = 2;
     if (ks > 16) ks = 16;
     if (ks > d.S / 4) ks = d.S / 4;                                   // at least 4 K steps each
@@ -742,11 +892,26 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
   const int y_elem = y_dtype == 0 ? 2 : 4;
   const bool post_permute = KS == 1 && f.perm_out && d.out * y_elem <= permute_rows_max_bytes();
   if (post_permute) a.perm_out = nullptr;
+  // Which operand each XCD's L2 fetches for itself: in grid order the weight (every XCD meets every row
+  // group), with the tiles of a row group on one XCD the staged X.  The latter where the weight is
+  // clearly the larger of the two: 4096 x 11008 at M = 5 42.8 -> 34.4 us at 320 tokens, 60.3 -> 56.6 at 700,
+  // 104 against 104 at 1500 (both 42 MB), 130 -> 136 at 3000; 11008 x 4096 48.0 -> 45.3 at 700, 113 against 112 at
+  // 2048, 168 -> 175 at 3000; 4096 x 4096 64.9 -> 71.7 at 4096.
+  a.tiles_per_xcd = 10 * (pl.pcol_off - pl.pa_off) > 14 * tiles * d.S * a.image_bytes && tiles * a.R * d.S < (1ll << 31);
   a.wide_store = (a.y_fp32 == 0) && (a.ldy % 8 == 0) && (((uintptr_t)a.Y & 15) == 0);
   a.vec_store = (a.ldy % 4 == 0) && (((uintptr_t)a.Y & (a.y_fp32 == 0 ? 7 : 15)) == 0);
   int rc = VNM_ERR_UNSUPPORTED;
   const bool ring4 = 4 * (size_t)a.image_bytes <= 150 * 1024;
-  if (!dual) {
+  // The deep loop where the launch leaves compute units without a workgroup: a step then waits for its operands
+  // rather than for the matrix cores.  Seven layers of a 4096 / 11008 block at 700 tokens, M = 5, weights from HBM:
+  // 399 -> 383 us; with all compute units busy (4096 tokens) 914 against 915, with one layer's weight in L2 no
+  // difference either way.  Six images fit LDS up to M = 9.  It looks five steps ahead: at least 8 steps per piece (its first ring of images), and
+  // 64 steps in all (its last loads of the weight end inside the sections behind it).
+  const int64_t last_piece = d.S - (int64_t)(KS - 1) * a.ks_steps;
+  const int64_t workgroups = tiles * (wide ? (a.R + 7) / 8 : (a.R + 3) / 4) * KS;
+  const bool deep6 = !dual && workgroups < 256 && d.M <= 9 && last_piece >= 8 && a.R * d.S >= 64;
+  if (deep6) rc = launch_deep(a, wide, st);
+  else if (!dual) {
     if (wide) rc = ring4 ? launch_v64_w8<4, false>(a, st) : launch_v64_w8<3, false>(a, st);
     else rc = deep ? launch_v64_w4<4, false>(a, st) : launch_v64_w4<3, false>(a, st);
   } else {
@@ -761,13 +926,8 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
 
 int launch_splitk_reduce(const void* part, int KS, int64_t T, int64_t out, void* Y, int64_t ldy,
                          int y_dtype, const Fused& f, hipStream_t st) {
-  const int64_t n = T * out;
-  if (y_dtype == 0)
-    hipLaunchKernelGGL(splitk_reduce_kernel<_Float16>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                       (const float*)part, KS, T, out, (_Float16*)Y, ldy, f.bias, f.perm_out);
-  else
-    hipLaunchKernelGGL(splitk_reduce_kernel<float>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                       (const float*)part, KS, T, out, (float*)Y, ldy, f.bias, f.perm_out);
+  if (y_dtype == 0) launch_reduce((const float*)part, KS, T, out, (_Float16*)Y, ldy, f, st);
+  else launch_reduce((const float*)part, KS, T, out, (float*)Y, ldy, f, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "splitk_reduce_kernel"); return VNM_ERR_HIP; }
   return VNM_OK;

@@ -1,0 +1,33 @@
+"""The staged product between a few and a few thousand tokens: both numberings of its workgroups over the XCDs,
+the K split and its reduction, at the edges of the rules that choose them."""
+
+import pytest
+import torch
+
+import paper_2410_16135_amd as vnm
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+# weight larger than X (tiles of a row group together) and smaller, numbers of workgroups that 8 does not divide,
+# exactly 128 (tile, row group) pairs with and without enough K steps, out not a multiple of 4 (scalar reduction),
+# one token past a tile; the deep K loop at its largest M, the next M, its fewest steps per piece and one below
+@pytest.mark.parametrize("out,inn,T,V,M", [
+    (4096, 1024, 257, 64, 4), (1100, 2048, 385, 64, 4), (640, 4096, 129, 128, 5), (4096, 3840, 1024, 64, 5),
+    (1030, 3080, 700, 32, 5), (513, 4096, 300, 64, 8), (2048, 768, 2048, 64, 8), (1026, 8192, 260, 64, 16),
+    (520, 2000, 300, 64, 9), (2064, 3000, 900, 128, 9), (520, 2000, 300, 64, 10), (2560, 256, 2049, 64, 4), (2560, 224, 2049, 64, 4)])
+@pytest.mark.parametrize("ydt", [torch.float16, torch.float32])
+def test_staged_product(out, inn, T, V, M, ydt):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(out + T)
+    c = vnm.vnm_prune_compress((torch.randn((out, inn), generator=g, device=DEV) * 0.02).half(), V, M)
+    X = torch.randn((T, inn), generator=g, device=DEV).half()
+    Y = vnm.vnm_spmm_staged(vnm.vnm_stage_x(X, M), T, c, out_dtype=ydt)
+    W = vnm.vnm_decompress(c).double()
+    want, mag = X.double() @ W.t(), X.double().abs() @ W.abs().t()
+    # 2 kept products per block, at most 16 K pieces, each addition rounded in fp32; then the rounding of the result
+    bound = (2 * -(-inn // M) + 32) * 2.0 ** -24 * mag
+    if ydt == torch.float16:
+        bound = bound + 2.0 ** -11 * want.abs() + 2.0 ** -24
+    assert bool(((Y.double() - want).abs() <= bound).all())
