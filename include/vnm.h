@@ -69,7 +69,7 @@ typedef struct vnm_sizes {
 /* Which kernel vnm_spmm uses. */
 typedef enum vnm_spmm_path {
   VNM_PATH_AUTO = 0,       /* sparse matrix-core kernel when `packed` is given and the shape allows, else generic */
-  VNM_PATH_GENERIC = 1,    /* scalar kernel on the canonical triple; any V, M, alignment */
+  VNM_PATH_GENERIC = 1,    /* scalar kernel on the canonical triple; any V, M, alignment (a cross-check: slow) */
   VNM_PATH_SMFMAC = 2      /* 2:4 sparse MFMA kernel on `packed`; fails with UNSUPPORTED if not applicable */
 } vnm_spmm_path;
 
@@ -258,7 +258,7 @@ int vnm_spmm_scratch_bytes(int64_t T, int64_t out, int64_t* bytes);
 /*
  * Host only.  Which kernel vnm_spmm (VNM_PATH_AUTO, `packed` given, X aligned as the matrix-core
  * kernels need it, no input permutation) runs for T tokens with a workspace of the given size:
- *   VNM_KERNEL_GENERIC     scalar kernel (no matrix-core copy for this V, M, or in % 8 != 0)
+ *   VNM_KERNEL_GENERIC     kernels on the canonical triple (no matrix-core copy for this V, M, or in % 8 != 0)
  *   VNM_KERNEL_FEW_TOKENS  no staging pass, X token-major in LDS (one to four tokens: a stream through the vector
  *                          ALUs): T <= 32 always; up to 256 tokens where one workgroup per (row blocks, group of 16
  *                          or 32 tokens, piece of K) fits the compute units at once (with the workspace that

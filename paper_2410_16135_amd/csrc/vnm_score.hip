@@ -17,79 +17,94 @@ __device__ __forceinline__ unsigned long long sc_fp16_units(unsigned short h) {
   return e ? ((unsigned long long)(1024u + m) << (e - 1)) : (unsigned long long)m;
 }
 
-__global__ void __launch_bounds__(256) zero_u64_kernel(unsigned long long* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
-// Column and row sums in one pass over W.  A workgroup owns 128 rows x 256 columns; thread (q, c) owns 8
-// adjacent columns (one 16-byte load per row) and the rows q, q + 8, ....  Its partial sums meet those of
-// the other threads in LDS and leave as one 64-bit integer atomic per row and column of the tile: integer
-// sums do not depend on their order.  Bound by the read of W.  (Before: one workgroup per 64 columns
-// walked all rows, 34 us on 4096 x 4096 with 64 workgroups on 256 compute units, and a second kernel read
-// W again for the row sums, 10 us.)  `vec` = rows are 16-byte aligned; otherwise 2-byte loads.
-constexpr int kSumRows = 128, kSumCols = 256;
-
-__global__ void __launch_bounds__(256)
-abs_sums_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, int64_t ldw, int vec,
-                unsigned long long* __restrict__ colsum, unsigned long long* __restrict__ rowsum) {
-  __shared__ unsigned long long rpart[kSumRows][33];
-  __shared__ unsigned long long cpart[8][kSumCols];
-  const int c = threadIdx.x & 31, q = threadIdx.x >> 5;
-  const int64_t col = (int64_t)blockIdx.x * kSumCols + c * 8;
-  const int64_t row0 = (int64_t)blockIdx.y * kSumRows + q;
+// Column sums: a workgroup owns 64 columns and walks all rows.  Thread (c, q) owns 8 adjacent columns
+// (one 16-byte load per row: with 8 such threads a row of the strip is one 128-byte line) and the rows
+// q, q + 128, ..., eight of them in flight; the 128 partial sums of a column meet in the wave and in LDS and
+// one thread stores their total, so every sum is written once, by one thread, without atomics.  Bound by what
+// one compute unit can fetch: with 256 threads and four rows in flight 34 us on 4096 x 4096, now 25.  `vec` = rows are 16-byte
+// aligned; otherwise 2-byte loads.
+__global__ void __launch_bounds__(1024)
+abs_colsum_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, int64_t ldw, int vec,
+                  unsigned long long* __restrict__ colsum) {
+  __shared__ unsigned long long part[16][64];
+  const int c = threadIdx.x & 7, q = threadIdx.x >> 3, wave = threadIdx.x >> 6;
+  const int64_t col = ((int64_t)blockIdx.x * 8 + c) * 8;
   const int nc = col >= in ? 0 : (int)((in - col) < 8 ? (in - col) : 8);
-  constexpr int kU = kSumRows / 8;
   unsigned long long acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (vec && nc == 8) {
-    // all 16 rows in flight: rows beyond the last repeat it and count as zero
-    uint4 v[kU];
+  if (nc > 0) {
+    if (vec && nc == 8) {
+      constexpr int kU = 8;                                   // rows in flight per thread
+      for (int64_t row = q; row < out; row += 128 * kU) {
+        uint4 v[kU];
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t rr = row0 + 8 * u;
-      v[u] = *(const uint4*)(W + (rr < out ? rr : out - 1) * ldw + col);
-    }
+        for (int u = 0; u < kU; ++u) {                        // rows beyond the last repeat it and count as zero
+          const int64_t rr = row + 128 * u;
+          v[u] = *(const uint4*)(W + (rr < out ? rr : out - 1) * ldw + col);
+        }
 #pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const bool ok = row0 + 8 * u < out;
-      const unsigned d[4] = {ok ? v[u].x : 0u, ok ? v[u].y : 0u, ok ? v[u].z : 0u, ok ? v[u].w : 0u};
-      unsigned long long s = 0;
+        for (int u = 0; u < kU; ++u) {
+          const bool ok = row + 128 * u < out;
+          const unsigned d[4] = {ok ? v[u].x : 0u, ok ? v[u].y : 0u, ok ? v[u].z : 0u, ok ? v[u].w : 0u};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const unsigned long long a = sc_fp16_units((unsigned short)(d[e] & 0xFFFFu)), b = sc_fp16_units((unsigned short)(d[e] >> 16));
-        acc[2 * e] += a; acc[2 * e + 1] += b;
-        s += a + b;
+          for (int e = 0; e < 4; ++e) {
+            acc[2 * e] += sc_fp16_units((unsigned short)(d[e] & 0xFFFFu));
+            acc[2 * e + 1] += sc_fp16_units((unsigned short)(d[e] >> 16));
+          }
+        }
       }
-      rpart[q + 8 * u][c] = s;
-    }
-  } else {
-    for (int u = 0; u < kU; ++u) {
-      const int64_t rr = row0 + 8 * u;
-      unsigned long long s = 0;
-      if (rr < out)
+    } else {
+      for (int64_t row = q; row < out; row += 128) {
+        const unsigned short* p = W + row * ldw + col;
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (e < nc) { const unsigned long long a = sc_fp16_units(W[rr * ldw + col + e]); acc[e] += a; s += a; }
-      rpart[q + 8 * u][c] = s;
+        for (int e = 0; e < 8; ++e) if (e < nc) acc[e] += sc_fp16_units(p[e]);
+      }
     }
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) cpart[q][c * 8 + e] = acc[e];
+  for (int e = 0; e < 8; ++e) {
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) {
+      const unsigned lo = __shfl_xor((unsigned)acc[e], o), hi = __shfl_xor((unsigned)(acc[e] >> 32), o);
+      acc[e] += ((unsigned long long)hi << 32) | lo;
+    }
+    if ((threadIdx.x & 63) < 8) part[wave][c * 8 + e] = acc[e];
+  }
   __syncthreads();
-  const int64_t gc = (int64_t)blockIdx.x * kSumCols + threadIdx.x;
-  unsigned long long t = 0;
+  if (threadIdx.x < 64) {
+    const int64_t gc = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    unsigned long long t = 0;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) t += cpart[k][threadIdx.x];
-  if (gc < in && t) atomicAdd(colsum + gc, t);
-  // two threads per row
-  const int lr = threadIdx.x >> 1, h = (threadIdx.x & 1) * 16;
-  unsigned long long s = 0;
+    for (int k = 0; k < 16; ++k) t += part[k][threadIdx.x];
+    if (gc < in) colsum[gc] = t;
+  }
+}
+
+// Row sums: one wave per row, lanes stride over the row 8 columns at a time, one reduction at the end.
+__global__ void __launch_bounds__(256)
+abs_rowsum_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, int64_t ldw, int vec,
+                  unsigned long long* __restrict__ rowsum) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= out) return;                                    // uniform over the wave
+  const unsigned short* p = W + row * ldw;
+  unsigned long long acc = 0;
+  for (int64_t c = (int64_t)lane * 8; c < in; c += 512) {
+    if (vec && c + 8 <= in) {
+      const uint4 v = *(const uint4*)(p + c);
+      const unsigned d[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-  for (int k = 0; k < 16; ++k) s += rpart[lr][h + k];
-  const unsigned lo = __shfl_xor((unsigned)s, 1), hi = __shfl_xor((unsigned)(s >> 32), 1);
-  s += ((unsigned long long)hi << 32) | lo;
-  const int64_t gr = (int64_t)blockIdx.y * kSumRows + lr;
-  if (h == 0 && gr < out && s) atomicAdd(rowsum + gr, s);
+      for (int e = 0; e < 4; ++e)
+        acc += sc_fp16_units((unsigned short)(d[e] & 0xFFFFu)) + sc_fp16_units((unsigned short)(d[e] >> 16));
+    } else {
+      for (int64_t e = c; e < in && e < c + 8; ++e) acc += sc_fp16_units(p[e]);
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned lo = __shfl_xor((unsigned)acc, o), hi = __shfl_xor((unsigned)(acc >> 32), o);
+    acc += ((unsigned long long)hi << 32) | lo;
+  }
+  if (lane == 0) rowsum[row] = acc;
 }
 
 // a / b rounded to nearest, from y = 1 / b rounded to nearest: q0 = a y is within 1.5 ulp, one correction
@@ -175,12 +190,10 @@ int launch_ria_scores(const void* W, int64_t out, int64_t in, int64_t ldw, const
   unsigned long long* colsum = (unsigned long long*)workspace;
   unsigned long long* rowsum = colsum + in;
   const int vec = (ldw % 8 == 0) && (((uintptr_t)W & 15) == 0);
-  hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)((in + out + 255) / 256)), dim3(256), 0, st, colsum, in + out);
-  for (int64_t o0 = 0; o0 < out; o0 += 65535ll * kSumRows) {      // grid.y limit
-    const int64_t rows = out - o0 < 65535ll * kSumRows ? out - o0 : 65535ll * kSumRows;
-    hipLaunchKernelGGL(abs_sums_kernel, dim3((unsigned)((in + kSumCols - 1) / kSumCols), (unsigned)((rows + kSumRows - 1) / kSumRows)),
-                       dim3(256), 0, st, (const unsigned short*)W + o0 * ldw, rows, in, ldw, vec, colsum, rowsum + o0);
-  }
+  hipLaunchKernelGGL(abs_colsum_kernel, dim3((unsigned)((in + 63) / 64)), dim3(1024), 0, st, (const unsigned short*)W, out, in,
+                     ldw, vec, colsum);
+  hipLaunchKernelGGL(abs_rowsum_kernel, dim3((unsigned)((out + 3) / 4)), dim3(256), 0, st, (const unsigned short*)W,
+                     out, in, ldw, vec, rowsum);
   const int vec_s = (ldw % 4 == 0) && (((uintptr_t)W & 7) == 0) && (lds % 4 == 0) && (((uintptr_t)S & 15) == 0);
   const int64_t gy = (out + kScoreRows - 1) / kScoreRows;
   hipLaunchKernelGGL(ria_score_kernel, dim3((unsigned)((in + 1023) / 1024), (unsigned)(gy < 65535 ? gy : 65535)), dim3(256), 0, st,
