@@ -163,12 +163,12 @@ ria_score_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, 
       for (int v = 0; v < kScoreRows; ++v) w[v] = *(const uint2*)(W + (row0 + (v < nr ? v : nr - 1)) * ldw + col);
 #pragma unroll
       for (int v = 0; v < kScoreRows; ++v) {
-        if (v >= nr) break;
         const unsigned short h[4] = {(unsigned short)(w[v].x & 0xFFFFu), (unsigned short)(w[v].x >> 16),
                                      (unsigned short)(w[v].y & 0xFFFFu), (unsigned short)(w[v].y >> 16)};
         float sc[4];
         scores(v, h, sc);
-        *(float4*)(S + (row0 + v) * lds + col) = make_float4(sc[0], sc[1], sc[2], sc[3]);
+        // (no break at the last row: the loop would stay a loop, and w would move to scratch memory)
+        if (v < nr) *(float4*)(S + (row0 + v) * lds + col) = make_float4(sc[0], sc[1], sc[2], sc[3]);
       }
     } else {
       for (int v = 0; v < nr; ++v) {
