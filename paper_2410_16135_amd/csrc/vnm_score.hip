@@ -8,6 +8,7 @@
 // the column L1 norms of the scores are added in fp64 one row after the other, a fixed order.
 #include <type_traits>
 #include "vnm_internal.h"
+#include "vnm_rules.h"
 
 namespace vnm {
 
@@ -19,31 +20,32 @@ __device__ __forceinline__ unsigned long long sc_fp16_units(unsigned short h) {
 
 // Column sums: a workgroup owns 64 columns and walks all rows.  Thread (c, q) owns 8 adjacent columns
 // (one 16-byte load per row: with 8 such threads a row of the strip is one 128-byte line) and the rows
-// q, q + 128, ..., eight of them in flight; the 128 partial sums of a column meet in the wave and in LDS and
-// one thread stores their total, so every sum is written once, by one thread, without atomics.  Bound by what
-// one compute unit can fetch: with 256 threads and four rows in flight 34 us on 4096 x 4096, now 25.  `vec` = rows are 16-byte
-// aligned; otherwise 2-byte loads.
-__global__ void __launch_bounds__(1024)
+// q, q + Q, ..., kU of them in flight (Q = 8 row groups per wave); the Q partial sums of a column meet in the wave
+// and in LDS and one thread stores their total, so every sum is written once, by one thread, without atomics.
+// `vec` = rows are 16-byte aligned; otherwise 2-byte loads.  Bound by what one compute unit can fetch (there are only
+// in / 64 workgroups); waves and rows in flight by colsum_shape.
+template <int WAVES, int kU>
+__global__ void __launch_bounds__(WAVES * 64)
 abs_colsum_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, int64_t ldw, int vec,
                   unsigned long long* __restrict__ colsum) {
-  __shared__ unsigned long long part[16][64];
+  __shared__ unsigned long long part[WAVES][64];
+  constexpr int Q = 8 * WAVES;                                // row groups
   const int c = threadIdx.x & 7, q = threadIdx.x >> 3, wave = threadIdx.x >> 6;
   const int64_t col = ((int64_t)blockIdx.x * 8 + c) * 8;
   const int nc = col >= in ? 0 : (int)((in - col) < 8 ? (in - col) : 8);
   unsigned long long acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   if (nc > 0) {
     if (vec && nc == 8) {
-      constexpr int kU = 8;                                   // rows in flight per thread
-      for (int64_t row = q; row < out; row += 128 * kU) {
+      for (int64_t row = q; row < out; row += Q * kU) {
         uint4 v[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {                        // rows beyond the last repeat it and count as zero
-          const int64_t rr = row + 128 * u;
+          const int64_t rr = row + Q * u;
           v[u] = *(const uint4*)(W + (rr < out ? rr : out - 1) * ldw + col);
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-          const bool ok = row + 128 * u < out;
+          const bool ok = row + Q * u < out;
           const unsigned d[4] = {ok ? v[u].x : 0u, ok ? v[u].y : 0u, ok ? v[u].z : 0u, ok ? v[u].w : 0u};
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -53,28 +55,35 @@ abs_colsum_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in,
         }
       }
     } else {
-      for (int64_t row = q; row < out; row += 128) {
+      for (int64_t row = q; row < out; row += Q) {
         const unsigned short* p = W + row * ldw + col;
 #pragma unroll
         for (int e = 0; e < 8; ++e) if (e < nc) acc[e] += sc_fp16_units(p[e]);
       }
     }
   }
+  // the 8 row groups of a wave (lanes 8 apart): in each of three steps a lane passes on half of its columns and
+  // keeps the other half, so that lane (c, q) ends with the wave's total of one column, c 8 + bits of q reversed
+  const int q0 = q & 1, q1 = (q >> 1) & 1, q2 = (q >> 2) & 1;
+  auto half = [&](int keep_upper, int o, auto count) {
+    constexpr int n = decltype(count)::value;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-#pragma unroll
-    for (int o = 8; o < 64; o <<= 1) {
-      const unsigned lo = __shfl_xor((unsigned)acc[e], o), hi = __shfl_xor((unsigned)(acc[e] >> 32), o);
-      acc[e] += ((unsigned long long)hi << 32) | lo;
+    for (int e = 0; e < n; ++e) {
+      const unsigned long long send = keep_upper ? acc[e] : acc[e + n], keep = keep_upper ? acc[e + n] : acc[e];
+      const unsigned lo = __shfl_xor((unsigned)send, o), hi = __shfl_xor((unsigned)(send >> 32), o);
+      acc[e] = keep + (((unsigned long long)hi << 32) | lo);
     }
-    if ((threadIdx.x & 63) < 8) part[wave][c * 8 + e] = acc[e];
-  }
+  };
+  half(q0, 8, std::integral_constant<int, 4>{});
+  half(q1, 16, std::integral_constant<int, 2>{});
+  half(q2, 32, std::integral_constant<int, 1>{});
+  part[wave][c * 8 + q0 * 4 + q1 * 2 + q2] = acc[0];
   __syncthreads();
   if (threadIdx.x < 64) {
     const int64_t gc = (int64_t)blockIdx.x * 64 + threadIdx.x;
     unsigned long long t = 0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) t += part[k][threadIdx.x];
+    for (int k = 0; k < WAVES; ++k) t += part[k][threadIdx.x];
     if (gc < in) colsum[gc] = t;
   }
 }
@@ -119,9 +128,9 @@ __device__ __forceinline__ double sc_div(double a, double b, double y) {
 }
 
 // Scores: thread t owns 4 adjacent columns (`vec`: one 8-byte load of W and one 16-byte store of S per
-// row) of 16 rows; the reciprocals are taken once per column and thread and once per row and workgroup.
-constexpr int kScoreRows = 16;
-
+// row) of kScoreRows rows (score_rows); the reciprocals are taken once per column and thread and once per row and
+// workgroup.
+template <int kScoreRows>
 __global__ void __launch_bounds__(256)
 ria_score_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, int64_t ldw,
                  const unsigned long long* __restrict__ colsum, const unsigned long long* __restrict__ rowsum,
@@ -138,6 +147,12 @@ ria_score_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, 
   }
   for (int64_t row0 = (int64_t)blockIdx.y * kScoreRows; row0 < out; row0 += (int64_t)gridDim.y * kScoreRows) {
     const int nr = (int)(out - row0 < kScoreRows ? out - row0 : kScoreRows);
+    uint2 w[kScoreRows];                              // requested before the barrier, which no load passes
+    const bool whole = vec && nc == 4;
+    if (whole) {
+#pragma unroll
+      for (int v = 0; v < kScoreRows; ++v) w[v] = *(const uint2*)(W + (row0 + (v < nr ? v : nr - 1)) * ldw + col);
+    }
     __syncthreads();
     if ((int)threadIdx.x < nr) {
       const double rd = (double)rowsum[row0 + threadIdx.x];
@@ -157,10 +172,7 @@ ria_score_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, 
         sc[e] = (float)(sum * ad[e]);
       }
     };
-    if (vec && nc == 4) {
-      uint2 w[kScoreRows];
-#pragma unroll
-      for (int v = 0; v < kScoreRows; ++v) w[v] = *(const uint2*)(W + (row0 + (v < nr ? v : nr - 1)) * ldw + col);
+    if (whole) {
 #pragma unroll
       for (int v = 0; v < kScoreRows; ++v) {
         const unsigned short h[4] = {(unsigned short)(w[v].x & 0xFFFFu), (unsigned short)(w[v].x >> 16),
@@ -190,14 +202,35 @@ int launch_ria_scores(const void* W, int64_t out, int64_t in, int64_t ldw, const
   unsigned long long* colsum = (unsigned long long*)workspace;
   unsigned long long* rowsum = colsum + in;
   const int vec = (ldw % 8 == 0) && (((uintptr_t)W & 15) == 0);
-  hipLaunchKernelGGL(abs_colsum_kernel, dim3((unsigned)((in + 63) / 64)), dim3(1024), 0, st, (const unsigned short*)W, out, in,
-                     ldw, vec, colsum);
+  const dim3 strips((unsigned)((in + 63) / 64));
+  auto sums = [&](auto waves, auto flight) {
+    constexpr int kW = decltype(waves)::value, kF = decltype(flight)::value;
+    hipLaunchKernelGGL((abs_colsum_kernel<kW, kF>), strips, dim3(kW * 64), 0, st, (const unsigned short*)W, out, in, ldw, vec,
+                       colsum);
+  };
+  using std::integral_constant;
+  const ColsumShape cs = colsum_shape(out, vec != 0);
+  if (cs.waves == 16) sums(integral_constant<int, 16>{}, integral_constant<int, 8>{});
+  else if (cs.waves == 8) sums(integral_constant<int, 8>{}, integral_constant<int, 8>{});
+  else if (cs.flight == 8) sums(integral_constant<int, 4>{}, integral_constant<int, 8>{});
+  else if (cs.flight == 4) sums(integral_constant<int, 4>{}, integral_constant<int, 4>{});
+  else sums(integral_constant<int, 4>{}, integral_constant<int, 1>{});
   hipLaunchKernelGGL(abs_rowsum_kernel, dim3((unsigned)((out + 3) / 4)), dim3(256), 0, st, (const unsigned short*)W,
                      out, in, ldw, vec, rowsum);
   const int vec_s = (ldw % 4 == 0) && (((uintptr_t)W & 7) == 0) && (lds % 4 == 0) && (((uintptr_t)S & 15) == 0);
-  const int64_t gy = (out + kScoreRows - 1) / kScoreRows;
-  hipLaunchKernelGGL(ria_score_kernel, dim3((unsigned)((in + 1023) / 1024), (unsigned)(gy < 65535 ? gy : 65535)), dim3(256), 0, st,
-                     (const unsigned short*)W, out, in, ldw, colsum, rowsum, (const float*)act, (float*)S, lds, vec_s);
+  auto scores = [&](auto rows) {
+    constexpr int kR = decltype(rows)::value;
+    const int64_t gy = (out + kR - 1) / kR;
+    hipLaunchKernelGGL(ria_score_kernel<kR>, dim3((unsigned)((in + 1023) / 1024), (unsigned)(gy < 65535 ? gy : 65535)),
+                       dim3(256), 0, st, (const unsigned short*)W, out, in, ldw, colsum, rowsum, (const float*)act, (float*)S,
+                       lds, vec_s);
+  };
+  switch (score_rows(out, in)) {
+    case 1: scores(integral_constant<int, 1>{}); break;
+    case 4: scores(integral_constant<int, 4>{}); break;
+    case 8: scores(integral_constant<int, 8>{}); break;
+    default: scores(integral_constant<int, 16>{});
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "ria score kernels"); return VNM_ERR_HIP; }
   return VNM_OK;
