@@ -222,8 +222,8 @@ int vnm::spmm_impl(const void* X, int64_t T, int64_t ldx, const void* values, co
     if (rc) return rc;
     return launch_spmm_smfmac(workspace, T, packed, d, Y, ldy, y_dtype, scratch, scratch_bytes, f, st);
   }
-  // no packed copy or rows of X that are not aligned: the kernels on the canonical triple; the one-thread-per-
-  // output kernel is the cross-check and takes what they do not (a column table that is not 4-byte aligned)
+  // no packed copy or rows of X that are not aligned: the kernels on the canonical triple.  The one-thread-per-output
+  // kernel is the cross-check, is faster where there are few column blocks, and takes what the others do not
   if (path != VNM_PATH_GENERIC && spmm_plain_applicable(T, colidx, d))
     return launch_spmm_plain(X, T, ldx, values, meta, colidx, d, Y, ldy, y_dtype, f, st);
   return launch_spmm_generic(X, T, ldx, values, meta, colidx, d, Y, ldy, y_dtype, f, st);

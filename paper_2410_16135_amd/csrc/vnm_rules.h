@@ -30,4 +30,46 @@ inline int score_rows(int64_t out, int64_t in) {
   return units <= 1024 ? 1 : units <= 4096 ? 4 : units <= 12288 ? 8 : 16;
 }
 
+// ---- products on the canonical triple (vnm_spmm_plain.hip, scalar kernel in vnm_aux.hip)
+constexpr int kPlainTok = 128;                // tokens of a workgroup of the many-token kernel, lane = two tokens
+constexpr int kPlainCols = 256;               // columns of X it holds in LDS at most
+constexpr int64_t kPlainManyTokens = 32;      // from here on it is used: a quarter of its tokens.  Below, the other
+                                              // kernel's work grows with the tokens, in groups of 4
+
+// Many tokens: column blocks per chunk of K (at most one per lane and kPlainCols columns; an even number, so that every
+// chunk starts at an even column), and rows per wave: as many as still give every compute unit two workgroups (a chunk
+// of X is turned around once per 16 rows_per_wave rows).
+struct PlainPlan { int blocks, rows_per_wave; int64_t groups; };
+inline PlainPlan plain_plan(int64_t T, int64_t out, int M) {
+  int nb = kPlainCols / M;
+  nb = nb > 64 ? 64 : (nb < 1 ? 1 : nb);
+  if (nb > 1) nb &= ~1;
+  const int64_t tiles = (T + kPlainTok - 1) / kPlainTok;
+  int rw = 4;
+  while (rw > 1 && tiles * ((out + 16 * rw - 1) / (16 * rw)) < 512) rw >>= 1;
+  return {nb, rw, tiles * ((out + 16 * rw - 1) / (16 * rw))};
+}
+
+// Whether the scalar kernel, one thread per output that walks all B column blocks, is the faster one: it is where
+// there are few blocks, because the others pay for a lane per block, or for moving all of X through LDS, whatever
+// their number (M = 255: 128 columns of X for each one that is used).  Estimates in us, from device times over 700
+// random layers (8 to 40000 x 8 to 9000, M 4 to 255, 1 to 8192 tokens): with the scalar kernel alone 13.2 us in the
+// geometric mean, without it 11.3, by this rule 8.65, with the better of both every time 8.60.
+//   scalar       0.45 us per block (two dependent loads), or its loads: 3 ps per output and block
+//   few tokens   3.7 us for one token, else 6.3, or 2.9 ns per wave of 8 rows x 4 tokens
+//   many tokens  per workgroup 3.4 us + 1.7 per chunk + 0.09 per block and row of a wave, 256 workgroups at once
+inline bool plain_scalar_faster(int64_t T, int64_t out, int64_t B, int M) {
+  const double by_latency = 1.6 + 0.45 * (double)B, by_loads = 2.0 + 3.0e-6 * (double)out * (double)T * (double)B;
+  const double scalar = by_latency > by_loads ? by_latency : by_loads;
+  if (T < kPlainManyTokens) {
+    const int64_t per = T < 3 ? T : 4;
+    const double waves = 2.9e-3 * (double)((out + 7) / 8) * (double)((T + per - 1) / per), least = T == 1 ? 3.7 : 6.3;
+    return scalar < (waves > least ? waves : least);
+  }
+  const PlainPlan p = plain_plan(T, out, M);
+  const int64_t chunks = (B + p.blocks - 1) / p.blocks, rounds = (p.groups + 255) / 256;
+  const double blocks = (double)(B < p.blocks ? B : p.blocks);
+  return scalar < (3.4 + (double)chunks * (1.7 + 0.09 * blocks * p.rows_per_wave)) * (double)rounds;
+}
+
 }  // namespace vnm

@@ -7,6 +7,7 @@
 // triple, stays as the cross-check behind VNM_PATH_GENERIC.
 #include <type_traits>
 #include "vnm_internal.h"
+#include "vnm_rules.h"
 
 namespace vnm {
 namespace {
@@ -53,12 +54,10 @@ __device__ __forceinline__ int64_t plain_src(const PlainArgs& a, int64_t c) {
 // Bound by that instruction stream, half of it next to the multiply-adds.  1000 x 1030 at V = 16, M = 7,
 // 333 tokens, fp32 result: 25 us per call (spmm_generic_kernel: 219 us).  Sums run over the blocks in
 // ascending order like that kernel's: the results are the same bits.
-constexpr int kPlainTok = 128;
 constexpr int kPlainPitch = kPlainTok * 2 + 4;
 
 // A chunk is at most kPlainCols columns: its 128 tokens then fit 16 (PAIR) or 32 registers per lane, which are
 // filled for the next chunk while the present one is multiplied.  PAIR: X moves two columns at a time.
-constexpr int kPlainCols = 256;
 
 template <int RW, bool PAIR>
 __global__ void __launch_bounds__(1024)
@@ -276,12 +275,7 @@ int launch_plain_tokens2(const PlainArgs& a, int NB, hipStream_t st) {
 }
 
 template <int RW>
-int launch_plain_tokens(const PlainArgs& a, hipStream_t st) {
-  // column blocks per chunk: at most one per lane and kPlainCols columns; an even number, so that every chunk
-  // starts at an even column
-  int NB = kPlainCols / a.M;
-  NB = NB > 64 ? 64 : (NB < 1 ? 1 : NB);
-  if (NB > 1) NB &= ~1;
+int launch_plain_tokens(const PlainArgs& a, int NB, hipStream_t st) {
   // two columns per load where every pair of a row is 4-byte aligned and inside the row
   const bool pair = !a.f.perm_in && a.in % 2 == 0 && a.ldx % 2 == 0 && ((uintptr_t)a.X & 3) == 0 && (NB * a.M) % 2 == 0;
   return pair ? launch_plain_tokens2<RW, true>(a, NB, st) : launch_plain_tokens2<RW, false>(a, NB, st);
@@ -289,14 +283,10 @@ int launch_plain_tokens(const PlainArgs& a, hipStream_t st) {
 
 }  // namespace
 
-// Tokens from which the token-per-lane kernel is used: a quarter of its 128-token tile.  Below, the
-// other kernel's work grows with the tokens (in groups of 4) and it has one wave per 8 rows and group.
-constexpr int64_t kPlainManyTokens = 32;
-
 bool spmm_plain_applicable(int64_t T, const void* colidx, const Dims& d) {
   // 16 rows per workgroup on grid.y; V a multiple of 8 and of the rows per wave; four kept columns as one dword
   return d.V % 16 == 0 && d.M <= 256 && ((uintptr_t)colidx & 3) == 0 && d.out / 16 < 65535 && d.in < (1 << 30) &&
-         (T + kPlainTok - 1) / kPlainTok <= 0x7FFFFFFF;
+         (T + kPlainTok - 1) / kPlainTok <= 0x7FFFFFFF && !plain_scalar_faster(T, d.out, d.B, d.M);
 }
 
 int launch_spmm_plain(const void* X, int64_t T, int64_t ldx, const void* values, const void* meta, const void* colidx,
@@ -308,13 +298,10 @@ int launch_spmm_plain(const void* X, int64_t T, int64_t ldx, const void* values,
   a.Y = Y; a.ldy = ldy; a.y_fp32 = y_dtype; a.f = f;
   int rc = VNM_OK;
   if (T >= kPlainManyTokens) {
-    // rows per wave: as many as still give every compute unit two workgroups (a chunk of X is turned
-    // around once per 16 RW rows)
-    const int64_t tiles = (T + kPlainTok - 1) / kPlainTok;
-    auto groups = [&](int rw) { return tiles * ((d.out + 16 * rw - 1) / (16 * rw)); };
-    if (groups(4) >= 512) rc = launch_plain_tokens<4>(a, st);
-    else if (groups(2) >= 512) rc = launch_plain_tokens<2>(a, st);
-    else rc = launch_plain_tokens<1>(a, st);
+    const PlainPlan p = plain_plan(T, d.out, d.M);
+    if (p.rows_per_wave == 4) rc = launch_plain_tokens<4>(a, p.blocks, st);
+    else if (p.rows_per_wave == 2) rc = launch_plain_tokens<2>(a, p.blocks, st);
+    else rc = launch_plain_tokens<1>(a, p.blocks, st);
   } else {
     const unsigned gx = (unsigned)((d.out + 4 * kPlainRows - 1) / (4 * kPlainRows));
     if (T == 1) hipLaunchKernelGGL(spmm_plain_blocks_kernel<1>, dim3(gx, 1), dim3(256), 0, st, a);

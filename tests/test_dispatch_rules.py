@@ -39,3 +39,26 @@ def test_ria_score_shapes(rule, out, inn, aligned, waves, flight, rows):
     assert rule("colsum_shape(%d, %d).waves" % (out, aligned)) == waves
     assert rule("colsum_shape(%d, %d).flight" % (out, aligned)) == flight
     assert rule("score_rows(%d, %d)" % (out, inn)) == rows
+
+
+# (T, out, column blocks, M) on both sides of the rule; the comments are the scalar and the other kernel's times in us
+@pytest.mark.parametrize("T,out,B,M,scalar", [
+    (1, 128, 1, 255, 1), (1, 4096, 4, 16, 1),           # 2.2 / 3.9, 3.6 / 3.7
+    (1, 1000, 17, 64, 0), (1, 4096, 17, 255, 0),        # 9.3 / 3.2, 9.5 / 3.4
+    (24, 128, 2, 64, 1), (31, 4096, 4, 16, 1),          # 2.9 / 7.0, 4.0 / 12.0
+    (24, 1000, 33, 32, 0), (31, 4096, 32, 128, 0),      # 22.9 / 6.1, 25.0 / 13.6
+    (32, 16, 17, 255, 1), (1024, 16, 17, 255, 1),       # 10.1 / 44.2, 11.0 / 45.5
+    (333, 1000, 5, 255, 1), (64, 4096, 17, 255, 1),     # 6.6 / 16.6, 13.6 / 46.3
+    (333, 1000, 148, 7, 0), (4096, 384, 24, 64, 0),     # 230 / 25.7, 162 / 47
+    (1024, 4096, 17, 255, 0), (4096, 128, 19, 7, 0)])   # 192 / 118, 27.6 / 6.9
+def test_scalar_kernel_where_there_are_few_column_blocks(rule, T, out, B, M, scalar):
+    assert rule("plain_scalar_faster(%d, %d, %d, %d)" % (T, out, B, M)) == scalar
+
+
+# rows per wave change at 512 workgroups, blocks per chunk at 64 blocks, 256 columns and one block
+@pytest.mark.parametrize("T,out,M,blocks,rows", [
+    (32, 1, 4, 64, 1), (128, 32 * 511, 7, 36, 1), (128, 32 * 511 + 1, 7, 36, 2), (128, 64 * 511, 128, 2, 2),
+    (128, 64 * 511 + 1, 129, 1, 4), (11008, 4096, 255, 1, 4)])
+def test_many_token_plan(rule, T, out, M, blocks, rows):
+    assert rule("plain_plan(%d, %d, %d).blocks" % (T, out, M)) == blocks
+    assert rule("plain_plan(%d, %d, %d).rows_per_wave" % (T, out, M)) == rows
