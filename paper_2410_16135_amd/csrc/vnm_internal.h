@@ -150,9 +150,10 @@ int launch_spmm_gemv(const void* X, int64_t T, int64_t ldx, const void* packed, 
 bool spmm_resident_applicable(int64_t T, const Dims& d);
 int launch_spmm_resident(const void* X, int64_t T, int64_t ldx, const void* packed, const Dims& d,
                          void* Y, int64_t ldy, int y_dtype, const Fused& f, hipStream_t st);
-// Y = sum of KS fp32 partial products [KS][T][out] held in `part` (+ bias, output permutation)
+// Y = sum of KS fp32 partial products [KS][T][out] held in `part` (+ bias, output permutation); in_l2: see
+// parts_stay_in_l2
 int launch_splitk_reduce(const void* part, int KS, int64_t T, int64_t out, void* Y, int64_t ldy,
-                         int y_dtype, const Fused& f, hipStream_t st);
+                         int y_dtype, bool in_l2, const Fused& f, hipStream_t st);
 // Split-K scratch of the product kernel for small token counts (fp32 partial products), 0 when unused.
 int64_t splitk_scratch_bytes(int64_t T, int64_t out);
 // f.perm_in is not this kernel's business (it is applied when X is staged)

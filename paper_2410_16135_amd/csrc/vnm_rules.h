@@ -72,4 +72,20 @@ inline bool plain_scalar_faster(int64_t T, int64_t out, int64_t B, int M) {
   return scalar < (3.4 + (double)chunks * (1.7 + 0.09 * blocks * p.rows_per_wave)) * (double)rounds;
 }
 
+// ---- reduction of a product whose K dimension is split (vnm_spmm_smfmac.hip, vnm_spmm_skinny.hip)
+// Whether the partial products are still in the L2 of the XCD that wrote them when the reduction reads them.  Workgroup
+// n runs on XCD n mod 8.  With one token tile (or the few-token kernels) and a multiple of 1024 channels the workgroups
+// that write 256 channels, and the workgroups of 256 results that reduce them, have the same n mod 8 (for a multiple of
+// 2048 every time, for 1024 every other token), and the eight L2s of 4 MiB hold the weight and the parts.  Measured up
+// to 34 MiB; beyond that the order makes no difference.
+inline bool parts_stay_in_l2(int64_t T, int64_t out, int pieces, int64_t weight_bytes, bool one_tile) {
+  return pieces > 1 && one_tile && out % 1024 == 0 && weight_bytes + pieces * T * out * 4 < (34ll << 20);
+}
+// The reduction with 16-byte loads and 1024 results per workgroup, rather than one result per thread.  Below 2^19
+// results the launch is what counts, and one per thread spreads it wider: a 4096 / 11008 block at 24 tokens (three
+// reductions) 73.7 us against 74.2.  And not where that kernel meets its parts in its own L2: whole call, M = 12,
+// 8192 x 2048 at 100 tokens 23.5 us against 28.4, 4096 x 4096 at 256 tokens 16.5 against 18.5; elsewhere the wide one:
+// 11008 x 4096 at 200 tokens 43.2 -> 40.7, 4096 x 4096 at 700 tokens 43.4 -> 40.7, 8192 x 8192 at 100 tokens 33.8 -> 33.3.
+inline bool reduce_wide(int64_t T, int64_t out, bool in_l2) { return T * out >= (1 << 19) && !in_l2; }
+
 }  // namespace vnm

@@ -43,6 +43,7 @@
 // (device time per call at 16 tokens, weights from HBM: 4096 x 4096 10.8 against 9.6 us, 11008 x 4096 13.3
 // against 13.0; at 32 tokens 18.6 against 18.3 us on 11008 x 4096).
 #include "vnm_internal.h"
+#include "vnm_rules.h"
 
 namespace vnm {
 
@@ -548,6 +549,7 @@ int launch_spmm_skinny(const void* X, int64_t T, int64_t ldx, const void* packed
   // one to four tokens: the vector-ALU stream of vnm_spmm_gemv.hip
   if (spmm_gemv_applicable(T, ldx, d)) return launch_spmm_gemv(X, T, ldx, packed, d, Y, ldy, y_dtype, f, st);
   const PackedLayout pl = packed_layout(d);
+  const int64_t weight_bytes = pl.pcol_off - pl.pa_off;
   const char* p = (const char*)packed;
   const bool dual = packed_tables(d.V) == 2;
   const int64_t R = packed_row_blocks(d);
@@ -586,7 +588,8 @@ int launch_spmm_skinny(const void* X, int64_t T, int64_t ldx, const void* packed
     }
 #undef VNM_SK_LAUNCH
     if (rc != VNM_OK || KSr == 1) return rc;
-    return launch_splitk_reduce(scratch, KSr, T, d.out, Y, ldy, y_dtype, f, st);
+    return launch_splitk_reduce(scratch, KSr, T, d.out, Y, ldy, y_dtype,
+                                parts_stay_in_l2(T, d.out, KSr, weight_bytes, true), f, st);
   }
   if (T > skinny_max_tokens()) return VNM_ERR_UNSUPPORTED;               // the phased kernel holds at most 32 token rows
   // steps per phase: a multiple of the 8 waves, at most 32, with at most kSkNX pieces of X per thread
@@ -619,7 +622,8 @@ int launch_spmm_skinny(const void* X, int64_t T, int64_t ldx, const void* packed
   if (!dual) rc = TT == 16 ? launch_skinny_cfg<false, 16>(a, R, KS, st) : launch_skinny_cfg<false, 32>(a, R, KS, st);
   else rc = TT == 16 ? launch_skinny_cfg<true, 16>(a, R, KS, st) : launch_skinny_cfg<true, 32>(a, R, KS, st);
   if (rc != VNM_OK || KS == 1) return rc;
-  return launch_splitk_reduce(scratch, KS, T, d.out, Y, ldy, y_dtype, f, st);
+  return launch_splitk_reduce(scratch, KS, T, d.out, Y, ldy, y_dtype, parts_stay_in_l2(T, d.out, KS, weight_bytes, true),
+                              f, st);
 }
 
 }  // namespace vnm

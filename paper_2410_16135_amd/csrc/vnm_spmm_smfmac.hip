@@ -23,6 +23,7 @@
 //     64-row block (V = 64, 128) or one per 32-row tile (V = 32).
 #include <type_traits>
 #include "vnm_internal.h"
+#include "vnm_rules.h"
 
 namespace vnm {
 
@@ -807,11 +808,10 @@ splitk_reduce4_kernel(const float* __restrict__ part, int KS, int64_t T, int64_t
   }
 }
 
-// Below 2^19 results the launch is what counts, and one result per thread spreads it wider: a 4096 / 11008 block at
-// 24 tokens (three reductions) 73.7 us with that kernel, 74.2 with the other.
 template <typename OutT>
-static void launch_reduce(const float* part, int KS, int64_t T, int64_t out, OutT* Y, int64_t ldy, const Fused& f, hipStream_t st) {
-  if (out % 4 == 0 && ((uintptr_t)part & 15) == 0 && T * out >= (1 << 19)) {
+static void launch_reduce(const float* part, int KS, int64_t T, int64_t out, OutT* Y, int64_t ldy, bool in_l2, const Fused& f,
+                          hipStream_t st) {
+  if (out % 4 == 0 && ((uintptr_t)part & 15) == 0 && reduce_wide(T, out, in_l2)) {
     const int vec_store = ldy % 4 == 0 && ((uintptr_t)Y % (4 * sizeof(OutT))) == 0;
     const dim3 grid((unsigned)((out / 4 + 255) / 256), (unsigned)(T < 65535 ? T : 65535));
     hipLaunchKernelGGL(splitk_reduce4_kernel<OutT>, grid, dim3(256), 0, st, part, KS, T, out, Y, ldy, vec_store, f.bias, f.perm_out);
@@ -886,6 +886,8 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
     a.bias = nullptr; a.perm_out = nullptr;                           // applied by the reduction
     wide = false;
   }
+  const int64_t weight_bytes = pl.pcol_off - pl.pa_off;
+  const bool in_l2 = parts_stay_in_l2(T, d.out, KS, weight_bytes, tiles == 1);
   // Output permutation: rather than scattering 2-byte stores from the epilogue, Y is written in the
   // weight's row order (contiguous runs) and its rows are permuted in place by a second pass
   // through LDS while they are still in cache; rows too long for LDS take the scattering epilogue.
@@ -921,13 +923,13 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
   if (rc != VNM_OK) return rc;
   if (post_permute) return launch_permute_rows(Y, ldy, Y, ldy, T, d.out, y_elem, true, f.perm_out, st);
   if (KS == 1) return rc;
-  return launch_splitk_reduce(scratch, KS, T, d.out, Y, ldy, y_dtype, f, st);
+  return launch_splitk_reduce(scratch, KS, T, d.out, Y, ldy, y_dtype, in_l2, f, st);
 }
 
 int launch_splitk_reduce(const void* part, int KS, int64_t T, int64_t out, void* Y, int64_t ldy,
-                         int y_dtype, const Fused& f, hipStream_t st) {
-  if (y_dtype == 0) launch_reduce((const float*)part, KS, T, out, (_Float16*)Y, ldy, f, st);
-  else launch_reduce((const float*)part, KS, T, out, (float*)Y, ldy, f, st);
+                         int y_dtype, bool in_l2, const Fused& f, hipStream_t st) {
+  if (y_dtype == 0) launch_reduce((const float*)part, KS, T, out, (_Float16*)Y, ldy, in_l2, f, st);
+  else launch_reduce((const float*)part, KS, T, out, (float*)Y, ldy, in_l2, f, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "splitk_reduce_kernel"); return VNM_ERR_HIP; }
   return VNM_OK;

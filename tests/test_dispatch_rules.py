@@ -62,3 +62,19 @@ def test_scalar_kernel_where_there_are_few_column_blocks(rule, T, out, B, M, sca
 def test_many_token_plan(rule, T, out, M, blocks, rows):
     assert rule("plain_plan(%d, %d, %d).blocks" % (T, out, M)) == blocks
     assert rule("plain_plan(%d, %d, %d).rows_per_wave" % (T, out, M)) == rows
+
+
+MB = 1 << 20
+
+
+# parts and weight within the L2s, the same XCD for writer and reader; the comments are the whole call with one result
+# per thread and with four, in us
+@pytest.mark.parametrize("T,out,pieces,weight,one_tile,wide", [
+    (100, 8192, 5, 6.2, 1, 0), (256, 4096, 2, 6.0, 1, 0),       # 23.5 / 28.4, 16.5 / 18.5
+    (128, 5120, 6, 4.6, 1, 0), (128, 16384, 3, 9.0, 1, 0),      # 24.0 / 25.7, 28.8 / 30.2
+    (100, 8192, 6, 58.0, 1, 1), (128, 16384, 3, 57.0, 1, 1),    # 33.8 / 33.3, 36.4 / 34.2
+    (100, 11008, 5, 17.0, 1, 1), (200, 8192, 3, 6.2, 0, 1),     # 28.8 / 27.8, 31.7 / 28.8
+    (700, 4096, 2, 15.0, 0, 1), (24, 4096, 4, 15.0, 1, 0)])     # 43.4 / 40.7; below 2^19 results
+def test_reduction_kernel(rule, T, out, pieces, weight, one_tile, wide):
+    local = "parts_stay_in_l2(%d, %d, %d, %d, %d)" % (T, out, pieces, int(weight * MB), one_tile)
+    assert rule("reduce_wide(%d, %d, %s)" % (T, out, local)) == wide
