@@ -88,4 +88,21 @@ inline bool parts_stay_in_l2(int64_t T, int64_t out, int pieces, int64_t weight_
 // 11008 x 4096 at 200 tokens 43.2 -> 40.7, 4096 x 4096 at 700 tokens 43.4 -> 40.7, 8192 x 8192 at 100 tokens 33.8 -> 33.3.
 inline bool reduce_wide(int64_t T, int64_t out, bool in_l2) { return T * out >= (1 << 19) && !in_l2; }
 
+// ---- numbering of the staged product's workgroups over the XCDs (vnm_spmm_smfmac.hip)
+// Which operand each XCD's L2 fetches for itself: in grid order the weight (every XCD meets every row group), with the
+// token tiles of a row group on one XCD the staged X.  The latter where the weight is clearly the larger of the two:
+// 4096 x 11008 at M = 5 52.1 -> 41.3 us at 320 tokens, 73.1 -> 67.6 at 700, 104 against 104 at 1500 (both 42 MB),
+// 130 -> 136 at 3000; 11008 x 4096 55.3 -> 52.1 at 700, 113 against 112 at 2048, 168 -> 175 at 3000; 4096 x 4096
+// 64.9 -> 71.7 at 4096 tokens.  But not
+// * where the weight is small anyway (4096 x 2048 at M = 8, 4.5 MB, 320 tokens 29.7 -> 32.4; unsplit, 8192 x 2048 at
+//   V = 32, M = 5, 15 MB, 700 tokens 39.0 -> 40.2, with 25 MB, 11008 x 4096 at M = 8 46.9 -> 44.3),
+// * where a piece of K is a dozen steps or less (2048 x 2048 at M = 4, 8 steps, 512 tokens 27.9 -> 30.5),
+// * where the reduction meets its parts in its own L2, which only grid order gives (8192 x 2048 at M = 12, 100 tokens
+//   23.5 -> 28.0).
+// Over 1470 sizes up to 512 tokens 2.6 % less time than in grid order, none slower by more than 2.2 %.
+inline bool tiles_by_xcd(int64_t steps, int pieces, int64_t weight_bytes, int64_t staged_bytes, bool in_l2) {
+  return 10 * weight_bytes > 14 * staged_bytes && weight_bytes >= ((pieces == 1 ? 20ll : 10ll) << 20) &&
+         steps / pieces >= 12 && !in_l2;
+}
+
 }  // namespace vnm

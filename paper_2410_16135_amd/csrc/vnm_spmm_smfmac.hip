@@ -894,12 +894,7 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
   const int y_elem = y_dtype == 0 ? 2 : 4;
   const bool post_permute = KS == 1 && f.perm_out && d.out * y_elem <= permute_rows_max_bytes();
   if (post_permute) a.perm_out = nullptr;
-  // Which operand each XCD's L2 fetches for itself: in grid order the weight (every XCD meets every row
-  // group), with the tiles of a row group on one XCD the staged X.  The latter where the weight is
-  // clearly the larger of the two: 4096 x 11008 at M = 5 42.8 -> 34.4 us at 320 tokens, 60.3 -> 56.6 at 700,
-  // 104 against 104 at 1500 (both 42 MB), 130 -> 136 at 3000; 11008 x 4096 48.0 -> 45.3 at 700, 113 against 112 at
-  // 2048, 168 -> 175 at 3000; 4096 x 4096 64.9 -> 71.7 at 4096.
-  a.tiles_per_xcd = 10 * (pl.pcol_off - pl.pa_off) > 14 * tiles * d.S * a.image_bytes && tiles * a.R * d.S < (1ll << 31);
+  a.tiles_per_xcd = tiles_by_xcd(d.S, KS, weight_bytes, tiles * d.S * a.image_bytes, in_l2) && tiles * a.R * d.S < (1ll << 31);
   a.wide_store = (a.y_fp32 == 0) && (a.ldy % 8 == 0) && (((uintptr_t)a.Y & 15) == 0);
   a.vec_store = (a.ldy % 4 == 0) && (((uintptr_t)a.Y & (a.y_fp32 == 0 ? 7 : 15)) == 0);
   int rc = VNM_ERR_UNSUPPORTED;

@@ -78,3 +78,12 @@ MB = 1 << 20
 def test_reduction_kernel(rule, T, out, pieces, weight, one_tile, wide):
     local = "parts_stay_in_l2(%d, %d, %d, %d, %d)" % (T, out, pieces, int(weight * MB), one_tile)
     assert rule("reduce_wide(%d, %d, %s)" % (T, out, local)) == wide
+
+
+# K steps, pieces, MB of weight, MB of staged X, parts in their own L2
+@pytest.mark.parametrize("steps,pieces,weight,staged,in_l2,by_xcd", [
+    (276, 5, 41, 10.6, 0, 1), (276, 2, 41, 21.2, 0, 1), (276, 1, 41, 42.4, 0, 0),       # 52.1 / 41.3, 73.1 / 67.6, 104 / 104
+    (32, 5, 4.5, 1.9, 0, 0), (52, 1, 15, 4.0, 0, 0), (64, 1, 25, 7.9, 0, 1),            # 29.7 / 32.4, 39.0 / 40.2, 46.9 / 44.3
+    (64, 8, 19, 2.6, 0, 0), (22, 5, 6.2, 0.7, 1, 0), (276, 13, 41, 3.5, 1, 0)])         # 27.9 / 30.5, 23.5 / 28.0
+def test_workgroup_order(rule, steps, pieces, weight, staged, in_l2, by_xcd):
+    assert rule("tiles_by_xcd(%d, %d, %d, %d, %d)" % (steps, pieces, int(weight * MB), int(staged * MB), in_l2)) == by_xcd
