@@ -105,4 +105,18 @@ inline bool tiles_by_xcd(int64_t steps, int pieces, int64_t weight_bytes, int64_
          steps / pieces >= 12 && !in_l2;
 }
 
+// ---- the staged product's deep K loop: six operand sets and images in flight instead of three or four
+// For pieces of a split K on a launch that leaves compute units without a workgroup: a step then waits for its operands
+// rather than for the matrix cores.  Most where the other loop has a ring of three images only (M >= 8): 4096 x 11008 at
+// M = 8 and 700 tokens 75.0 -> 63.2 us, 8192 x 8192 at 320 tokens 60.1 -> 51.0, 232 sizes with M = 8 and 9 and 8 steps or
+// more per piece 5.5 % less time, none 1 % slower.  For M <= 7, with a ring of four, filling the longer ring costs more
+// than it gives below 48 steps (272 sizes 0.6 % slower, up to 3.9) and pays from there on (151 sizes, 1.2 % less).  Not
+// unsplit: 644 sizes 1.3 % slower, 16384 x 1024 at M = 4 and 700 tokens 31.7 -> 34.1.
+// It looks five steps ahead: at least 8 steps in every piece (its first ring of images), and 64 steps in all (its last
+// loads of the weight end inside the sections behind it).  Instantiated for one column table and up to six copies of
+// the image per wave, which is M = 9.
+inline bool deep_loop(int pieces, int64_t workgroups, int64_t last_piece, int64_t row_blocks, int64_t steps, int M, int tables) {
+  return pieces > 1 && workgroups < 256 && last_piece >= (M >= 8 ? 8 : 48) && row_blocks * steps >= 64 && M <= 9 && tables == 1;
+}
+
 }  // namespace vnm

@@ -44,7 +44,7 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 // Steady-state K loop for V = 64 (2 A tiles x 4 B tiles per wave), written in assembly.
 //
 // Why assembly: the loop keeps two kinds of vector-memory operations in flight at once -- the
-// register loads of the A operand two steps ahead and the asynchronous global->LDS copies of the
+// register loads of the A operand two steps ahead (five in the deep loop) and the asynchronous global->LDS copies of the
 // image NBUF-1 steps ahead -- and must wait for the older ones while the younger ones keep flying
 // (vmcnt counts both, in issue order).  Compiled code drains everything (vmcnt(0)) at each use,
 // which serialises the copies with the multiply.  Here every wait is explicit; the schedule of one
@@ -64,7 +64,7 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 // hazard and ends with 24 idle states of its own, whatever else stands between the last
 // v_smfmac and the exit.
 // Validated with the HIP compiler of ROCm 7.2.0 (HIP 7.2.26015, AMD clang 22.0.0git roc-7.2.0); the loops name physical registers
-// v178-v253 and s80-s89 and declare them clobbered, which needs the compiler to keep its own live
+// v178-v253 (the deep loop also v148-v177) and s80-s89 and declare them clobbered, which needs the compiler to keep its own live
 // values below them: a build that fails with "register allocation" errors here means a newer
 // compiler needs more registers around the block.
 #define VNM_ASM_MFMA_DRAIN "s_nop 15\n s_nop 7\n"
@@ -231,7 +231,7 @@ typedef float f16v __attribute__((ext_vector_type(16)));
         "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89")
 
 // The same loop with six A register sets and a ring of six images: operands are requested five steps
-// ahead instead of two and three, for launches that do not fill the chip (see launch_spmm_smfmac).
+// ahead instead of two and three, for launches that do not fill the chip (see deep_loop).
 // Sets 3-5:
 //   v[148:151] v[152:155] v156 v157, v[158:161] v[162:165] v166 v167, v[168:171] v[172:175] v176 v177
 // The image pointer stops at the workgroup's last image (five images would reach past the three that
@@ -502,8 +502,8 @@ spmm_smfmac_kernel(const SpmmArgs a) {
   for (int k = 0; k < NBUF - 1 && k < S; ++k) copy_image(k, k);
 
   {
-    // All S steps run in the assembly loop.  Every step requests the image NBUF-1 steps ahead and
-    // the A operand 2 steps ahead without looking at S: near the end these requests reach past the
+    // All S steps run in the assembly loop.  Every step requests the image NBUF-1 steps ahead (the deep loop stops at
+    // the last one) and the A operand 2 steps ahead (the deep loop 5) without looking at S: near the end these requests reach past the
     // tile's images and past the row block's operands, into the next tile / row block or into the
     // slack that the staged buffer (3 images) and the packed weight (8 KiB) carry for this
     // purpose; what they fetch is never used.
@@ -526,19 +526,22 @@ spmm_smfmac_kernel(const SpmmArgs a) {
       // its start and, with a ring of 4, the NCW copies issued after the previous step's barrier
       // (with a ring of 3 those copies are image s+1 itself and must have landed); with the ring of 6 image
       // s+1 was requested before the loads of four steps and the copies of three
-#define VNM_GO(W, N, VM3, VM4, VM6)                                               \
-      if constexpr (NW == W && NCW == N && !DUAL) {                              \
-        if constexpr (NBUF == 6) VNM_ASM_LOOP_DEEP(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM6);  \
-        else if constexpr (NBUF == 4) VNM_ASM_LOOP_V64(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM4);  \
+#define VNM_GO(W, N, VM3, VM4)                                                    \
+      if constexpr (NW == W && NCW == N && NBUF != 6 && !DUAL) {                 \
+        if constexpr (NBUF == 4) VNM_ASM_LOOP_V64(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM4);  \
         else VNM_ASM_LOOP_V64(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM3);         \
       }                                                                          \
       if constexpr (NW == W && NCW == N && DUAL) {                               \
         if constexpr (NBUF == 4) VNM_ASM_LOOP_D(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM4);    \
         else VNM_ASM_LOOP_D(VNM_C##W##_##N##A, VNM_C##W##_##N##B, VM3);           \
       }
-      VNM_GO(4, 3, "4", "7", "25") VNM_GO(4, 4, "4", "8", "28") VNM_GO(4, 5, "4", "9", "31") VNM_GO(4, 6, "4", "10", "34")
-      VNM_GO(4, 7, "4", "11", "37") VNM_GO(4, 8, "4", "12", "40") VNM_GO(4, 9, "4", "13", "43") VNM_GO(4, 10, "4", "14", "46")
-      VNM_GO(8, 2, "4", "6", "22") VNM_GO(8, 3, "4", "7", "25") VNM_GO(8, 4, "4", "8", "28") VNM_GO(8, 5, "4", "9", "31")
+#define VNM_GO_DEEP(N, VM6)                                                       \
+      if constexpr (NW == 4 && NCW == N && NBUF == 6 && !DUAL) VNM_ASM_LOOP_DEEP(VNM_C4_##N##A, VNM_C4_##N##B, VM6);
+      VNM_GO(4, 3, "4", "7") VNM_GO(4, 4, "4", "8") VNM_GO(4, 5, "4", "9") VNM_GO(4, 6, "4", "10")
+      VNM_GO(4, 7, "4", "11") VNM_GO(4, 8, "4", "12") VNM_GO(4, 9, "4", "13") VNM_GO(4, 10, "4", "14")
+      VNM_GO(8, 2, "4", "6") VNM_GO(8, 3, "4", "7") VNM_GO(8, 4, "4", "8") VNM_GO(8, 5, "4", "9")
+      VNM_GO_DEEP(3, "25") VNM_GO_DEEP(4, "28") VNM_GO_DEEP(5, "31") VNM_GO_DEEP(6, "34")
+#undef VNM_GO_DEEP
 #undef VNM_GO
     }
   }
@@ -711,20 +714,13 @@ static int launch_v64_w4(const SpmmArgs& a, hipStream_t st) {
   }
   return VNM_ERR_UNSUPPORTED;
 }
-// the deep loop (ring of 6, M <= 9)
-static int launch_deep(const SpmmArgs& a, bool wide, hipStream_t st) {
-  if (wide) {
-    switch ((a.image_bytes / 1024 + 7) / 8) {
-      case 2: return launch_cfg<64, 128, 8, 1, 2, 6, false>(a, st);
-      case 3: return launch_cfg<64, 128, 8, 1, 3, 6, false>(a, st);
-    }
-    return VNM_ERR_UNSUPPORTED;
-  }
+// the deep loop (ring of 6; bias and permutation are the reduction's)
+static int launch_deep(const SpmmArgs& a, hipStream_t st) {
   switch ((a.image_bytes / 1024 + 3) / 4) {
-    case 3: return launch_cfg<64, 128, 4, 1, 3, 6, false>(a, st);
-    case 4: return launch_cfg<64, 128, 4, 1, 4, 6, false>(a, st);
-    case 5: return launch_cfg<64, 128, 4, 1, 5, 6, false>(a, st);
-    case 6: return launch_cfg<64, 128, 4, 1, 6, 6, false>(a, st);
+    case 3: return launch_cfg2<64, 128, 4, 1, 3, 6, false, false>(a, st);
+    case 4: return launch_cfg2<64, 128, 4, 1, 4, 6, false, false>(a, st);
+    case 5: return launch_cfg2<64, 128, 4, 1, 5, 6, false, false>(a, st);
+    case 6: return launch_cfg2<64, 128, 4, 1, 6, 6, false, false>(a, st);
   }
   return VNM_ERR_UNSUPPORTED;
 }
@@ -899,15 +895,8 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
   a.vec_store = (a.ldy % 4 == 0) && (((uintptr_t)a.Y & (a.y_fp32 == 0 ? 7 : 15)) == 0);
   int rc = VNM_ERR_UNSUPPORTED;
   const bool ring4 = 4 * (size_t)a.image_bytes <= 150 * 1024;
-  // The deep loop where the launch leaves compute units without a workgroup: a step then waits for its operands
-  // rather than for the matrix cores.  Seven layers of a 4096 / 11008 block at 700 tokens, M = 5, weights from HBM:
-  // 399 -> 383 us; with all compute units busy (4096 tokens) 914 against 915, with one layer's weight in L2 no
-  // difference either way.  Six images fit LDS up to M = 9.  It looks five steps ahead: at least 8 steps per piece (its first ring of images), and
-  // 64 steps in all (its last loads of the weight end inside the sections behind it).
   const int64_t last_piece = d.S - (int64_t)(KS - 1) * a.ks_steps;
-  const int64_t workgroups = tiles * (wide ? (a.R + 7) / 8 : (a.R + 3) / 4) * KS;
-  const bool deep6 = !dual && workgroups < 256 && d.M <= 9 && last_piece >= 8 && a.R * d.S >= 64;
-  if (deep6) rc = launch_deep(a, wide, st);
+  if (deep_loop(KS, base * KS, last_piece, a.R, d.S, d.M, packed_tables(d.V))) rc = launch_deep(a, st);
   else if (!dual) {
     if (wide) rc = ring4 ? launch_v64_w8<4, false>(a, st) : launch_v64_w8<3, false>(a, st);
     else rc = deep ? launch_v64_w4<4, false>(a, st) : launch_v64_w4<3, false>(a, st);

@@ -87,3 +87,13 @@ def test_reduction_kernel(rule, T, out, pieces, weight, one_tile, wide):
     (64, 8, 19, 2.6, 0, 0), (22, 5, 6.2, 0.7, 1, 0), (276, 13, 41, 3.5, 1, 0)])         # 27.9 / 30.5, 23.5 / 28.0
 def test_workgroup_order(rule, steps, pieces, weight, staged, in_l2, by_xcd):
     assert rule("tiles_by_xcd(%d, %d, %d, %d, %d)" % (steps, pieces, int(weight * MB), int(staged * MB), in_l2)) == by_xcd
+
+
+# pieces, workgroups, steps of the last piece, row blocks, steps, M, column tables
+@pytest.mark.parametrize("args,deep", [
+    ((2, 192, 86, 64, 172, 8, 1), 1), ((2, 192, 32, 128, 64, 8, 1), 1), ((1, 132, 103, 172, 103, 5, 1), 0),
+    ((2, 256, 52, 64, 103, 5, 1), 0), ((2, 192, 8, 24, 16, 8, 1), 1), ((2, 192, 7, 24, 15, 8, 1), 0),
+    ((2, 192, 48, 64, 96, 7, 1), 1), ((2, 192, 47, 64, 95, 7, 1), 0),
+    ((2, 192, 57, 64, 114, 9, 1), 1), ((2, 192, 52, 64, 103, 10, 1), 0), ((2, 192, 86, 64, 172, 8, 2), 0)])
+def test_deep_loop(rule, args, deep):
+    assert rule("deep_loop(%s)" % ", ".join(map(str, args))) == deep

@@ -12,11 +12,14 @@ DEV = "cuda:0"
 
 # weight larger than X (tiles of a row group together) and smaller, numbers of workgroups that 8 does not divide,
 # exactly 128 (tile, row group) pairs with and without enough K steps, out not a multiple of 4 (scalar reduction),
-# one token past a tile; the deep K loop at its largest M, the next M, its fewest steps per piece and one below
+# one token past a tile; the deep K loop at its largest M and the next; 8 and 7 steps unsplit; 8 and 7 in the last of
+# two pieces, where 8 are the fewest the deep loop takes at M = 8, 48 and 47 at M = 4; every number of copies per wave
 @pytest.mark.parametrize("out,inn,T,V,M", [
     (4096, 1024, 257, 64, 4), (1100, 2048, 385, 64, 4), (640, 4096, 129, 128, 5), (4096, 3840, 1024, 64, 5),
     (1030, 3080, 700, 32, 5), (513, 4096, 300, 64, 8), (2048, 768, 2048, 64, 8), (1026, 8192, 260, 64, 16),
-    (520, 2000, 300, 64, 9), (2064, 3000, 900, 128, 9), (520, 2000, 300, 64, 10), (2560, 256, 2049, 64, 4), (2560, 224, 2049, 64, 4)])
+    (520, 2000, 300, 64, 9), (2064, 3000, 900, 128, 9), (520, 2000, 300, 64, 10), (2560, 256, 2049, 64, 4), (2560, 224, 2049, 64, 4),
+    (1536, 1024, 2000, 64, 8), (1536, 960, 2000, 64, 8),
+    (1536, 3072, 2000, 64, 4), (1536, 3040, 2000, 64, 4), (1536, 5368, 2000, 64, 7), (1536, 7000, 2000, 64, 9)])
 @pytest.mark.parametrize("ydt", [torch.float16, torch.float32])
 def test_staged_product(out, inn, T, V, M, ydt):
     g = torch.Generator(device=DEV)
