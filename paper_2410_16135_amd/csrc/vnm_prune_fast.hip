@@ -6,6 +6,7 @@
 // vnm_prune.hip: column L1 norms are exact integer sums of the fp16 magnitudes, ties go to the
 // lower index.
 #include "vnm_internal.h"
+#include "vnm_rules.h"
 
 namespace vnm {
 
@@ -382,11 +383,6 @@ static int prune_fast_ksw(const Dims& d) {
   return k;
 }
 
-static size_t prune_fast_lds(int V, int M, int KSW, bool scored = false) {
-  const size_t NC = (size_t)KSW * 8 * M, NBW = (size_t)KSW * 8;
-  return (size_t)V * (NC + 4) * 2 + NC * 8 + NBW * 4 + (scored ? (size_t)V * (NC + 4) * 4 : 0);
-}
-
 bool prune_fast_applicable(const void* W, int64_t ldw, const Dims& d, const void* mask) {
   // ldw: a row's byte pitch is a 24-bit factor of a thread's 32-bit offset inside its workgroup's rows of W
   return d.M <= 16 && d.V % 32 == 0 && d.V <= 128 && d.in % 8 == 0 && ldw % 8 == 0 && ((uintptr_t)W & 15) == 0 &&
@@ -405,9 +401,7 @@ int launch_prune_fast_scored(const void* W, int64_t ldw, const void* S, int64_t 
   a.W = (const unsigned short*)W; a.ldw = ldw; a.out = d.out; a.in = d.in; a.V = d.V; a.M = d.M;
   a.R = d.R; a.B = d.B; a.S = d.S;
   a.Sc = (const float*)S; a.lds_s = lds_s;
-  int k = 8;
-  while (k > 1 && prune_fast_lds(d.V, d.M, k, true) > 40 * 1024) k >>= 1;     // four workgroups per CU
-  a.KSW = k;
+  a.KSW = prune_scored_steps(d.V, d.M, d.R, d.S);
   const int chunks = a.KSW * d.M;
   a.G = 256 / chunks < d.V ? 256 / chunks : d.V;
   a.values = (unsigned short*)values; a.meta = (unsigned char*)meta; a.colidx = (unsigned char*)colidx;
@@ -417,7 +411,7 @@ int launch_prune_fast_scored(const void* W, int64_t ldw, const void* S, int64_t 
     char* p = (char*)packed;
     a.pa = (uint4*)(p + pl.pa_off); a.pidx = (unsigned short*)(p + pl.pidx_off); a.pcol = (unsigned*)(p + pl.pcol_off);
   }
-  const size_t lds = prune_fast_lds(d.V, d.M, a.KSW, true);
+  const size_t lds = (size_t)prune_fast_lds(d.V, d.M, a.KSW, true);
   if (int rc_lds = allow_big_lds((const void*)prune_pack_kernel<true>, "hipFuncSetAttribute(prune_pack scored)")) return rc_lds;
   dim3 grid((unsigned)((d.S + a.KSW - 1) / a.KSW), (unsigned)d.R);
   hipLaunchKernelGGL(prune_pack_kernel<true>, grid, dim3(256), lds, st, a);
@@ -442,7 +436,7 @@ int launch_prune_fast(const void* W, int64_t ldw, const Dims& d, void* values, v
     char* p = (char*)packed;
     a.pa = (uint4*)(p + pl.pa_off); a.pidx = (unsigned short*)(p + pl.pidx_off); a.pcol = (unsigned*)(p + pl.pcol_off);
   }
-  const size_t lds = prune_fast_lds(d.V, d.M, a.KSW);
+  const size_t lds = (size_t)prune_fast_lds(d.V, d.M, a.KSW, false);
   if (int rc_lds = allow_big_lds((const void*)prune_pack_kernel<false>, "hipFuncSetAttribute(prune_pack)")) return rc_lds;
   // column spans along x: the workgroups that run together then read whole rows of W (every memory
   // channel in use) instead of one window of columns in many rows; on weights that come from HBM

@@ -119,4 +119,23 @@ inline bool deep_loop(int pieces, int64_t workgroups, int64_t last_piece, int64_
   return pieces > 1 && workgroups < 256 && last_piece >= (M >= 8 ? 8 : 48) && row_blocks * steps >= 64 && M <= 9 && tables == 1;
 }
 
+// ---- pruning (vnm_prune_fast.hip): K steps of 8 column blocks that a workgroup takes at a time
+// Its LDS: weight tile u16 [V][NC + 4], column sums f64 [NC], kept columns u32 [blocks], with scores f32 [V][NC + 4]
+inline int64_t prune_fast_lds(int V, int M, int steps, bool scored) {
+  const int64_t NC = (int64_t)steps * 8 * M, blocks = (int64_t)steps * 8;
+  return V * (NC + 4) * 2 + NC * 8 + blocks * 4 + (scored ? V * (NC + 4) * 4 : 0);
+}
+// Pruning from scores.  As wide as three workgroups per compute unit allow: a wider span reads longer runs of a row,
+// another workgroup hides more of the dependent phases.  11008 x 4096 with at most 40 / 52 / 64 KiB of LDS, us:
+// V = 64, M = 8 101.6 / 86.5 / 86.5; V = 32, M = 8 91.9 / 77.4 / 77.4; V = 32, M = 9 90.8 / 90.8 / 105.3;
+// V = 128, M = 4 133 / 114 / 114; V = 64, M = 5 112 / 112 / 106; V = 32, M = 5 102 / 102 / 111.
+// Narrower while there are too few workgroups for that to matter: 1024 x 1024 at V = 32, M = 4 with 128 / 256
+// workgroups 10.5 / 8.8, at M = 8 9.1 / 8.6; with 160 at M = 7 9.7 against 10.3 with 320; 8 steps with 256 workgroups
+// (500 x 4096, V = 32, M = 4) 11.7 against 10.8 for 4 steps.  Over 324 sizes and patterns 0.3 % from the best choice.
+inline int prune_scored_steps(int V, int M, int64_t row_blocks, int64_t steps) {
+  int k = 8;
+  while (k > 1 && (prune_fast_lds(V, M, k, true) > 52 * 1024 || (steps + k - 1) / k * row_blocks < (k > 4 ? 512 : 160))) k >>= 1;
+  return k;
+}
+
 }  // namespace vnm

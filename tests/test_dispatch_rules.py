@@ -97,3 +97,13 @@ def test_workgroup_order(rule, steps, pieces, weight, staged, in_l2, by_xcd):
     ((2, 192, 57, 64, 114, 9, 1), 1), ((2, 192, 52, 64, 103, 10, 1), 0), ((2, 192, 86, 64, 172, 8, 2), 0)])
 def test_deep_loop(rule, args, deep):
     assert rule("deep_loop(%s)" % ", ".join(map(str, args))) == deep
+
+
+# V, M, rows, columns; LDS of three workgroups per compute unit, and at least 160 workgroups (512 for eight steps)
+@pytest.mark.parametrize("V,M,out,inn,steps", [
+    (64, 8, 11008, 4096, 2), (32, 8, 11008, 4096, 4), (32, 9, 11008, 4096, 2), (128, 4, 11008, 4096, 2), (32, 4, 11008, 4096, 8),
+    (64, 5, 4096, 4096, 2), (128, 10, 4096, 4096, 1), (32, 4, 1024, 1024, 4), (32, 8, 1024, 1024, 2), (32, 7, 1024, 1024, 4),
+    (32, 4, 500, 4096, 4), (64, 5, 128, 160, 1)])
+def test_scored_pruning_span(rule, V, M, out, inn, steps):
+    blocks = -(-inn // M)
+    assert rule("prune_scored_steps(%d, %d, %d, %d)" % (V, M, -(-out // V), -(-blocks // 8))) == steps

@@ -26,3 +26,23 @@ def test_ria_scores_at_the_edges_of_the_launch_shapes(out, inn):
     got = S.cpu().numpy()
     assert np.array_equal(got[:out].view(np.uint32), orc.importance_ria(W, act).view(np.uint32))
     assert bool((got[out] == -1.0).all())             # nothing stored behind the last row
+
+
+# every span the scored pruning takes (8, 4, 2, 1 K steps of 8 blocks), with steps left over, a ragged last row block
+# and a last block that is cut
+@pytest.mark.parametrize("out,inn,V,M", [(5470, 592, 32, 4), (3190, 296, 32, 4), (3000, 504, 32, 7), (5753, 328, 64, 8),
+                                         (5110, 296, 128, 4), (5000, 248, 32, 16), (200, 304, 64, 5)])
+def test_scored_pruning_in_every_span(out, inn, V, M):
+    rng = np.random.default_rng(out + M)
+    W, _ = syn.make_weight_and_input(out, inn, 1, seed=M)
+    S = np.round(rng.random((out, inn)) * 64).astype(np.float32)          # many ties
+    c = vnm.vnm_prune_compress_scored(torch.from_numpy(W).to(DEV), torch.from_numpy(S).to(DEV), V, M, want_mask=True)
+    torch.cuda.synchronize()
+    values, meta, colidx, mask = orc.compress(W, V, M, score=S)
+    assert np.array_equal(c.mask.cpu().numpy(), mask)
+    assert np.array_equal(c.values.cpu().numpy().view(np.uint16), values.reshape(-1).view(np.uint16))
+    assert np.array_equal(c.meta.cpu().numpy(), meta.reshape(-1)) and np.array_equal(c.colidx.cpu().numpy(), colidx.reshape(-1))
+    # the matrix-core copy made in the same pass is the one made from the triple
+    X = torch.from_numpy(rng.standard_normal((40, inn)).astype(np.float16)).to(DEV)
+    again = vnm.vnm_pack(vnm.Compressed(c.values, c.meta, c.colidx, None, out, inn, V, M))
+    assert torch.equal(vnm.vnm_spmm(X, c), vnm.vnm_spmm(X, again))
