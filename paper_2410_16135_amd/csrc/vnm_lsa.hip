@@ -27,6 +27,8 @@
 //   keep the invariants above; only the rows still unmatched afterwards go through the exact
 //   augmentation, which alone would be correct too.
 #include <stdint.h>
+#include <memory>
+#include <new>
 #include <vector>
 #include "vnm_internal.h"
 
@@ -41,15 +43,16 @@
 
 namespace {
 
-// One row scan of the auction: values v[j] = row[j] - pp[j], n a multiple of 8 (rows are padded with the
-// lowest value at price zero); returns the largest, the second largest (equal to the largest if that
-// occurs twice) and the lowest position of the largest.  `next` is the row that will be scanned next.
-void scan_top2_scalar(const int64_t* row, const int64_t* pp, int n, const int64_t* next, int64_t& v1, int64_t& v2, int& j1) {
-  (void)next;
+// One row scan of the auction: values v[j] = (row[j] << sh) - pp[j]; returns the largest, the second largest (equal to
+// the largest if that occurs twice) and the lowest position of the largest.  `next` is the row that will be scanned next.
+// SHIFT = false: sh is 0.
+template <bool SHIFT>
+void scan_top2_scalar(const int64_t* row, const int64_t* pp, int n, int sh, const int64_t* next, int64_t& v1, int64_t& v2, int& j1) {
+  (void)next; (void)sh;
   int64_t b1 = INT64_MIN, b2 = INT64_MIN;
   int k1 = -1;
   for (int j = 0; j < n; ++j) {
-    const int64_t v = row[j] - pp[j];
+    const int64_t v = (SHIFT ? row[j] << sh : row[j]) - pp[j];
     if (v > b1) { b2 = b1; b1 = v; k1 = j; }
     else if (v > b2) b2 = v;
   }
@@ -63,13 +66,22 @@ void scan_top2_scalar(const int64_t* row, const int64_t* pp, int n, const int64_
 // looks for the first occurrence and stops there.  Rows follow each other in queue order, anywhere in
 // a matrix that is larger than the L2 cache, so the next one is requested while this one is scanned.
 // Gain matrices of a 2048 x 2048 layer, n = 409: 11-15 ms per solve before, 7-9 ms now on one CPU; the
-// permutation search on that layer (ten such solves) 76 -> 55 ms.
+// permutation search on that layer (ten such solves) 76 -> 55 ms.  SHIFT = false: sh is 0.
+template <bool SHIFT>
 __attribute__((target("avx512f")))
-void scan_top2_avx512(const int64_t* row, const int64_t* pp, int n, const int64_t* next, int64_t& v1, int64_t& v2, int& j1) {
+void scan_top2_avx512(const int64_t* row, const int64_t* pp, int n, int sh, const int64_t* next, int64_t& v1, int64_t& v2, int& j1) {
   const __m512i lowest = _mm512_set1_epi64(INT64_MIN);
+  const __m128i shv = _mm_cvtsi32_si128(sh);
   __m512i a0 = lowest, a1 = lowest, a2 = lowest, a3 = lowest, s0 = lowest, s1 = lowest, s2 = lowest, s3 = lowest;
   auto value = [&](int j) __attribute__((target("avx512f"), always_inline)) {
-    return _mm512_sub_epi64(_mm512_loadu_si512(row + j), _mm512_loadu_si512(pp + j));
+    const __m512i g = _mm512_loadu_si512(row + j);
+    return _mm512_sub_epi64(SHIFT ? _mm512_sll_epi64(g, shv) : g, _mm512_loadu_si512(pp + j));
+  };
+  // the last n % 8 columns; nothing is read behind them, and the other lanes hold the lowest value
+  auto value_tail = [&](int j) __attribute__((target("avx512f"), always_inline)) {
+    const __mmask8 m = (__mmask8)((1u << (n - j)) - 1);
+    const __m512i g = _mm512_maskz_loadu_epi64(m, row + j);
+    return _mm512_mask_sub_epi64(lowest, m, SHIFT ? _mm512_sll_epi64(g, shv) : g, _mm512_maskz_loadu_epi64(m, pp + j));
   };
   int j = 0;
   for (; j + 32 <= n; j += 32) {
@@ -81,10 +93,14 @@ void scan_top2_avx512(const int64_t* row, const int64_t* pp, int n, const int64_
     s2 = _mm512_max_epi64(s2, _mm512_min_epi64(a2, x2)); a2 = _mm512_max_epi64(a2, x2);
     s3 = _mm512_max_epi64(s3, _mm512_min_epi64(a3, x3)); a3 = _mm512_max_epi64(a3, x3);
   }
-  for (; j < n; j += 8) {
+  for (; j + 8 <= n; j += 8) {
     const __m512i x = value(j);
     __builtin_prefetch(next + j);
     s0 = _mm512_max_epi64(s0, _mm512_min_epi64(a0, x)); a0 = _mm512_max_epi64(a0, x);
+  }
+  if (j < n) {
+    const __m512i x = value_tail(j);
+    s1 = _mm512_max_epi64(s1, _mm512_min_epi64(a1, x)); a1 = _mm512_max_epi64(a1, x);
   }
   // two (largest, second) pairs into one: the second largest of the four is the larger of the smaller
   // largest and the seconds
@@ -106,23 +122,27 @@ void scan_top2_avx512(const int64_t* row, const int64_t* pp, int n, const int64_
     b2 = b2 > lo ? b2 : lo;
   }
   const __m512i top = _mm512_set1_epi64(b1);
-  for (j = 0; j < n; j += 8) {
-    const __mmask8 eq = _mm512_cmpeq_epi64_mask(value(j), top);
-    if (eq) { j += __builtin_ctz((unsigned)eq); break; }
+  __mmask8 eq = 0;
+  for (j = 0; j + 8 <= n; j += 8) {
+    eq = _mm512_cmpeq_epi64_mask(value(j), top);
+    if (eq) break;
   }
+  if (!eq) eq = _mm512_cmpeq_epi64_mask(value_tail(j), top);      // it is in the last columns then
+  j += __builtin_ctz((unsigned)eq);
   v1 = b1; v2 = b2; j1 = j;
 }
 
 #endif
 
-typedef void (*ScanFn)(const int64_t*, const int64_t*, int, const int64_t*, int64_t&, int64_t&, int&);
+typedef void (*ScanFn)(const int64_t*, const int64_t*, int, int, const int64_t*, int64_t&, int64_t&, int&);
 
-ScanFn pick_scan() {
+ScanFn pick_scan(bool simd, bool shift) {
 #if VNM_LSA_X86_HOST
   __builtin_cpu_init();
-  if (__builtin_cpu_supports("avx512f")) return scan_top2_avx512;
+  if (simd && __builtin_cpu_supports("avx512f")) return shift ? scan_top2_avx512<true> : scan_top2_avx512<false>;
 #endif
-  return scan_top2_scalar;
+  (void)simd;
+  return shift ? scan_top2_scalar<true> : scan_top2_scalar<false>;
 }
 
 // Auction; false = gave up (nothing written that matters), true = assign and total are set.
@@ -134,13 +154,27 @@ bool lsa_auction(const int64_t* gain, int n, int64_t gmax, int* assign, int64_t*
   int sh = 1;
   while (((int64_t)1 << sh) <= n) ++sh;
   if (gmax > ((((int64_t)1 << 61) - 1) >> sh)) return false;
-  const ScanFn scan = simd ? pick_scan() : scan_top2_scalar;
-  // value of column j for row i: gs[i][j] - pp[j], gs = gain << sh in rows padded to whole vectors,
-  // pp[j] = (colmin[j] << sh) + price[j]
+  // value of column j for row i: (gain[i][j] << sh) - pp[j], pp[j] = (colmin[j] << sh) + price[j].  Up to 4 MiB of gains
+  // (n = 724) are shifted once, into rows that start on cache lines and are padded to whole vectors with the lowest value
+  // at price zero: n = 409 7.2-17.2 ms against 8.8-21.7 in place.  Beyond, or where there is no memory for it, the caller's
+  // rows are read and shifted where they are: n = 1500 47 ms against 57 with the copy, which would double the call's memory.
   const int n8 = (n + 7) & ~7;
-  std::vector<int64_t> gs((size_t)n * n8, INT64_MIN), pp((size_t)n8, 0);
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j < n; ++j) gs[(size_t)i * n8 + j] = gain[(int64_t)i * n + j] << sh;
+  std::unique_ptr<int64_t[]> copy;
+  if ((int64_t)n * n8 * 8 <= (4 << 20)) copy.reset(new (std::nothrow) int64_t[(size_t)n * n8 + 8]);
+  const int64_t* rows = gain;
+  int64_t pitch = n;
+  int width = n, row_sh = sh;
+  if (copy) {
+    int64_t* c = copy.get();
+    while ((uintptr_t)c & 63) ++c;
+    rows = c; pitch = n8; width = n8; row_sh = 0;
+    for (int i = 0; i < n; ++i, c += n8) {
+      for (int j = 0; j < n; ++j) c[j] = gain[(int64_t)i * n + j] << sh;
+      for (int j = n; j < n8; ++j) c[j] = INT64_MIN;
+    }
+  }
+  const ScanFn scan = pick_scan(simd, row_sh != 0);
+  std::vector<int64_t> pp((size_t)n8, 0);
   int64_t C = 0;
   {
     std::vector<int64_t> cmin(gain, gain + n), cmax(gain, gain + n);
@@ -169,10 +203,10 @@ bool lsa_auction(const int64_t* gain, int n, int64_t gmax, int* assign, int64_t*
     for (int i = 0; i < n; ++i) {
       if (col[(size_t)i] >= 0) {
         int64_t v1, v2; int j1;
-        const int64_t* row = gs.data() + (size_t)i * n8;
-        scan(row, pp.data(), n8, i + 1 < n ? row + n8 : row, v1, v2, j1);
+        const int64_t* row = rows + i * pitch;
+        scan(row, pp.data(), width, row_sh, i + 1 < n ? row + pitch : row, v1, v2, j1);
         const int j = col[(size_t)i];
-        if (row[j] - pp[(size_t)j] < v1 - eps) { owner[(size_t)j] = -1; col[(size_t)i] = -1; }
+        if ((row[j] << row_sh) - pp[(size_t)j] < v1 - eps) { owner[(size_t)j] = -1; col[(size_t)i] = -1; }
       }
       if (col[(size_t)i] < 0) queue.push_back(i);
     }
@@ -181,7 +215,7 @@ bool lsa_auction(const int64_t* gain, int n, int64_t gmax, int* assign, int64_t*
       const int i = queue[head];
       int64_t v1, v2; int j1;
       const int next = head + 1 < queue.size() ? queue[head + 1] : i;
-      scan(gs.data() + (size_t)i * n8, pp.data(), n8, gs.data() + (size_t)next * n8, v1, v2, j1);
+      scan(rows + i * pitch, pp.data(), width, row_sh, rows + next * pitch, v1, v2, j1);
       pp[(size_t)j1] += (v1 - v2) + eps;
       const int prev = owner[(size_t)j1];
       owner[(size_t)j1] = i; col[(size_t)i] = j1;

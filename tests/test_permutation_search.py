@@ -212,3 +212,40 @@ def test_library_assignment_errors(lib):
     assert lib.vnm_lsa_max(g.ctypes.data_as(ctypes.c_void_p), 0, a.ctypes.data_as(ctypes.c_void_p), ctypes.byref(t)) == 2
     g[0, 0] = -1
     assert lib.vnm_lsa_max(g.ctypes.data_as(ctypes.c_void_p), 2, a.ctypes.data_as(ctypes.c_void_p), ctypes.byref(t)) == 2
+
+
+@pytest.mark.parametrize("n", [720, 728, 733])
+@pytest.mark.parametrize("kind", ["ties", "search"])
+def test_auction_on_both_sides_of_the_copy_limit(lib, n, kind):
+    """Up to 4 MiB (n = 724) the gains are copied into padded rows, beyond they are read where they are: the same bids,
+    with and without vectors, and the Hungarian method's optimum."""
+    gain = _search_like_gain(n, n) if kind == "search" else np.random.default_rng(n).integers(0, 50, size=(n, n))
+    got = {m: _lib_lsa_method(lib, gain, m) for m in (LSA_HUNGARIAN, LSA_AUCTION, LSA_AUCTION_SCALAR)}
+    for rc, assign, total in got.values():
+        assert rc == 0 and sorted(assign) == list(range(n))
+        assert total == sum(int(gain[i, assign[i]]) for i in range(n)) == got[LSA_HUNGARIAN][2]
+    assert np.array_equal(got[LSA_AUCTION][1], got[LSA_AUCTION_SCALAR][1])
+
+
+def test_assignment_needs_no_copy_of_the_gains(lib):
+    """The solver's own memory is a few rows: with less address space left than half the matrix it still runs."""
+    import os
+    import subprocess
+    import sys
+    code = """
+import ctypes, resource, numpy as np
+import paper_2410_16135_amd as vnm
+lib = vnm.load_library()
+n = 3000
+gain = np.random.default_rng(1).integers(0, 1000, size=(n, n))
+gain[np.arange(n), (np.arange(n) * 7 + 3) % n] += 10 ** 6
+assign, total = np.full(n, -1, dtype=np.int32), ctypes.c_int64(0)
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + n * n * 4, resource.RLIM_INFINITY))
+rc = lib.vnm_lsa_max(gain.ctypes.data_as(ctypes.c_void_p), n, assign.ctypes.data_as(ctypes.c_void_p), ctypes.byref(total))
+assert rc == 0, rc
+assert (assign == (np.arange(n) * 7 + 3) % n).all() and total.value == int(gain[np.arange(n), assign].sum())
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300, cwd=root)
+    assert res.returncode == 0, res.stderr[-2000:]
