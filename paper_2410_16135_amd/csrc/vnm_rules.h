@@ -52,15 +52,16 @@ inline PlainPlan plain_plan(int64_t T, int64_t out, int M) {
 
 // Whether the scalar kernel, one thread per output that walks all B column blocks, is the faster one: it is where
 // there are few blocks, because the others pay for a lane per block, or for moving all of X through LDS, whatever
-// their number (M = 255: 128 columns of X for each one that is used).  Estimates in us, from device times over 700
-// random layers (8 to 40000 x 8 to 9000, M 4 to 255, 1 to 8192 tokens): with the scalar kernel alone 13.2 us in the
-// geometric mean, without it 11.3, by this rule 8.65, with the better of both every time 8.60.
-//   scalar       0.45 us per block (two dependent loads), or its loads: 3 ps per output and block
+// their number (M = 255: 128 columns of X for each one that is used).  Estimates in us, from device times over 1283
+// layers (8 to 40000 x 8 to 9000, M 4 to 255, 1 to 8192 tokens): with the scalar kernel alone 20.3 us in the geometric
+// mean, without it 12.6, by this rule 9.99, with the better of both every time 9.97.
+//   scalar       0.45 us per block (two dependent loads) and its loads, 2.6 ps per output and block: the larger of the
+//                two and 0.6 of the smaller
 //   few tokens   3.7 us for one token, else 6.3, or 2.9 ns per wave of 8 rows x 4 tokens
-//   many tokens  per workgroup 3.4 us + 1.7 per chunk + 0.09 per block and row of a wave, 256 workgroups at once
+//   many tokens  per workgroup 2.8 us + 1.7 per chunk + 0.09 per block and row of a wave, 256 workgroups at once
 inline bool plain_scalar_faster(int64_t T, int64_t out, int64_t B, int M) {
-  const double by_latency = 1.6 + 0.45 * (double)B, by_loads = 2.0 + 3.0e-6 * (double)out * (double)T * (double)B;
-  const double scalar = by_latency > by_loads ? by_latency : by_loads;
+  const double by_latency = 1.6 + 0.45 * (double)B, by_loads = 2.6e-6 * (double)out * (double)T * (double)B;
+  const double scalar = by_latency > by_loads ? by_latency + 0.6 * by_loads : by_loads + 0.6 * by_latency;
   if (T < kPlainManyTokens) {
     const int64_t per = T < 3 ? T : 4;
     const double waves = 2.9e-3 * (double)((out + 7) / 8) * (double)((T + per - 1) / per), least = T == 1 ? 3.7 : 6.3;
@@ -69,7 +70,7 @@ inline bool plain_scalar_faster(int64_t T, int64_t out, int64_t B, int M) {
   const PlainPlan p = plain_plan(T, out, M);
   const int64_t chunks = (B + p.blocks - 1) / p.blocks, rounds = (p.groups + 255) / 256;
   const double blocks = (double)(B < p.blocks ? B : p.blocks);
-  return scalar < (3.4 + (double)chunks * (1.7 + 0.09 * blocks * p.rows_per_wave)) * (double)rounds;
+  return scalar < (2.8 + (double)chunks * (1.7 + 0.09 * blocks * p.rows_per_wave)) * (double)rounds;
 }
 
 // ---- reduction of a product whose K dimension is split (vnm_spmm_smfmac.hip, vnm_spmm_skinny.hip)

@@ -50,7 +50,8 @@ def test_ria_score_shapes(rule, out, inn, aligned, waves, flight, rows):
     (32, 16, 17, 255, 1), (1024, 16, 17, 255, 1),       # 10.1 / 44.2, 11.0 / 45.5
     (333, 1000, 5, 255, 1), (64, 4096, 17, 255, 1),     # 6.6 / 16.6, 13.6 / 46.3
     (333, 1000, 148, 7, 0), (4096, 384, 24, 64, 0),     # 230 / 25.7, 162 / 47
-    (1024, 4096, 17, 255, 0), (4096, 128, 19, 7, 0)])   # 192 / 118, 27.6 / 6.9
+    (1024, 4096, 17, 255, 0), (4096, 128, 19, 7, 0),    # 192 / 118, 27.6 / 6.9
+    (40, 4096, 64, 64, 0), (333, 384, 24, 64, 0)])      # 63.7 / 37.1, 21.6 / 15.9
 def test_scalar_kernel_where_there_are_few_column_blocks(rule, T, out, B, M, scalar):
     assert rule("plain_scalar_faster(%d, %d, %d, %d)" % (T, out, B, M)) == scalar
 
