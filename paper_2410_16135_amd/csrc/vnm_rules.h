@@ -50,6 +50,15 @@ inline PlainPlan plain_plan(int64_t T, int64_t out, int M) {
   return {nb, rw, tiles * ((out + 16 * rw - 1) / (16 * rw))};
 }
 
+// Sizes both kernels can index: row groups on grid.y for many tokens (on grid.x for few), token tiles on grid.x, 32-bit
+// byte offsets into a row of X.
+inline bool plain_sizes_fit(int64_t T, int64_t out, int64_t in, int M) {
+  if (in >= (1 << 30)) return false;
+  if (T < kPlainManyTokens) return out <= 32ll * 0x7FFFFFFF;
+  const int64_t tiles = (T + kPlainTok - 1) / kPlainTok;
+  return tiles <= 0x7FFFFFFF && plain_plan(T, out, M).groups / tiles <= 65535;
+}
+
 // Whether the scalar kernel, one thread per output that walks all B column blocks, is the faster one: it is where
 // there are few blocks, because the others pay for a lane per block, or for moving all of X through LDS, whatever
 // their number (M = 255: 128 columns of X for each one that is used).  Estimates in us, from device times over 1283

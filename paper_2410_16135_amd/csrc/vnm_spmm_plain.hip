@@ -284,9 +284,8 @@ int launch_plain_tokens(const PlainArgs& a, int NB, hipStream_t st) {
 }  // namespace
 
 bool spmm_plain_applicable(int64_t T, const void* colidx, const Dims& d) {
-  // 16 rows per workgroup on grid.y; V a multiple of 8 and of the rows per wave; four kept columns as one dword
-  return d.V % 16 == 0 && d.M <= 256 && ((uintptr_t)colidx & 3) == 0 && d.out / 16 < 65535 && d.in < (1 << 30) &&
-         (T + kPlainTok - 1) / kPlainTok <= 0x7FFFFFFF && !plain_scalar_faster(T, d.out, d.B, d.M);
+  // the four kept columns of a block are read as one dword
+  return ((uintptr_t)colidx & 3) == 0 && plain_sizes_fit(T, d.out, d.in, d.M) && !plain_scalar_faster(T, d.out, d.B, d.M);
 }
 
 int launch_spmm_plain(const void* X, int64_t T, int64_t ldx, const void* values, const void* meta, const void* colidx,

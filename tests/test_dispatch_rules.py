@@ -108,3 +108,11 @@ def test_deep_loop(rule, args, deep):
 def test_scored_pruning_span(rule, V, M, out, inn, steps):
     blocks = -(-inn // M)
     assert rule("prune_scored_steps(%d, %d, %d, %d)" % (V, M, -(-out // V), -(-blocks // 8))) == steps
+
+
+# 2^20 rows and more: rows are on grid.x for few tokens, 64 of them per workgroup on grid.y for many
+@pytest.mark.parametrize("T,out,inn,fit", [
+    (1, 1 << 20, 64, 1), (31, 1 << 26, 64, 1), (32, 1 << 20, 64, 1), (32, 64 * 65535, 64, 1), (32, 64 * 65535 + 1, 64, 0),
+    (1, 64, 1 << 30, 0), (1, 64, (1 << 30) - 1, 1), (4096, 16, 64, 1)])
+def test_sizes_of_the_plain_kernels(rule, T, out, inn, fit):
+    assert rule("plain_sizes_fit(%d, %d, %d, 4)" % (T, out, inn)) == fit

@@ -80,11 +80,12 @@ def test_plain_unaligned_rows_of_a_layer_with_a_packed_copy():
 
 # layers with enough column blocks not to go to the scalar kernel: one, two and more tokens by block, and every
 # instantiation by token -- 1, 2 and 4 rows per wave with X moved one and two columns at a time, one and several blocks
-# per chunk, rows and tokens that fill no tile
+# per chunk, rows and tokens that fill no tile; more than 2^20 rows
 @pytest.mark.parametrize("fused", [False, True])
 @pytest.mark.parametrize("out,inn,T,V,M", [
     (17, 64, 1, 16, 4), (18, 129, 2, 16, 5), (33, 127, 4, 32, 9), (40, 4103, 31, 128, 255), (4100, 333, 31, 16, 4),
     (70, 666, 127, 16, 7), (70, 667, 129, 64, 7), (4100, 334, 700, 16, 8), (4100, 333, 700, 16, 8), (11008, 70, 300, 16, 4),
-    (11001, 71, 300, 16, 4), (11001, 74, 300, 128, 5), (4100, 2182, 1030, 16, 130), (4100, 2181, 1030, 32, 129)])
+    (11001, 71, 300, 16, 4), (11001, 74, 300, 128, 5), (4100, 2182, 1030, 16, 130), (4100, 2181, 1030, 32, 129),
+    (1048577, 62, 33, 16, 4)])
 def test_plain_product_in_every_instantiation(out, inn, T, V, M, fused):
     test_plain_product(out, inn, T, V, M, torch.float32, fused)
