@@ -82,6 +82,22 @@ inline bool plain_scalar_faster(int64_t T, int64_t out, int64_t B, int M) {
   return scalar < (2.8 + (double)chunks * (1.7 + 0.09 * blocks * p.rows_per_wave)) * (double)rounds;
 }
 
+// ---- pieces of K of the staged product, for T <= 2048 tokens and `pairs` (token tile, 256 channels) pairs, before the
+// limits that scratch and 4 steps per piece set.
+// Up to 256 tokens about 200 workgroups measured best.  Beyond that the partial products (pieces x T x out floats
+// written, then read by the reduction) weigh in: 256 workgroups while that fills the compute units in one generation,
+// and a split in two only where K is long enough to pay for the reduction; exactly 128 pairs (powers of two in tokens
+// and channels) need more of it than 127.  Two pieces against one, in this order at
+// 26 / 43 / 52 / 64 / 103 / 205 steps (V = 64; M = 5 but M = 12 for 43 and M = 8 for 64): 96 pairs 1.12 / 0.96 / 0.91 / 0.87 /
+// 0.75 / 0.64, 112 pairs 1.12 / 1.01 / 0.93 / 0.99 / 0.78 / 0.67, 125 pairs 1.20 / 0.98 / 0.97 / 0.85 / 0.81 / 0.70, 128
+// pairs 1.20 / 1.06 / 1.01 / 1.01 / 0.85 / 0.72.  One pair more and they take a second generation: 129 pairs 1.36 / 1.44 /
+// 1.16 / 1.04 / 1.02 / 0.66, 160 pairs 1.44 / 1.46 / 1.21 / 1.15 / 1.08 / 0.96.
+inline int64_t split_pieces(int64_t T, int64_t pairs, int64_t steps) {
+  if (T <= 256) return (200 + pairs / 2) / pairs;
+  if (pairs <= 85) return 256 / pairs;
+  return steps >= (pairs < 128 ? 40 : pairs == 128 ? 96 : 192) ? 2 : 1;
+}
+
 // ---- reduction of a product whose K dimension is split (vnm_spmm_smfmac.hip, vnm_spmm_skinny.hip)
 // Whether the partial products are still in the L2 of the XCD that wrote them when the reduction reads them.  Workgroup
 // n runs on XCD n mod 8.  With one token tile (or the few-token kernels) and a multiple of 1024 channels the workgroups

@@ -859,16 +859,7 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
   int KS = 1;
   const int64_t base = tiles * ((a.R + 3) / 4);
   if (scratch && T <= kSplitKMaxTokens && base < 192) {
-    // up to 256 tokens: about 200 workgroups measured best.  Beyond that the partial products (ks x T x
-    // out floats written, then read by the reduction) weigh in: about 256 workgroups while fewer than
-    // half the CUs would have one, and a split in two only where the K loop is long enough to pay
-    // for the reduction.  At exactly half the CUs a split in two fills them without a second generation:
-    // 4096 x 4096 at 1024 tokens, 103 steps, 43.2 -> 36.5 us; 2048 x 5504 at 2048 tokens, 138 steps, 52.7 -> 41.4;
-    // 64 steps gain nothing (33.8 against 34.6).  Above, pieces share CUs: 192 pairs of 103 steps 43.4 against 51.0.
-    int64_t ks = 1;
-    if (T <= 256) ks = (200 + base / 2) / base;
-    else if (base < 128 || (base == 128 && d.S >= 96)) ks = 256 / base;
-    else if (d.S >= 192) ks = 2;
+    int64_t ks = split_pieces(T, base, d.S);
     if (ks > 16) ks = 16;
     if (ks > d.S / 4) ks = d.S / 4;                                   // at least 4 K steps each
     while (ks > 1 && ks * T * d.out * 4 > scratch_bytes) --ks;

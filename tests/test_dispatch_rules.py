@@ -116,3 +116,11 @@ def test_scored_pruning_span(rule, V, M, out, inn, steps):
     (1, 64, 1 << 30, 0), (1, 64, (1 << 30) - 1, 1), (4096, 16, 64, 1)])
 def test_sizes_of_the_plain_kernels(rule, T, out, inn, fit):
     assert rule("plain_sizes_fit(%d, %d, %d, 4)" % (T, out, inn)) == fit
+
+
+# two pieces against one, as measured: 128 pairs 0.85 at 103 steps, 1.20 at 26; 129 pairs 1.02 and 0.66 at 205
+@pytest.mark.parametrize("T,pairs,steps,pieces", [
+    (100, 43, 103, 5), (256, 32, 43, 6), (300, 48, 103, 5), (300, 85, 26, 3), (700, 86, 39, 1), (700, 86, 40, 2), (900, 112, 26, 1),
+    (1000, 127, 40, 2), (1000, 128, 96, 2), (1000, 128, 95, 1), (1000, 129, 103, 1), (1000, 129, 191, 1), (1000, 191, 192, 2)])
+def test_split_pieces(rule, T, pairs, steps, pieces):
+    assert rule("split_pieces(%d, %d, %d)" % (T, pairs, steps)) == pieces
