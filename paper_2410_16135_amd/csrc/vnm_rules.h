@@ -115,20 +115,30 @@ inline bool parts_stay_in_l2(int64_t T, int64_t out, int pieces, int64_t weight_
 inline bool reduce_wide(int64_t T, int64_t out, bool in_l2) { return T * out >= (1 << 19) && !in_l2; }
 
 // ---- numbering of the staged product's workgroups over the XCDs (vnm_spmm_smfmac.hip)
-// Which operand each XCD's L2 fetches for itself: in grid order the weight (every XCD meets every row group), with the
-// token tiles of a row group on one XCD the staged X.  The latter where the weight is clearly the larger of the two:
-// 4096 x 11008 at M = 5 52.1 -> 41.3 us at 320 tokens, 73.1 -> 67.6 at 700, 104 against 104 at 1500 (both 42 MB),
-// 130 -> 136 at 3000; 11008 x 4096 55.3 -> 52.1 at 700, 113 against 112 at 2048, 168 -> 175 at 3000; 4096 x 4096
-// 64.9 -> 71.7 at 4096 tokens.  But not
-// * where the weight is small anyway (4096 x 2048 at M = 8, 4.5 MB, 320 tokens 29.7 -> 32.4; unsplit, 8192 x 2048 at
-//   V = 32, M = 5, 15 MB, 700 tokens 39.0 -> 40.2, with 25 MB, 11008 x 4096 at M = 8 46.9 -> 44.3),
-// * where a piece of K is a dozen steps or less (2048 x 2048 at M = 4, 8 steps, 512 tokens 27.9 -> 30.5),
-// * where the reduction meets its parts in its own L2, which only grid order gives (8192 x 2048 at M = 12, 100 tokens
-//   23.5 -> 28.0).
-// Over 1470 sizes up to 512 tokens 2.6 % less time than in grid order, none slower by more than 2.2 %.
-inline bool tiles_by_xcd(int64_t steps, int pieces, int64_t weight_bytes, int64_t staged_bytes, bool in_l2) {
-  return 10 * weight_bytes > 14 * staged_bytes && weight_bytes >= ((pieces == 1 ? 20ll : 10ll) << 20) &&
-         steps / pieces >= 12 && !in_l2;
+// Workgroup n runs on XCD n mod 8, each with an L2 of its own.  What each of them fetches of the weight and of the staged
+// X, as shares of the whole, where n counts token tiles first, then groups of 256 channels, then pieces of K:
+//   grid order   X: the tiles of one residue modulo gcd(tiles, 8) -- all of them where the number of tiles is odd;
+//                the weight: min(1, tiles / 8); with one tile the groups of one residue modulo gcd(groups, 8)
+//   XCD order    (an XCD takes consecutive n) an eighth of the weight; X of one piece, an eighth at least
+// The XCD order is taken where it saves each L2 4 MiB, in a split product with pieces of 10 steps or more, or 8 MiB
+// unsplit, and where the reduction does not need grid order to meet its parts in its own L2.  Time against grid order
+// by MiB saved, 1500 random sizes (600 to 16384 x 600 to 12000, 65 to 4000 tokens): split 0-2 1.008, 2-4 1.001, 4-6 0.979,
+// 6-8 0.950, 10-12 0.897, 20 and more 0.862; unsplit 0-2 1.019, 4-6 1.006, 6-8 0.991, 8-10 0.986, 12-14 0.978, 20 and more
+// 0.975.  4096 x 11008 at M = 5: 320 tokens 52.1 -> 41.3 us, 1124 tokens (9 tiles) 146 -> 106; 2048 x 11008 at M = 8 and 868
+// tokens 67 -> 44; 4096 x 4096 unsplit at 4096 tokens saves nothing and would lose 64.9 -> 71.7.
+inline bool tiles_by_xcd(int64_t tiles, int64_t groups, int64_t steps, int pieces, int64_t weight_bytes, int64_t staged_bytes,
+                         bool in_l2) {
+  auto residues = [](int64_t n) { return n % 8 == 0 ? 8 : n % 4 == 0 ? 4 : n % 2 == 0 ? 2 : 1; };
+  double x_grid = 1.0, w_grid = tiles < 8 ? (double)tiles / 8 : 1.0;
+  if (tiles > 1) x_grid = 1.0 / residues(tiles);
+  else {
+    const double spread = pieces < 8 ? (double)pieces / 8 : 1.0, met = 1.0 / residues(groups);
+    w_grid = spread < met ? (spread > 0.125 ? spread : 0.125) : met;
+  }
+  const double x_xcd = pieces > 8 ? 0.125 : 1.0 / pieces;
+  const double saved = (w_grid - 0.125) * (double)weight_bytes + (x_grid - x_xcd) * (double)staged_bytes;
+  if (in_l2) return false;
+  return pieces > 1 ? saved >= (4 << 20) && steps / pieces >= 10 : saved >= (8 << 20);
 }
 
 // ---- the staged product's deep K loop: six operand sets and images in flight instead of three or four

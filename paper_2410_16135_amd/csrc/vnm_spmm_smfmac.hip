@@ -881,7 +881,8 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
   const int y_elem = y_dtype == 0 ? 2 : 4;
   const bool post_permute = KS == 1 && f.perm_out && d.out * y_elem <= permute_rows_max_bytes();
   if (post_permute) a.perm_out = nullptr;
-  a.tiles_per_xcd = tiles_by_xcd(d.S, KS, weight_bytes, tiles * d.S * a.image_bytes, in_l2) && tiles * a.R * d.S < (1ll << 31);
+  a.tiles_per_xcd = tiles_by_xcd(tiles, (a.R + 3) / 4, d.S, KS, weight_bytes, tiles * d.S * a.image_bytes, in_l2) &&
+                    tiles * a.R * d.S < (1ll << 31);
   a.wide_store = (a.y_fp32 == 0) && (a.ldy % 8 == 0) && (((uintptr_t)a.Y & 15) == 0);
   a.vec_store = (a.ldy % 4 == 0) && (((uintptr_t)a.Y & (a.y_fp32 == 0 ? 7 : 15)) == 0);
   int rc = VNM_ERR_UNSUPPORTED;

@@ -81,13 +81,16 @@ def test_reduction_kernel(rule, T, out, pieces, weight, one_tile, wide):
     assert rule("reduce_wide(%d, %d, %s)" % (T, out, local)) == wide
 
 
-# K steps, pieces, MB of weight, MB of staged X, parts in their own L2
-@pytest.mark.parametrize("steps,pieces,weight,staged,in_l2,by_xcd", [
-    (276, 5, 41, 10.6, 0, 1), (276, 2, 41, 21.2, 0, 1), (276, 1, 41, 42.4, 0, 0),       # 52.1 / 41.3, 73.1 / 67.6, 104 / 104
-    (32, 5, 4.5, 1.9, 0, 0), (52, 1, 15, 4.0, 0, 0), (64, 1, 25, 7.9, 0, 1),            # 29.7 / 32.4, 39.0 / 40.2, 46.9 / 44.3
-    (64, 8, 19, 2.6, 0, 0), (22, 5, 6.2, 0.7, 1, 0), (276, 13, 41, 3.5, 1, 0)])         # 27.9 / 30.5, 23.5 / 28.0
-def test_workgroup_order(rule, steps, pieces, weight, staged, in_l2, by_xcd):
-    assert rule("tiles_by_xcd(%d, %d, %d, %d, %d)" % (steps, pieces, int(weight * MB), int(staged * MB), in_l2)) == by_xcd
+# token tiles, groups of 256 channels, K steps, pieces, MB of weight, MB of staged X, parts in their own L2
+@pytest.mark.parametrize("tiles,groups,steps,pieces,weight,staged,in_l2,by_xcd", [
+    (3, 16, 276, 5, 39, 10.1, 0, 1), (6, 16, 276, 2, 39, 20.2, 0, 1),          # 52.1 / 41.3, 73.1 / 67.6 us
+    (9, 16, 276, 2, 39, 30.3, 0, 1), (7, 8, 172, 4, 12.1, 23.5, 0, 1),         # an odd number of tiles: 146 / 106, 67 / 44
+    (16, 16, 276, 1, 39, 53.9, 0, 0), (32, 16, 103, 1, 14.5, 40.2, 0, 0),      # unsplit, every XCD has its tiles: 64.9 / 71.7
+    (3, 16, 32, 5, 4.5, 1.9, 0, 0), (6, 32, 52, 1, 15, 4.0, 0, 0),             # 29.7 / 32.4, 39.0 / 40.2
+    (11, 43, 64, 1, 25, 13.7, 0, 1), (3, 4, 128, 16, 4.5, 3.8, 0, 0),          # 61.2 / 52.9, 25.6 / 28.9
+    (1, 32, 22, 5, 6.2, 0.7, 1, 0), (1, 16, 276, 13, 39, 3.4, 1, 0), (1, 16, 276, 13, 39, 3.4, 0, 0), (1, 43, 128, 5, 48, 1.3, 0, 1)])
+def test_workgroup_order(rule, tiles, groups, steps, pieces, weight, staged, in_l2, by_xcd):
+    assert rule("tiles_by_xcd(%d, %d, %d, %d, %d, %d, %d)" % (tiles, groups, steps, pieces, int(weight * MB), int(staged * MB), in_l2)) == by_xcd
 
 
 # pieces, workgroups, steps of the last piece, row blocks, steps, M, column tables
