@@ -68,8 +68,8 @@ typedef struct vnm_sizes {
 
 /* Which kernel vnm_spmm uses. */
 typedef enum vnm_spmm_path {
-  VNM_PATH_AUTO = 0,       /* sparse matrix-core kernel when `packed` is given and the shape allows, else generic */
-  VNM_PATH_GENERIC = 1,    /* scalar kernel on the canonical triple; any V, M, alignment (a cross-check: slow) */
+  VNM_PATH_AUTO = 0,       /* matrix-core kernels when `packed` is given and the shape allows, else the fastest on the triple */
+  VNM_PATH_GENERIC = 1,    /* scalar kernel on the canonical triple; any V, M, alignment (the cross-check: slow on long rows) */
   VNM_PATH_SMFMAC = 2      /* 2:4 sparse MFMA kernel on `packed`; fails with UNSUPPORTED if not applicable */
 } vnm_spmm_path;
 
@@ -144,7 +144,7 @@ int vnm_pack(const void* values, const void* meta, const void* colidx,
  * fp16 operands, fp32 accumulation; X counts as 0 at padded columns and is never read there.
  *   X        dev fp16 [T x in], leading dimension ldx >= in
  *   Y        dev [T x out], leading dimension ldy >= out; y_dtype 0 = fp16, 1 = fp32
- *   packed   dev or NULL (NULL forces the generic kernel under VNM_PATH_AUTO)
+ *   packed   dev or NULL (NULL: VNM_PATH_AUTO works on the canonical triple)
  *   path     a vnm_spmm_path
  *   workspace  dev, 256-byte aligned, vnm_spmm_workspace_bytes(T, ...) bytes: the matrix-core
  *            kernel first re-lays X there (token tiles x K steps, column-major inside, the order
@@ -152,12 +152,12 @@ int vnm_pack(const void* values, const void* meta, const void* colidx,
  *            (vnm_spmm_scratch_bytes, optional) holds fp32 partial products when, for few tokens,
  *            the K dimension is split over workgroups; contents are scratch, nothing persists
  * The matrix-core kernel needs V in {32, 64, 128}, M <= 16, in % 8 == 0, ldx % 8 == 0 and X 16-byte
- * aligned; otherwise (or when `packed` is NULL) AUTO uses the generic kernel, which needs no
- * workspace.  For T <= 32 the matrix-core path is a single kernel that reads X directly and needs no
- * workspace (if one is given, its scratch part may hold split-K partial products).  For larger T, when the
- * matrix-core kernel applies but the workspace is missing or too small the call fails with VNM_ERR_WORKSPACE
- * instead of silently taking the slow kernel (also where, up to 256 tokens, the few-token kernels end up
- * serving the call and use at most the scratch part).
+ * aligned; otherwise (or when `packed` is NULL) AUTO works on the canonical triple, with the kernel that
+ * the sizes favour, and needs no workspace.  For T <= 32 the matrix-core path is a single kernel that
+ * reads X directly and needs no workspace (if one is given, its scratch part may hold split-K partial
+ * products).  For larger T, when the matrix-core kernel applies but the workspace is missing or too small
+ * the call fails with VNM_ERR_WORKSPACE instead of silently taking a slower kernel (also where, up to 256
+ * tokens, the few-token kernels end up serving the call and use at most the scratch part).
  * T == 0 is a successful no-op (X and Y may then be NULL).
  */
 int vnm_spmm(const void* X, int64_t T, int64_t ldx,
@@ -243,7 +243,7 @@ int vnm_fold_permutations(const void* perm_out_prev, const void* perm_in_next, i
  * `scratch` (vnm_spmm_scratch_bytes(T, out)
  * bytes, 256-byte aligned, or NULL) is the optional split-K scratch: without it, or with less than
  * asked for, the product is still correct, only slower for small T.  vnm_spmm_staged fails with
- * VNM_ERR_UNSUPPORTED where vnm_spmm would have used the generic kernel.
+ * VNM_ERR_UNSUPPORTED where vnm_spmm would have worked on the canonical triple.
  */
 int vnm_stage_x(const void* X, int64_t T, int64_t ldx, int64_t in, int M,
                 void* staged, int64_t staged_bytes, void* stream);

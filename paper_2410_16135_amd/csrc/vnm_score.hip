@@ -118,7 +118,10 @@ abs_rowsum_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in,
 
 // a / b rounded to nearest, from y = 1 / b rounded to nearest: q0 = a y is within 1.5 ulp, one correction
 // makes q1 a faithful quotient, and for a faithful quotient the second one gives the correctly rounded result
-// (Markstein's theorem; no overflow or underflow here: a is 0 or an integer up to 2^41, b one up to 2^63).
+// (Markstein's theorem).  It needs exact residuals, so nothing may overflow or underflow: a is 0 or k 2^-136 with an
+// integer k < 2^41, b an integer-valued double up to 2^63, so quotients are at least 2^-199 and residuals, multiples of
+// 2^-136 or of half an ulp of the quotient, above 2^-252.  (a comes from an fp32 conversion that keeps subnormals: fp32
+// denormals must not be flushed in this file.)
 // Five operations per element; the division by itself takes about fifteen, two of them per element
 // (53 us on 4096 x 4096, of which the memory traffic needs a third).
 __device__ __forceinline__ double sc_div(double a, double b, double y) {

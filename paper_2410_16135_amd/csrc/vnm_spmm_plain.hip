@@ -4,7 +4,8 @@
 // Both kernels multiply exactly the kept weights with the columns they select (no dense expansion:
 // an infinity in a column that a row does not select must not reach it) and accumulate in fp32.
 // spmm_generic_kernel, one thread per output walking all of K with uncoalesced 2-byte loads of the
-// triple, stays as the cross-check behind VNM_PATH_GENERIC.
+// triple, is the cross-check behind VNM_PATH_GENERIC and the faster one where there are few column blocks
+// (plain_scalar_faster).
 #include <type_traits>
 #include "vnm_internal.h"
 #include "vnm_rules.h"
