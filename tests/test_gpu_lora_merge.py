@@ -30,6 +30,12 @@ def test_merge_bit_exact(out, inn, r):
     assert np.array_equal(got.view(np.uint16), orc.lora_merge(W, B, A, 2.0).view(np.uint16))
 
 
+# whole aligned tiles with 1, 2 and 3 rows of A left over after groups of four, and ranks below four
+@pytest.mark.parametrize("out,inn,r", [(128, 128, 1), (128, 128, 3), (136, 264, 5), (128, 128, 6), (128, 128, 7), (2048, 4096, 11)])
+def test_merge_of_aligned_tiles_bit_exact(out, inn, r):
+    test_merge_bit_exact(out, inn, r)
+
+
 def test_merge_strided_and_in_place():
     rng = np.random.default_rng(9)
     big = _dev(syn.make_weight_and_input(96, 160, 1, seed=9)[0])

@@ -34,3 +34,31 @@ def test_staged_product(out, inn, T, V, M, ydt):
     if ydt == torch.float16:
         bound = bound + 2.0 ** -11 * want.abs() + 2.0 ** -24
     assert bool(((Y.double() - want).abs() <= bound).all())
+
+
+# the reduction's epilogue, four results per thread and one: bias and output permutation after the deep loop (M = 8, 9)
+# and after the shorter one (two column tables, M = 12), with vector stores and without
+@pytest.mark.parametrize("out,inn,T,V,M", [(1536, 1024, 2000, 64, 8), (1540, 1104, 900, 64, 9), (1030, 1024, 900, 64, 8),
+                                           (2048, 2048, 700, 32, 5), (1100, 3000, 500, 64, 12), (8192, 1024, 100, 64, 8)])
+@pytest.mark.parametrize("ydt", [torch.float16, torch.float32])
+@pytest.mark.parametrize("which", [("bias",), ("perm_out",), ("bias", "perm_out")])
+def test_staged_product_epilogue(out, inn, T, V, M, ydt, which):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(out + T)
+    c = vnm.vnm_prune_compress((torch.randn((out, inn), generator=g, device=DEV) * 0.02).half(), V, M)
+    X = torch.randn((T, inn), generator=g, device=DEV).half()
+    kw = {"bias": torch.randn(out, generator=g, device=DEV).half(),
+          "perm_out": torch.randperm(out, generator=g, device=DEV).to(torch.int32)}
+    kw = {k: v for k, v in kw.items() if k in which}
+    Y = vnm.vnm_spmm_fused(X, c, out_dtype=ydt, **kw)
+    W = vnm.vnm_decompress(c).double()
+    want, mag = X.double() @ W.t(), X.double().abs() @ W.abs().t()
+    if "bias" in kw:
+        want, mag = want + kw["bias"].double(), mag + kw["bias"].double().abs()
+    if "perm_out" in kw:
+        po = kw["perm_out"].long()
+        want, mag = torch.empty_like(want).index_copy_(1, po, want), torch.empty_like(mag).index_copy_(1, po, mag)
+    bound = (2 * -(-inn // M) + 32) * 2.0 ** -24 * mag
+    if ydt == torch.float16:
+        bound = bound + 2.0 ** -11 * want.abs() + 2.0 ** -24
+    assert bool(((Y.double() - want).abs() <= bound).all())
