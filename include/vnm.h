@@ -132,6 +132,21 @@ int vnm_lora_merge(const void* W, int64_t out, int64_t in, int64_t ldw, const vo
                    const void* A, int64_t lda, int r, float scale, void* W_merged, int64_t ldm,
                    void* stream);
 
+/*
+ * The mask refresh with RIA scores in one call: the same bits as vnm_lora_merge, vnm_ria_scores and
+ * vnm_prune_compress_scored one after the other, without the score matrix between them.
+ *   W, B, A, r, scale, W_merged   as for vnm_lora_merge;  act as for vnm_ria_scores
+ *   values, meta, colidx, mask, packed   as for vnm_prune_compress_scored (mask and packed may be NULL)
+ *   workspace  dev, 8-byte aligned, vnm_refresh_mask_workspace_bytes(...) bytes; contents are scratch
+ * Takes layers with M <= 16, V >= 32 and in % 8 == 0 (for others the query gives 0 bytes) whose rows of W, A
+ * and W_merged are 16-byte aligned; VNM_ERR_UNSUPPORTED otherwise: the three single calls take everything.
+ */
+int vnm_refresh_mask_workspace_bytes(int64_t out, int64_t in, int V, int N, int M, int64_t* bytes);
+int vnm_refresh_mask(const void* W, int64_t out, int64_t in, int64_t ldw, const void* B, int64_t ldb,
+                     const void* A, int64_t lda, int r, float scale, const void* act, int V, int N, int M,
+                     void* W_merged, int64_t ldm, void* values, void* meta, void* colidx, void* mask,
+                     void* packed, void* workspace, int64_t workspace_bytes, void* stream);
+
 /* Builds `packed` from an existing canonical triple (e.g. one loaded from storage). */
 int vnm_pack(const void* values, const void* meta, const void* colidx,
              int64_t out, int64_t in, int V, int N, int M, void* packed, void* stream);

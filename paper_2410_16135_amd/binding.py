@@ -72,6 +72,11 @@ def load_library():
     lib.vnm_retained_score.restype = ci
     lib.vnm_lora_merge.argtypes = [vp, i64, i64, i64, vp, i64, vp, i64, ci, ctypes.c_float, vp, i64, vp]
     lib.vnm_lora_merge.restype = ci
+    lib.vnm_refresh_mask_workspace_bytes.argtypes = [i64, i64, ci, ci, ci, ctypes.POINTER(i64)]
+    lib.vnm_refresh_mask_workspace_bytes.restype = ci
+    lib.vnm_refresh_mask.argtypes = [vp, i64, i64, i64, vp, i64, vp, i64, ci, ctypes.c_float, vp, ci, ci, ci, vp, i64, vp,
+                                     vp, vp, vp, vp, vp, i64, vp]
+    lib.vnm_refresh_mask.restype = ci
     lib.vnm_lsa_max.argtypes = [vp, ci, vp, ctypes.POINTER(i64)]
     lib.vnm_lsa_max.restype = ci
     lib.vnm_lsa_max_method.argtypes = [vp, ci, ci, vp, ctypes.POINTER(i64)]
@@ -434,9 +439,32 @@ def vnm_lora_merge(W, B, A, scale: float, W_merged=None):
 def vnm_refresh_mask(W, B, A, scale: float, V: int, M: int, act=None, N: int = 2) -> Compressed:
     """Mask update of the LoRA stage with dynamic masks (Section 4.3): merge, score (RIA when `act`
     is given, else |w|), prune.  Returns the Compressed of the merged weight with its mask."""
-    merged = vnm_lora_merge(W, B, A, scale)
     if act is None:
-        return vnm_prune_compress(merged, V, M, N, want_mask=True)
+        return vnm_prune_compress(vnm_lora_merge(W, B, A, scale), V, M, N, want_mask=True)
+    import torch
+    assert W.is_cuda and W.dtype == torch.float16 and W.dim() == 2 and W.stride(1) == 1
+    out, inn = W.shape
+    r = B.shape[1]
+    assert B.dtype == torch.float32 and A.dtype == torch.float32 and B.shape == (out, r) and A.shape == (r, inn)
+    assert (r == 0) or (B.stride(1) == 1 and A.stride(1) == 1)
+    assert act.is_cuda and act.dtype == torch.float32 and act.shape == (inn,) and act.is_contiguous()
+    lib = load_library()
+    b = ctypes.c_int64(0)
+    _check(lib.vnm_refresh_mask_workspace_bytes(out, inn, V, N, M, ctypes.byref(b)), "vnm_refresh_mask_workspace_bytes")
+    if b.value > 0:                     # three kernels without a score matrix, where sizes and alignment allow them
+        merged = torch.empty_like(W)
+        values, meta, colidx, packed = _alloc(vnm_query_sizes(out, inn, V, M, N), W.device)
+        mask = torch.empty((out, inn), dtype=torch.uint8, device=W.device)
+        ws = torch.empty(b.value, dtype=torch.uint8, device=W.device)
+        status = lib.vnm_refresh_mask(
+            _ptr(W), out, inn, W.stride(0), _ptr(B), B.stride(0) if r else 0, _ptr(A), A.stride(0) if r else inn, r,
+            float(scale), _ptr(act), V, N, M, _ptr(merged), merged.stride(0), _ptr(values), _ptr(meta), _ptr(colidx),
+            _ptr(mask), _ptr(packed), _ptr(ws), ws.numel(), _stream(W))
+        if status == 0:
+            return Compressed(values, meta, colidx, packed, out, inn, V, M, mask)
+        if status != 3:                 # rows that are not 16-byte aligned are the single steps' business
+            _check(status, "vnm_refresh_mask")
+    merged = vnm_lora_merge(W, B, A, scale)
     return vnm_prune_compress_scored(merged, vnm_ria_scores(merged, act), V, M, N, want_mask=True)
 
 

@@ -97,6 +97,11 @@ int launch_prune_fast(const void* W, int64_t ldw, const Dims& d, void* values, v
 bool prune_fast_scored_applicable(const void* W, int64_t ldw, const void* S, int64_t lds_s, const Dims& d);
 int launch_prune_fast_scored(const void* W, int64_t ldw, const void* S, int64_t lds_s, const Dims& d, void* values,
                              void* meta, void* colidx, void* mask, void* packed, hipStream_t st);
+// The same from RIA scores computed on the fly: prep f64 [3][in] (column sum, its reciprocal, act * 2^136), f64 [2][out] (row
+// sum, its reciprocal; vnm_refresh.hip)
+bool prune_fast_ria_applicable(const void* W, int64_t ldw, const Dims& d);
+int launch_prune_fast_ria(const void* W, int64_t ldw, const double* prep, const Dims& d,
+                          void* values, void* meta, void* colidx, void* mask, void* packed, hipStream_t st);
 bool decompress_fast_applicable(const void* W_out, int64_t ldw, const Dims& d);
 int launch_decompress_fast(const void* values, const void* meta, const void* colidx, const Dims& d,
                            void* W_out, int64_t ldw, hipStream_t st);

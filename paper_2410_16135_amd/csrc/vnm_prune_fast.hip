@@ -7,6 +7,7 @@
 // lower index.
 #include "vnm_internal.h"
 #include "vnm_rules.h"
+#include "vnm_score.h"
 
 namespace vnm {
 
@@ -45,18 +46,20 @@ __device__ __forceinline__ unsigned top2_of_4_f(unsigned w0, unsigned w1, unsign
   return (lo >> 16) | ((hi >> 16) << 2);
 }
 
-// The same selection on importance scores handed in (finite, non-negative fp32, compared through
-// their bit patterns without the sign): positions p0 < p1 of the two largest, ties to the lower position.
-__device__ __forceinline__ unsigned top2_of_4_s(unsigned g0, unsigned g1, unsigned g2, unsigned g3) {
-  const unsigned g[4] = {g0, g1, g2, g3};
-  int a = 0;
-#pragma unroll
-  for (int k = 1; k < 4; ++k) if (g[k] > g[a]) a = k;
-  int b = (a == 0) ? 1 : 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) if (k != a && k != b && g[k] > g[b]) b = k;
-  const int p0 = a < b ? a : b, p1 = a < b ? b : a;
-  return (unsigned)p0 | ((unsigned)p1 << 2);
+// The same selection on importance scores (finite, non-negative fp32, as bit patterns without the sign): an element is kept
+// when fewer than two others beat it, a later one by being larger, an earlier one by being no smaller.  Six comparisons whose
+// results stay in scalar masks.  (With two of them kept, one is always kept on each side, whatever the scores are.)
+__device__ __forceinline__ unsigned top2_of_4_s(unsigned g0, unsigned g1, unsigned g2, unsigned g3, unsigned w0, unsigned w1,
+                                                unsigned w2, unsigned w3, unsigned& pair) {
+  const bool b01 = g1 > g0, b02 = g2 > g0, b03 = g3 > g0, b12 = g2 > g1, b13 = g3 > g1, b23 = g3 > g2;
+  const bool k0 = !((b01 & b02) | (b01 & b03) | (b02 & b03));
+  const bool k3 = (b03 & b13) | (b03 & b23) | (b13 & b23);
+  // beaten: element 1 by 0 unless b01, by 2 if b12, by 3 if b13; element 2 by 0 unless b02, by 1 unless b12, by 3 if b23
+  const bool k1 = !((!b01 & b12) | (!b01 & b13) | (b12 & b13));
+  const bool k2 = !((!b02 & !b12) | (!b02 & b23) | (!b12 & b23));
+  const unsigned lo = k0 ? w0 : k1 ? w1 : w2, hi = k3 ? w3 : k2 ? w2 : w1;
+  pair = lo | (hi << 16);
+  return (k0 ? 0u : k1 ? 1u : 2u) | (k3 ? 12u : k2 ? 8u : 4u);
 }
 
 struct PruneFastArgs {
@@ -66,15 +69,21 @@ struct PruneFastArgs {
   int G;                   // row groups that sum columns in parallel
   unsigned short* values; unsigned char* meta; unsigned char* colidx; unsigned char* mask;
   uint4* pa; unsigned short* pidx; unsigned* pcol;   // matrix-core copy or null
-  const float* Sc; int64_t lds_s;                    // importance scores (SCORED instantiation only)
+  const float* Sc; int64_t lds_s;                    // importance scores (kScored only)
+  const double* prep;                                // f64 [3][in], [2][out]: what the RIA scores need (kRia only)
 };
+enum PruneBy { kAbs, kScored, kRia };
 
-// LDS layout (dynamic): tile u16 [V][NCP = NC + 4] | tot f64 [NC] | keep u32 [NBW] | (SCORED) scores f32 [V][NC + 4]
-// SCORED: the selections are driven by the score matrix a.Sc instead of |w| (Section 3, steps 2-3 on
-// any importance score, e.g. RIA, Eq. 1): column norms are the fp64 sums of the scores added in row
-// order (their value can depend on the order, so it is fixed), step 3 compares the scores; the kept
-// values are W's.  The plain instantiation is the kernel of the hot path, unchanged.
-template <bool SCORED>
+// LDS layout (dynamic): tile u16 [V][NCP = NC + 4] | tot f64 [NC] | keep u32 [NBW] | kScored: scores f32 [V][NC + 4],
+// kRia: prep f64 [3][NC], rows f64 [V][2], above u32 [4]
+// BY: what drives the selections of Section 3, steps 2-3.  kAbs: |w|, the kernel of the hot path.  kScored: the score matrix
+// a.Sc (any importance score); column norms are the fp64 sums of the scores added in row order (their value can depend
+// on the order, so it is fixed), step 3 compares the scores; the kept values are W's.  kRia: the same with RIA scores (Eq. 1)
+// computed from the weight tile and the sums of its rows and columns, once per element for the column norms and once more
+// per kept candidate: fp64 operations are cheaper than an fp32 tile next to the weights, which takes twice their room and
+// leaves a third of the workgroups (or of the span) per compute unit.  4096 x 4096 at 64:2:5 with the mask: 49 us, against
+// 19 for writing the scores and 57 for kScored reading them; 12 of the 49 are the norms' scores, 6 the candidates'.
+template <PruneBy BY>
 __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int V = a.V, M = a.M;
@@ -93,13 +102,31 @@ __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) 
   double* tot = (double*)(smem + (size_t)V * NCP * 2);
   unsigned* keep = (unsigned*)(tot + NC);
   float* stile = (float*)(keep + NBW);
+  double* prep = (double*)(keep + NBW);             // (NBW is a multiple of 8)
+  double* rows = prep + 3 * (size_t)NC;
+  unsigned* above = (unsigned*)(rows + 2 * V);
   const int NCS = NC + 4;                           // score tile pitch in floats (16-byte rows)
   const int tid = threadIdx.x;
   const int chunks = NC / 8;
 
   for (int c = tid; c < NC; c += 256) tot[c] = 0.0;
   for (int b = tid; b < NBW; b += 256) keep[b] = 0;
-  __syncthreads();
+  // kRia: what the scores need of column c0 + tid and of row tid travels while the weights are requested
+  double pcol[3] = {0.0, 0.0, 0.0}, prow[2] = {0.0, 0.0};
+  if constexpr (BY == kRia) {
+    const bool col_ok = tid < NC && c0 + tid < a.in, row_ok = tid < V && r * V + tid < a.out;
+    const double* pc = a.prep + (col_ok ? c0 + tid : 0);
+    const double* pr = a.prep + 3 * a.in + (row_ok ? r * V + tid : 0);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) pcol[k] = pc[k * a.in];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) prow[k] = pr[k * a.out];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) pcol[k] = col_ok ? pcol[k] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) prow[k] = row_ok ? prow[k] : 0.0;
+  }
+  if constexpr (BY == kAbs) __syncthreads();        // (the sums start from zero)
   // phase 0: W tile -> LDS, 16 bytes per load and two 8-byte halves per store (zero where W is padded); the same registers feed
   // the column sums: thread (g, ch) owns 8 columns and the rows g, g + G, g + 2G, ...; the partial
   // sums meet in LDS by atomic adds (exact, so their order is immaterial)
@@ -142,7 +169,7 @@ __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) 
           td[0] = make_uint2(w[u].x, w[u].y);
           td[1] = make_uint2(w[u].z, w[u].w);
           const unsigned d[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
-          if constexpr (!SCORED) {
+          if constexpr (BY == kAbs) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               acc[2 * e] += fp16_abs_f64(d[e]);
@@ -152,12 +179,12 @@ __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) 
         }
       }
     }
-    if constexpr (!SCORED) {
+    if constexpr (BY == kAbs) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) unsafeAtomicAdd(tot + ch * 8 + e, acc[e]);
     }
   }
-  if constexpr (SCORED) {
+  if constexpr (BY == kScored) {
     // score tile -> LDS with 16-byte accesses (zero where the matrix is padded), then one thread per
     // column adds its V scores in row order
     const int chunks4 = NC / 4;
@@ -201,6 +228,38 @@ __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) 
       }
       tot[c] = acc;
     }
+  }
+  if constexpr (BY == kRia) {
+    if (tid < NC) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) prep[k * NC + tid] = pcol[k];
+    }
+    for (int c = tid + 256; c < NC; c += 256)
+      for (int k = 0; k < 3; ++k) prep[k * NC + c] = c0 + c < a.in ? a.prep[k * a.in + c0 + c] : 0.0;
+    if (tid < V) { rows[2 * tid] = prow[0]; rows[2 * tid + 1] = prow[1]; }
+    bool large = pcol[0] > kScSmall || prow[0] > kScSmall;
+    for (int c = tid + 256; c < NC; c += 256) large |= prep[c] > kScSmall;          // (this thread's own stores)
+    const bool any = __ballot(large) != 0;
+    if ((tid & 63) == 0) above[tid >> 6] = any;
+    __syncthreads();
+    const bool small = !(above[0] | above[1] | above[2] | above[3]);
+    auto norms = [&](auto sm) {
+      for (int c = tid; c < NC; c += 256) {
+        const double cd = prep[c], cy = prep[NC + c], ad = prep[2 * NC + c];
+        double acc = 0.0;
+        // V is a multiple of 32: 8 scores at a time, added in row order (rows and columns of the padding score 0)
+        for (int v = 0; v < V; v += 8) {
+          float x[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            x[u] = sc_ria<decltype(sm)::value>(tile[(size_t)(v + u) * NCP + c], cd, cy, ad, rows[2 * (v + u)], rows[2 * (v + u) + 1]);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) acc += (double)x[u];
+        }
+        tot[c] = acc;
+      }
+    };
+    if (small) norms(std::true_type{}); else norms(std::false_type{});
   }
   __syncthreads();
   // phase 1: per block keep the 4 columns of largest L1 norm (ties to the lower index), ascending:
@@ -248,7 +307,7 @@ __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) 
     const int blk0 = ks * 8 + 4 * h;
     const uint4 kp4 = *(const uint4*)(keep + blk0);
     const unsigned kp[4] = {kp4.x, kp4.y, kp4.z, kp4.w};
-    unsigned short ixs[4] = {0, 0, 0, 0};
+    unsigned ixlo = 0, ixhi = 0;                              // positions of tiles 0, 1 and 2, 3
     for (int at = 0; at < tiles; ++at) {
       const int v = at * 32 + i;
       unsigned short* trow = tile + (size_t)v * NCP + blk0 * M;
@@ -259,18 +318,28 @@ __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) 
         const unsigned w0 = tb[kp[g] & 255u], w1 = tb[(kp[g] >> 8) & 255u], w2 = tb[(kp[g] >> 16) & 255u],
                        w3 = tb[kp[g] >> 24];
         unsigned nib;
-        if constexpr (SCORED) {
+        if constexpr (BY == kRia) {
+          const int cb = (blk0 + g) * M;
+          const double rd = rows[2 * v], ry = rows[2 * v + 1];
+          const unsigned w4[4] = {w0, w1, w2, w3};
+          unsigned sc[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int c = cb + (int)((kp[g] >> (8 * k)) & 255u);
+            sc[k] = __float_as_uint(sc_ria(w4[k], prep[c], prep[NC + c], prep[2 * NC + c], rd, ry)) & 0x7FFFFFFFu;
+          }
+          nib = top2_of_4_s(sc[0], sc[1], sc[2], sc[3], w0, w1, w2, w3, q[g]);
+        } else if constexpr (BY == kScored) {
           const float* sb = stile + (size_t)v * NCS + (blk0 + g) * M;
           nib = top2_of_4_s(__float_as_uint(sb[kp[g] & 255u]) & 0x7FFFFFFFu, __float_as_uint(sb[(kp[g] >> 8) & 255u]) & 0x7FFFFFFFu,
-                            __float_as_uint(sb[(kp[g] >> 16) & 255u]) & 0x7FFFFFFFu, __float_as_uint(sb[kp[g] >> 24]) & 0x7FFFFFFFu);
-          const unsigned w4[4] = {w0, w1, w2, w3};
-          q[g] = w4[nib & 3] | (w4[nib >> 2] << 16);
+                            __float_as_uint(sb[(kp[g] >> 16) & 255u]) & 0x7FFFFFFFu, __float_as_uint(sb[kp[g] >> 24]) & 0x7FFFFFFFu,
+                            w0, w1, w2, w3, q[g]);
         } else {
           nib = top2_of_4_f(w0, w1, w2, w3, q[g]);
         }
         ix |= nib << (4 * g);
       }
-      ixs[at] = (unsigned short)ix;
+      if (at < 2) ixlo |= ix << (16 * at); else ixhi |= ix << (16 * (at - 2));
       if (a.pa) {
         const int64_t gt = r * tiles + at;
         a.pa[(((gt >> 1) * a.S + s_begin + ks) * 2 + (gt & 1)) * 64 + lane] = make_uint4(q[0], q[1], q[2], q[3]);
@@ -282,7 +351,7 @@ __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) 
     }
     if (a.pa) {
       if (tiles == 1) {
-        a.pidx[(((r >> 1) * a.S + s_begin + ks) * 64 + lane) * 2 + (r & 1)] = ixs[0];
+        a.pidx[(((r >> 1) * a.S + s_begin + ks) * 64 + lane) * 2 + (r & 1)] = (unsigned short)ixlo;
         if (odd_tail) {           // the missing second tile: values 0, positions (0, 1)
           a.pa[(((r >> 1) * a.S + s_begin + ks) * 2 + 1) * 64 + lane] = make_uint4(0, 0, 0, 0);
           a.pidx[(((r >> 1) * a.S + s_begin + ks) * 64 + lane) * 2 + 1] = (unsigned short)0x4444u;
@@ -290,7 +359,7 @@ __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) 
       } else {
         for (int sb = 0; sb < tiles / 2; ++sb)
           *(unsigned*)(a.pidx + (((r * (tiles / 2) + sb) * a.S + s_begin + ks) * 64 + lane) * 2) =
-              (unsigned)ixs[2 * sb] | ((unsigned)ixs[2 * sb + 1] << 16);
+              sb ? ixhi : ixlo;
       }
     }
   }
@@ -352,20 +421,46 @@ __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) 
       }
     }
   }
-  // phase 4: optional dense 0-1 mask, from the positions parked in the tile
-  if (a.mask) {
-    for (int item = tid; item < V * NBW; item += 256) {
-      const int v = item / NBW, b = item - v * NBW;
-      if (b >= nbw) continue;
-      const int64_t row = r * V + v;
-      if (row >= a.out) continue;
-      const unsigned ix = tile[(size_t)v * NCP + (b & ~3) * M + 8];
-      const unsigned nib = (ix >> (4 * (b & 3))) & 15u;
-      const unsigned kp = keep[b];
-      const unsigned ca = (kp >> (8 * (nib & 3))) & 255u, cb = (kp >> (8 * (nib >> 2))) & 255u;
-      const int64_t colb = (b0 + b) * M;
-      for (int c = 0; c < M; ++c)
-        if (colb + c < a.in) a.mask[row * a.in + colb + c] = (unsigned char)((unsigned)c == ca || (unsigned)c == cb);
+  // phase 4: optional dense 0-1 mask, from the positions parked in the tile.  Thread (g, ch) owns 8 columns, as in phase 0:
+  // it gathers the kept columns of the up to three blocks they lie in as bits and stores the 8 of them as bytes.
+  // (A block per thread and a store per byte: pruning with mask at 64:2:5 and 11008 x 4096 73 us, now 49; 4096 x 4096 at
+  // V = 128, M = 16 34 and 18)
+  if (a.mask && tid < chunks * G) {
+    const int g = tid / chunks, ch = tid - g * chunks;
+    const int first = ch * 8 / M;                             // its first block
+    const int skip = ch * 8 - first * M;                      // columns of that block in front of it
+    unsigned kp[3];
+    int at[3];                                                // where a row keeps the block's positions
+    unsigned sh[3];
+#pragma unroll
+    for (int n = 0; n < 3; ++n) {
+      const int b = first + n < NBW ? first + n : NBW - 1;
+      kp[n] = keep[b];
+      at[n] = (b & ~3) * M + 8;
+      sh[n] = 4 * (b & 3);
+    }
+    const bool mask8 = ((uintptr_t)a.mask & 7) == 0;
+    unsigned char* dst = a.mask + r * V * a.in + c0 + ch * 8;
+    const int64_t rows_left = a.out - r * V;
+    const int v_real = c0 + ch * 8 >= a.in || rows_left <= 0 ? 0 : (rows_left < V ? (int)rows_left : V);
+    for (int v = g; v < v_real; v += G) {
+      const unsigned short* trow = tile + (size_t)v * NCP;
+      unsigned bits[3];
+#pragma unroll
+      for (int n = 0; n < 3; ++n) {
+        const unsigned nib = (unsigned)trow[at[n]] >> sh[n];
+        bits[n] = (1u << ((kp[n] >> (8 * (nib & 3))) & 31u)) | (1u << ((kp[n] >> (8 * ((nib >> 2) & 3))) & 31u));
+      }
+      // columns skip .. skip + 7 counted from the first block; a block starts M columns after the one before it
+      const unsigned b8 = (unsigned)((((unsigned long long)bits[2] << (2 * M)) | ((unsigned long long)bits[1] << M) | bits[0]) >> skip);
+      // bit e of a nibble to byte e
+      const unsigned lo = ((b8 & 15u) * 0x00204081u) & 0x01010101u, hi = (((b8 >> 4) & 15u) * 0x00204081u) & 0x01010101u;
+      unsigned char* p = dst + (int64_t)v * a.in;
+      if (mask8) *(uint2*)p = make_uint2(lo, hi);
+      else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = (unsigned char)((e < 4 ? lo : hi) >> (8 * (e & 3)));
+      }
     }
   }
 }
@@ -412,11 +507,41 @@ int launch_prune_fast_scored(const void* W, int64_t ldw, const void* S, int64_t 
     a.pa = (uint4*)(p + pl.pa_off); a.pidx = (unsigned short*)(p + pl.pidx_off); a.pcol = (unsigned*)(p + pl.pcol_off);
   }
   const size_t lds = (size_t)prune_fast_lds(d.V, d.M, a.KSW, true);
-  if (int rc_lds = allow_big_lds((const void*)prune_pack_kernel<true>, "hipFuncSetAttribute(prune_pack scored)")) return rc_lds;
+  if (int rc_lds = allow_big_lds((const void*)prune_pack_kernel<kScored>, "hipFuncSetAttribute(prune_pack scored)")) return rc_lds;
   dim3 grid((unsigned)((d.S + a.KSW - 1) / a.KSW), (unsigned)d.R);
-  hipLaunchKernelGGL(prune_pack_kernel<true>, grid, dim3(256), lds, st, a);
+  hipLaunchKernelGGL(prune_pack_kernel<kScored>, grid, dim3(256), lds, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "prune_pack_kernel<scored>"); return VNM_ERR_HIP; }
+  return VNM_OK;
+}
+
+// RIA scores computed on the fly
+bool prune_fast_ria_applicable(const void* W, int64_t ldw, const Dims& d) {
+  return prune_fast_applicable(W, ldw, d, nullptr) && prune_ria_lds(d.V, d.M, 1) <= 64 * 1024;
+}
+
+int launch_prune_fast_ria(const void* W, int64_t ldw, const double* prep, const Dims& d,
+                          void* values, void* meta, void* colidx, void* mask, void* packed, hipStream_t st) {
+  PruneFastArgs a{};
+  a.W = (const unsigned short*)W; a.ldw = ldw; a.out = d.out; a.in = d.in; a.V = d.V; a.M = d.M;
+  a.R = d.R; a.B = d.B; a.S = d.S;
+  a.prep = prep;
+  a.KSW = prune_ria_steps(d.V, d.M, d.R, d.S);
+  const int chunks = a.KSW * d.M;
+  a.G = 256 / chunks < d.V ? 256 / chunks : d.V;
+  a.values = (unsigned short*)values; a.meta = (unsigned char*)meta; a.colidx = (unsigned char*)colidx;
+  a.mask = (unsigned char*)mask;
+  if (packed) {
+    const PackedLayout pl = packed_layout(d);
+    char* p = (char*)packed;
+    a.pa = (uint4*)(p + pl.pa_off); a.pidx = (unsigned short*)(p + pl.pidx_off); a.pcol = (unsigned*)(p + pl.pcol_off);
+  }
+  const size_t lds = (size_t)prune_ria_lds(d.V, d.M, a.KSW);
+  if (int rc_lds = allow_big_lds((const void*)prune_pack_kernel<kRia>, "hipFuncSetAttribute(prune_pack ria)")) return rc_lds;
+  dim3 grid((unsigned)((d.S + a.KSW - 1) / a.KSW), (unsigned)d.R);
+  hipLaunchKernelGGL(prune_pack_kernel<kRia>, grid, dim3(256), lds, st, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) { set_hip_error(e, "prune_pack_kernel<ria>"); return VNM_ERR_HIP; }
   return VNM_OK;
 }
 
@@ -437,12 +562,12 @@ int launch_prune_fast(const void* W, int64_t ldw, const Dims& d, void* values, v
     a.pa = (uint4*)(p + pl.pa_off); a.pidx = (unsigned short*)(p + pl.pidx_off); a.pcol = (unsigned*)(p + pl.pcol_off);
   }
   const size_t lds = (size_t)prune_fast_lds(d.V, d.M, a.KSW, false);
-  if (int rc_lds = allow_big_lds((const void*)prune_pack_kernel<false>, "hipFuncSetAttribute(prune_pack)")) return rc_lds;
+  if (int rc_lds = allow_big_lds((const void*)prune_pack_kernel<kAbs>, "hipFuncSetAttribute(prune_pack)")) return rc_lds;
   // column spans along x: the workgroups that run together then read whole rows of W (every memory
   // channel in use) instead of one window of columns in many rows; on weights that come from HBM
   // 11008 x 4096 takes 62 us instead of 71, 4096 x 11008 66 instead of 71, 4096 x 4096 the same
   dim3 grid((unsigned)((d.S + a.KSW - 1) / a.KSW), (unsigned)d.R);
-  hipLaunchKernelGGL(prune_pack_kernel<false>, grid, dim3(256), lds, st, a);
+  hipLaunchKernelGGL(prune_pack_kernel<kAbs>, grid, dim3(256), lds, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "prune_pack_kernel"); return VNM_ERR_HIP; }
   return VNM_OK;

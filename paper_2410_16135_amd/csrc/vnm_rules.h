@@ -174,4 +174,20 @@ inline int prune_scored_steps(int V, int M, int64_t row_blocks, int64_t steps) {
   return k;
 }
 
+// Pruning from RIA scores computed on the fly (mask refresh): weight tile u16 [V][NC + 4], column sums f64 [NC], kept columns
+// u32 [blocks], f64 [3][NC] of the columns and [2][V] of the rows, four flags
+inline int64_t prune_ria_lds(int V, int M, int steps) {
+  const int64_t NC = (int64_t)steps * 8 * M, blocks = (int64_t)steps * 8;
+  return V * (NC + 4) * 2 + NC * 8 + blocks * 4 + 3 * NC * 8 + 2 * V * 8 + 16;
+}
+// Whole refresh of 4096 x 4096, us, with 2 / 4 / 8 steps: V = 64, M = 5 98 / 82 / 91; V = 64, M = 8 75 / 69 / 85; V = 128,
+// M = 5 95 / 87 / 117; V = 64, M = 12 (80 KiB at 4) 72 / 80 / 102; V = 32, M = 8 (49 KiB at 8) 82 / 69 / 70 and on 2000 x 3000
+// 43 / 37 / 41; V = 32, M = 4 120 / 90 / 79.  Fewer where that leaves too few workgroups: 200 x 304 at V = 128, M = 8 with
+// 1 / 2 / 4 / 8 steps 32 / 34 / 36 / 55; 1000 x 1000 at V = 32, M = 8 25.0 / 24.3 / 24.4 / 30.2.
+inline int prune_ria_steps(int V, int M, int64_t row_blocks, int64_t steps) {
+  int k = 8;
+  while (k > 1 && (prune_ria_lds(V, M, k) > (k > 4 ? 40 : 50) * 1024 || (steps + k - 1) / k * row_blocks < (k > 4 ? 512 : 160))) k >>= 1;
+  return k;
+}
+
 }  // namespace vnm

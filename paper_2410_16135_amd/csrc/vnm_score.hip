@@ -9,6 +9,7 @@
 #include <type_traits>
 #include "vnm_internal.h"
 #include "vnm_rules.h"
+#include "vnm_score.h"
 
 namespace vnm {
 
@@ -116,20 +117,6 @@ abs_rowsum_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in,
   if (lane == 0) rowsum[row] = acc;
 }
 
-// a / b rounded to nearest, from y = 1 / b rounded to nearest: q0 = a y is within 1.5 ulp, one correction
-// makes q1 a faithful quotient, and for a faithful quotient the second one gives the correctly rounded result
-// (Markstein's theorem).  It needs exact residuals, so nothing may overflow or underflow: a is 0 or k 2^-136 with an
-// integer k < 2^41, b an integer-valued double up to 2^63, so quotients are at least 2^-199 and residuals, multiples of
-// 2^-136 or of half an ulp of the quotient, above 2^-252.  (a comes from an fp32 conversion that keeps subnormals: fp32
-// denormals must not be flushed in this file.)
-// Five operations per element; the division by itself takes about fifteen, two of them per element
-// (53 us on 4096 x 4096, of which the memory traffic needs a third).
-__device__ __forceinline__ double sc_div(double a, double b, double y) {
-  const double q0 = a * y;
-  const double q1 = fma(fma(-b, q0, a), y, q0);
-  return fma(fma(-b, q1, a), y, q1);
-}
-
 // Scores: thread t owns 4 adjacent columns (`vec`: one 8-byte load of W and one 16-byte store of S per
 // row) of kScoreRows rows (score_rows); the reciprocals are taken once per column and thread and once per row and
 // workgroup.
@@ -168,11 +155,7 @@ ria_score_kernel(const unsigned short* __restrict__ W, int64_t out, int64_t in, 
       const double rd = rsum[v], ry = rrec[v];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        // the 15 magnitude bits read as fp32 are the magnitude times 2^-112 (subnormals and the top exponent
-        // included): units times 2^-136, a scale that act takes back exactly
-        const double a = (double)__uint_as_float((unsigned)(h[e] & 0x7FFFu) << 13);
-        const double sum = sc_div(a, cd[e], cy[e]) + sc_div(a, rd, ry);
-        sc[e] = (float)(sum * ad[e]);
+        sc[e] = sc_ria(h[e], cd[e], cy[e], ad[e], rd, ry);
       }
     };
     if (whole) {
@@ -367,8 +350,6 @@ int launch_prune_scored(const void* W, int64_t ldw, const void* S, int64_t lds, 
 // 16-byte accesses, B[o, :] is uniform over the threads of a row.
 namespace vnm {
 
-constexpr int kMergeRows = 8;   // rows per thread: A is fetched once per 8 rows instead of once per row
-
 __global__ void __launch_bounds__(256)
 lora_merge_kernel(const unsigned short* __restrict__ W, int64_t ldw, const float* __restrict__ B, int64_t ldb,
                   const float* __restrict__ A, int64_t lda, int r, float scale, int64_t out, int64_t in,
@@ -386,52 +367,13 @@ lora_merge_kernel(const unsigned short* __restrict__ W, int64_t ldw, const float
   for (int v = 0; v < kMergeRows; ++v)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[v][e] = 0.f;
-  // whole tiles with aligned rows: W and four rows of A at a time are requested before the first use (one row
-  // per trip left a memory round trip exposed per k: 28 us on 4096 x 4096 at r = 16)
+  // whole tiles with aligned rows
   if (vec && avec && n == 8 && rows == kMergeRows) {
-    uint4 w4[kMergeRows];
+    uint4 w[kMergeRows], m[kMergeRows];
+    merge_load<false>(W + o0 * ldw + i0, ldw, kMergeRows - 1, w);
+    merge_tile<false>(w, B + o0 * ldb, ldb, A + i0, lda, r, scale, kMergeRows - 1, m);
 #pragma unroll
-    for (int v = 0; v < kMergeRows; ++v) w4[v] = *(const uint4*)(W + (o0 + v) * ldw + i0);
-    auto steps = [&](int k, auto count) {
-#pragma clang fp contract(off)
-      constexpr int K = decltype(count)::value;
-      float4 a0[K], a1[K];
-#pragma unroll
-      for (int u = 0; u < K; ++u) {
-        a0[u] = *(const float4*)(A + (int64_t)(k + u) * lda + i0);
-        a1[u] = *(const float4*)(A + (int64_t)(k + u) * lda + i0 + 4);
-      }
-#pragma unroll
-      for (int u = 0; u < K; ++u) {
-        const float a[8] = {a0[u].x, a0[u].y, a0[u].z, a0[u].w, a1[u].x, a1[u].y, a1[u].z, a1[u].w};
-#pragma unroll
-        for (int v = 0; v < kMergeRows; ++v) {
-          const float b = B[(o0 + v) * ldb + k + u];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) { const float p = b * a[e]; acc[v][e] = acc[v][e] + p; }
-        }
-      }
-    };
-    int k = 0;
-    for (; k + 4 <= r; k += 4) steps(k, std::integral_constant<int, 4>{});
-    for (; k < r; ++k) steps(k, std::integral_constant<int, 1>{});
-#pragma unroll
-    for (int v = 0; v < kMergeRows; ++v) {
-      const unsigned d[4] = {w4[v].x, w4[v].y, w4[v].z, w4[v].w};
-      unsigned m[4];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const unsigned short hb = (unsigned short)(d[e / 2] >> (16 * (e & 1)));
-        _Float16 h;
-        __builtin_memcpy(&h, &hb, 2);
-        const float sp = scale * acc[v][e];
-        const _Float16 res = (_Float16)(sp + (float)h);
-        unsigned short rb;
-        __builtin_memcpy(&rb, &res, 2);
-        m[e / 2] = (e & 1) ? (m[e / 2] | ((unsigned)rb << 16)) : rb;
-      }
-      *(uint4*)(Wm + (o0 + v) * ldm + i0) = make_uint4(m[0], m[1], m[2], m[3]);
-    }
+    for (int v = 0; v < kMergeRows; ++v) *(uint4*)(Wm + (o0 + v) * ldm + i0) = m[v];
     return;
   }
   for (int k = 0; k < r; ++k) {

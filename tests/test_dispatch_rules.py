@@ -127,3 +127,11 @@ def test_sizes_of_the_plain_kernels(rule, T, out, inn, fit):
     (1000, 127, 40, 2), (1000, 128, 96, 2), (1000, 128, 95, 1), (1000, 129, 103, 1), (1000, 129, 191, 1), (1000, 191, 192, 2)])
 def test_split_pieces(rule, T, pairs, steps, pieces):
     assert rule("split_pieces(%d, %d, %d)" % (T, pairs, steps)) == pieces
+
+
+# K steps of a workgroup of the pruning inside a mask refresh (V, M, row blocks, steps)
+@pytest.mark.parametrize("V,M,R,S,k", [(64, 5, 64, 103, 4), (32, 4, 128, 128, 8), (64, 8, 64, 64, 4), (64, 12, 64, 43, 2), (128, 16, 32, 32, 1),
+                                       (128, 16, 2, 3, 1), (32, 5, 3, 3, 1), (64, 8, 16, 16, 1)])
+def test_refresh_pruning_steps(rule, V, M, R, S, k):
+    assert rule("prune_ria_steps(%d, %d, %d, %d)" % (V, M, R, S)) == k
+    assert rule("prune_ria_lds(%d, %d, %d)" % (V, M, k)) <= 64 * 1024

@@ -69,6 +69,52 @@ def test_refreshed_mask_bit_exact(out, inn, V, M, with_act):
                           orc.masked_dense(merged, mask).view(np.uint16))
 
 
+# One call for the whole refresh: tiles of 32 rows x 512 columns cut off on both sides, one and two column tiles, row tiles
+# beyond one group of 32, an odd number of 32-row blocks, every width of a span, ranks around the groups of four; weights
+# whose sums pass 2^24 (the division then takes its second correction); and rows that are not 16-byte aligned (single steps).
+@pytest.mark.parametrize("out,inn,V,M,r,amp", [(32, 8, 32, 4, 1, 1.0), (33, 520, 32, 16, 3, 1.0), (95, 512, 64, 5, 4, 1.0),
+                                               (1100, 24, 128, 8, 7, 1.0), (160, 1032, 32, 5, 16, 1.0), (200, 304, 64, 12, 33, 1.0),
+                                               (900, 200, 64, 5, 2, 3.0e6), (64, 1000, 128, 16, 0, 1.0), (70, 1030, 64, 5, 4, 1.0)])
+def test_refresh_in_one_call(out, inn, V, M, r, amp):
+    rng = np.random.default_rng(out + inn)
+    W, _ = syn.make_weight_and_input(out, inn, 1, seed=M)
+    W = np.clip(W.astype(np.float32) * amp, -60000.0, 60000.0).astype(np.float16)
+    B, A = _adapter(rng, out, inn, r, amp=0.1)
+    act = (0.5 + rng.random(inn)).astype(np.float32)
+    if amp > 1:
+        assert float(np.abs(W.astype(np.float64)).sum(0).max()) > 2.0 ** 24 > float(np.abs(W.astype(np.float64)).sum(1).min())
+    c = vnm.vnm_refresh_mask(_dev(W), _dev(B), _dev(A), 2.0, V, M, act=_dev(act))
+    torch.cuda.synchronize()
+    merged, mask = orc.refresh_mask(W, B, A, 2.0, V, M, act)
+    values, meta, colidx, _ = orc.compress(merged, V, M, score=orc.importance_ria(merged, act))
+    assert np.array_equal(c.mask.cpu().numpy(), mask)
+    assert np.array_equal(c.values.cpu().numpy().view(np.uint16), values.reshape(-1).view(np.uint16))
+    assert np.array_equal(c.meta.cpu().numpy(), meta.reshape(-1))
+    assert np.array_equal(c.colidx.cpu().numpy(), colidx.reshape(-1))
+    # the single steps end in the same matrix-core copy, padding aside: the same product on it
+    m = vnm.vnm_lora_merge(_dev(W), _dev(B), _dev(A), 2.0)
+    c3 = vnm.vnm_prune_compress_scored(m, vnm.vnm_ria_scores(m, _dev(act)), V, M, want_mask=True)
+    if inn % 8 == 0:
+        X = torch.ones((40, inn), dtype=torch.float16, device=DEV)
+        assert torch.equal(vnm.vnm_spmm(X, c, out_dtype=torch.float32), vnm.vnm_spmm(X, c3, out_dtype=torch.float32))
+
+
+@pytest.mark.parametrize("out,inn,V,M", [(70, 104, 32, 4), (200, 304, 64, 5), (130, 1000, 128, 16), (64, 72, 64, 9)])
+def test_mask_at_any_address(out, inn, V, M):
+    W, _ = syn.make_weight_and_input(out, inn, 1, seed=M)
+    c = vnm.vnm_prune_compress(_dev(W), V, M, want_mask=True)
+    want = orc.compress(W, V, M)[3]
+    assert np.array_equal(c.mask.cpu().numpy(), want)
+    buf = torch.full((out * inn + 64,), 7, dtype=torch.uint8, device=DEV)
+    for off in (1, 8, 12):
+        buf.fill_(7)
+        c.mask = buf[off:off + out * inn].view(out, inn)
+        vnm.vnm_prune_compress(_dev(W), V, M, out=c)
+        got = buf.cpu().numpy()
+        assert np.array_equal(got[off:off + out * inn].reshape(out, inn), want)
+        assert (got[:off] == 7).all() and (got[off + out * inn:] == 7).all()      # nothing around it is touched
+
+
 def test_merge_llama_shaped_layer_full_size():
     layer = syn.config_llama2_7b()[0]
     W, _ = syn.layer_tensors(layer, tokens=1)
