@@ -141,6 +141,49 @@ inline bool tiles_by_xcd(int64_t tiles, int64_t groups, int64_t steps, int piece
   return pieces > 1 ? saved >= (4 << 20) && steps / pieces >= 10 : saved >= (8 << 20);
 }
 
+// The numberings: grid order, runs (the XCD order above), and boxes: the XCDs form a grid of 2^log_t parts of the token
+// tiles x 8 / 2^log_t parts of the groups, each takes one box, token tiles fastest; boxes differ by at most one in each
+// direction, the launch is 8 of the largest.
+struct XcdOrder {
+  enum Kind { kGrid, kRuns, kBoxes } kind;
+  unsigned log_t;
+};
+inline unsigned xcd_box_most(int64_t tiles, int64_t groups, unsigned log_t) {
+  const int64_t xt = 1 << log_t, xg = 8 / xt;
+  return (unsigned)(((tiles + xt - 1) / xt) * ((groups + xg - 1) / xg));
+}
+// Boxes for two kinds of unsplit launches.
+// A single generation (two wave groups, below): the grid that makes an XCD fetch least without a second one.  4096 x 4096 at
+// M = 5, 16 tiles x 16 groups 45.4 -> 44.4 us against runs, 12 x 16 42.9 -> 42.7; M = 8 32.4 -> 30.9.
+// Otherwise 8 parts of the tiles (8 row blocks per workgroup only: the others carry no code for it), where runs and grid order make every XCD fetch most of X (the number of tiles not a
+// multiple of 8) and the weight is the smaller part: 3072 x 768 at M = 8 and 12608 tokens (99 tiles) 48 -> 40 us, 2304 x 1536 at
+// 6000 (47) 26.0 -> 20.3, 10174 x 2824 at 2888 (23 tiles, 3 MiB less per XCD) 147 -> 140.  Boxes in other shapes lose on more than one generation: 11008 x 4096 at V = 32, M = 5 and 2048 tokens
+// in 2 x 4 boxes 46.0 -> 49.1.
+inline XcdOrder xcd_order(int64_t tiles, int64_t groups, int64_t steps, int pieces, int64_t weight_bytes, int64_t staged_bytes,
+                          bool one_generation, bool wide, bool in_l2) {
+  XcdOrder o{XcdOrder::kGrid, 0};
+  if (in_l2) return o;
+  const double w = (double)weight_bytes, x = (double)staged_bytes;
+  if (one_generation) {
+    const int64_t share = (tiles * groups + 7) / 8;
+    double best = 1e300;
+    for (unsigned l = 0; l <= 3; ++l) {
+      const int64_t xt = 1 << l, xg = 8 / xt;
+      if (tiles < xt || groups < xg || (xcd_box_most(tiles, groups, l) > 32 && share <= 32)) continue;
+      const double bytes = w * (double)((groups + xg - 1) / xg) / (double)groups + x * (double)((tiles + xt - 1) / xt) / (double)tiles;
+      if (bytes < best) { best = bytes; o = {XcdOrder::kBoxes, l}; }
+    }
+    return o;
+  }
+  if (tiles_by_xcd(tiles, groups, steps, pieces, weight_bytes, staged_bytes, in_l2)) o.kind = XcdOrder::kRuns;
+  if (pieces == 1 && tiles >= 16 && wide) {
+    const int64_t residues = tiles % 8 == 0 ? 8 : tiles % 4 == 0 ? 4 : tiles % 2 == 0 ? 2 : 1;
+    const double now = o.kind == XcdOrder::kRuns ? w / 8 + x : w + x / (double)residues;
+    if (now - (w + x / 8) >= 1048576.0) o = {XcdOrder::kBoxes, 3};
+  }
+  return o;
+}
+
 // ---- the staged product's deep K loop: six operand sets and images in flight instead of three or four
 // For pieces of a split K on a launch that leaves compute units without a workgroup: a step then waits for its operands
 // rather than for the matrix cores.  Most where the other loop has a ring of three images only (M >= 8): 4096 x 11008 at
@@ -153,6 +196,17 @@ inline bool tiles_by_xcd(int64_t tiles, int64_t groups, int64_t steps, int piece
 // the image per wave, which is M = 9.
 inline bool deep_loop(int pieces, int64_t workgroups, int64_t last_piece, int64_t row_blocks, int64_t steps, int M, int tables) {
   return pieces > 1 && workgroups < 256 && last_piece >= (M >= 8 ? 8 : 48) && row_blocks * steps >= 64 && M <= 9 && tables == 1;
+}
+
+// ---- the staged product with two groups of waves per workgroup, each on half of the steps
+// For unsplit launches of at most one workgroup of 4 row blocks per compute unit: with 8 row blocks they would leave half
+// of the units idle, with one wave per SIMD every step waits for its operands.  Weights from HBM, before / with two groups:
+// 4096 x 4096 at 2048 tokens (256 workgroups) M = 5 61.6 / 44.4 us, M = 8 41.5 / 30.9, V = 32 and M = 8 46.8 / 33.4; at 1500
+// (192) 60.9 / 42.7; 8192 x 4096 at 1024 63.4 / 46.0; 11008 x 4096 at 300 63.0 / 43.9; 5504 x 2048 at 1000 33.4 / 25.0.
+// Pieces of a split K keep the deep loop (4096 x 4096 at 700 tokens 33.0 against 34.3 with two groups; two groups instead of
+// the split 42).  LDS holds two rings up to M = 10.
+inline bool kgroups(int pieces, int64_t workgroups, int64_t steps, int M) {
+  return pieces == 1 && workgroups <= 256 && steps >= 8 && M <= 10;
 }
 
 // ---- pruning (vnm_prune_fast.hip): K steps of 8 column blocks that a workgroup takes at a time

@@ -425,7 +425,8 @@ struct SpmmArgs {
   int64_t ks_steps, z_stride;
   // fused epilogue (null = none): bias per weight row, destination channel per weight row
   const _Float16* bias; const int* perm_out;
-  int tiles_per_xcd; // 1: the token tiles of one (row group, K piece) run on one XCD, see launch_spmm_smfmac
+  XcdOrder order;                  // numbering of the workgroups over the XCDs
+  unsigned tiles, groups;          // token tiles and groups of row blocks of the launch
 };
 
 // One K step = 8 column blocks = 8*M raw input columns = 32 compacted K = one staged image.
@@ -434,40 +435,58 @@ struct SpmmArgs {
 // DUAL: the packed row blocks carry two column tables (V = 32 patterns), assembly loop only.
 // FUSED: the epilogue looks at bias and perm_out (the plain instantiation ignores them and is exactly
 // the kernel the benchmark times).
-template <int V, int TW, int WR, int WT, int NCW, int NBUF, bool DUAL, bool FUSED>
-__global__ void __launch_bounds__(64 * WR * WT)
+// KG: groups of WR waves that share the row blocks and tokens and cut the workgroup's K range into KG parts, each with
+// a ring of images of its own; at the end each group takes the sums of its share of the tokens over through LDS.  For
+// launches of at most one workgroup per compute unit (see kgroups): one wave per SIMD waits at every step for what it
+// requested, two of them keep the matrix cores busy in turn, and no partial product leaves the chip.
+template <int V, int TW, int WR, int KG, int NCW, int NBUF, bool DUAL, bool FUSED, bool BOXES>
+__global__ void __launch_bounds__(64 * WR * KG)
 spmm_smfmac_kernel(const SpmmArgs a) {
-  constexpr int AT = V / 32, BT = TW / 32, NW = WR * WT;
-  static_assert(WT * TW == kTokTile, "a workgroup spans one staged token tile");
+  constexpr int AT = V / 32, BT = TW / 32, NW = WR;
+  static_assert(TW == kTokTile, "a workgroup spans one staged token tile");
+  static_assert(KG == 1 || KG == 2, "the exchange at the end is written for two groups");
   static_assert(BT <= 4 && AT <= 4, "tiling assumed by the step body");
   constexpr int P = kImagePitch;
   static_assert(V == 64 && TW == 128 && NCW > 0, "the K loop exists as the assembly loop for 64-row blocks only");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wr = wave / WT, wt = wave % WT;
-  // Workgroup n of the launch runs on XCD n mod 8, each with an L2 of its own.  With tiles_per_xcd the
-  // workgroups of one XCD take consecutive (K piece, row group, token tile) triples, tiles fastest.
+  const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = KG == 1 ? 0 : wave_id / WR, wave = KG == 1 ? wave_id : wave_id % WR, wr = wave;
+  // Workgroup n of the launch runs on XCD n mod 8, each with an L2 of its own; see XcdOrder for the numberings.
   unsigned tile_id = blockIdx.x, group_id = blockIdx.y, piece_id = blockIdx.z;
-  if (a.tiles_per_xcd) {
+  // (a division is done on the vector unit: back to scalars)
+  auto scalar = [](unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane(v); };
+  if (!BOXES && a.order.kind == XcdOrder::kRuns) {
     const unsigned n = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     const unsigned total = gridDim.x * gridDim.y * gridDim.z, xcd = n & 7, each = total >> 3, rest = total & 7;
     const unsigned id = xcd * each + (xcd < rest ? xcd : rest) + (n >> 3);
     const unsigned pair = id / gridDim.x;
-    // (a division is done on the vector unit: back to scalars)
-    tile_id = __builtin_amdgcn_readfirstlane(id - pair * gridDim.x);
-    group_id = __builtin_amdgcn_readfirstlane(pair % gridDim.y);
-    piece_id = __builtin_amdgcn_readfirstlane(pair / gridDim.y);
+    tile_id = scalar(id - pair * gridDim.x);
+    group_id = scalar(pair % gridDim.y);
+    piece_id = scalar(pair / gridDim.y);
+  } else if (BOXES && a.order.kind == XcdOrder::kBoxes) {
+    const unsigned n = blockIdx.x, xcd = n & 7, lt = a.order.log_t, lg = 3 - lt;
+    const unsigned ct = xcd & ((1u << lt) - 1), cg = xcd >> lt;
+    const unsigned t_lo = (ct * a.tiles) >> lt, t_n = (((ct + 1) * a.tiles) >> lt) - t_lo;
+    const unsigned g_lo = (cg * a.groups) >> lg, g_n = (((cg + 1) * a.groups) >> lg) - g_lo;
+    const unsigned i = n >> 3, row = scalar(i / t_n);
+    if (row >= g_n) return;                              // the whole workgroup: a box smaller than the largest
+    tile_id = t_lo + i - row * t_n;
+    group_id = g_lo + row;
+    piece_id = 0;
   }
   const int64_t r = (int64_t)group_id * WR + wr;
   const bool r_valid = r < a.R;
   const int64_t rr = r_valid ? r : a.R - 1;      // out-of-range waves compute a valid row block, store nothing
   const int64_t t0 = (int64_t)tile_id * kTokTile;
-  const int64_t s0 = (int64_t)piece_id * a.ks_steps;
-  const int64_t S = (a.S - s0) < a.ks_steps ? (a.S - s0) : a.ks_steps;   // steps of this workgroup
+  const int64_t p0 = (int64_t)piece_id * a.ks_steps;
+  const int64_t SP = (a.S - p0) < a.ks_steps ? (a.S - p0) : a.ks_steps;  // steps of this workgroup
+  const int64_t SG = (SP + KG - 1) / KG;                                 // steps of its first group
+  const int64_t s0 = p0 + kg * SG, S = KG == 1 || kg == 0 ? SG : SP - SG;
   const int64_t rs0 = rr * a.S + s0;                                      // its first (row block, step)
   const int img = a.image_bytes;
+  unsigned char* const ring = smem + (KG == 1 ? 0 : kg * NBUF * img);    // this group's ring of images
   const int n_ci = img / 1024;                   // wave-wide copies per image
   const int ncw = (n_ci + NW - 1) / NW;          // copies per wave and image
 
@@ -481,8 +500,8 @@ spmm_smfmac_kernel(const SpmmArgs a) {
 
   // B-operand lane roles
   const int hB = lane >> 5, tg = (lane >> 4) & 1, kq = (lane & 15) >> 2, q = lane & 3;
-  const unsigned lds0 = (unsigned)(size_t)(VNM_LDS(unsigned char))smem;
-  const unsigned tokoff = (unsigned)((wt * TW + tg * 16 + q * 4) * 2);
+  const unsigned lds0 = (unsigned)(size_t)(VNM_LDS(unsigned char))ring;
+  const unsigned tokoff = (unsigned)((tg * 16 + q * 4) * 2);
 
   const unsigned char* xs_tile = a.Xs + ((int64_t)tile_id * a.S + s0) * img;
   // copy this wave's share of image s into ring slot `slot`; chunks beyond the image are clamped to
@@ -493,7 +512,7 @@ spmm_smfmac_kernel(const SpmmArgs a) {
       int ci = wave + k * NW;
       ci = ci < n_ci ? ci : n_ci - 1;
       __builtin_amdgcn_global_load_lds((VNM_GLB(void))(src + ci * 1024),
-                                       (VNM_LDS(void))(smem + slot * img + ci * 1024), 16, 0, 0);
+                                       (VNM_LDS(void))(ring + slot * img + ci * 1024), 16, 0, 0);
     }
   };
 
@@ -552,6 +571,42 @@ spmm_smfmac_kernel(const SpmmArgs a) {
   // turned around in LDS (the ring is free after the last barrier): written as [token][V channels]
   // with a pitch of V*2+8 bytes (conflict-free 8-byte writes), read back 16 bytes per lane with
   // V/8 lanes per token, and stored as whole V*2-byte runs of each Y row.
+  constexpr int BE = BT / KG, TE = TW / KG;              // token tiles and tokens this wave has the results of
+  unsigned char* ep = smem + (size_t)wave_id * TE * (V * 2 + 8);       // its private region of LDS
+  const int64_t t_wave = t0 + kg * TE;
+  if constexpr (KG == 2) {
+    // A step has one barrier, so the group with a step less has one to add.  Each wave then hands the sums of the other
+    // group's half of the tokens over: 16 KiB per wave, [16-byte piece][lane].
+    if (S < SG) __builtin_amdgcn_s_barrier();
+    constexpr int XB = AT * BE * 16 * 64 * 4;
+    float* mine = (float*)(smem + (size_t)wave_id * XB);
+    const unsigned char* theirs = smem + (size_t)(wave_id ^ WR) * XB;
+#pragma unroll
+    for (int i = 0; i < AT; ++i)
+#pragma unroll
+      for (int j = 0; j < BE; ++j) {
+        const f16v send = kg ? acc[i][j] : acc[i][j + BE];
+        acc[i][j] = kg ? acc[i][j + BE] : acc[i][j];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const f4 v = {send[4 * k], send[4 * k + 1], send[4 * k + 2], send[4 * k + 3]};
+          *(f4*)(mine + (((i * BE + j) * 4 + k) * 64 + lane) * 4) = v;
+        }
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < AT; ++i)
+#pragma unroll
+      for (int j = 0; j < BE; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const f4 v = *(const f4*)(theirs + (((i * BE + j) * 4 + k) * 64 + lane) * 16);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[i][j][4 * k + e] += v[e];
+        }
+    ep = (unsigned char*)theirs;                         // nobody else reads it
+    static_assert(TE * (V * 2 + 8) <= XB, "the turned-around tile fits there");
+  }
   if (!r_valid) return;
   const int tokl = lane & 31;
   if constexpr (FUSED) {
@@ -572,14 +627,13 @@ spmm_smfmac_kernel(const SpmmArgs a) {
 #pragma unroll
         for (int k = 0; k < 16; ++k)
 #pragma unroll
-          for (int j = 0; j < BT; ++j) acc[i][j][k] += bv[i][k];
+          for (int j = 0; j < BE; ++j) acc[i][j][k] += bv[i][k];
     }
   }
   if (!a.y_fp32 && a.wide_store && (!FUSED || !a.perm_out)) {
     constexpr int EP = V * 2 + 8;                         // bytes per token row in LDS
-    unsigned char* ep = smem + (size_t)wave * TW * EP;    // this wave's private region
 #pragma unroll
-    for (int j = 0; j < BT; ++j)
+    for (int j = 0; j < BE; ++j)
 #pragma unroll
       for (int i = 0; i < AT; ++i)
 #pragma unroll
@@ -593,10 +647,10 @@ spmm_smfmac_kernel(const SpmmArgs a) {
     const int ch = lane % LPT, tl = lane / LPT;
     _Float16* Yh = (_Float16*)a.Y + (int64_t)piece_id * a.z_stride;
 #pragma unroll
-    for (int it = 0; it < TW / TPI; ++it) {
+    for (int it = 0; it < TE / TPI; ++it) {
       const int tk = it * TPI + tl;
       const uint4 v = *(const uint4*)(ep + (size_t)tk * EP + ch * 16);
-      const int64_t tok = t0 + wt * TW + tk;
+      const int64_t tok = t_wave + tk;
       const int64_t o = r * V + ch * 8;
       // Y is written once and not read again here: non-temporal stores keep it from displacing the
       // operands other workgroups still stream through L2 (measured 5-10 % of the kernel)
@@ -644,8 +698,8 @@ spmm_smfmac_kernel(const SpmmArgs a) {
           const int64_t dst = o < a.out ? (int64_t)a.perm_out[o] : -1;
           if (dst < 0 || dst >= a.out) continue;
 #pragma unroll
-          for (int j = 0; j < BT; ++j) {
-            const int64_t tok = t0 + wt * TW + j * 32 + tokl;
+          for (int j = 0; j < BE; ++j) {
+            const int64_t tok = t_wave + j * 32 + tokl;
             if (tok >= a.T) continue;
             const float v = acc[i][j][4 * jq + e];
             if (a.y_fp32) ((float*)a.Y)[tok * a.ldy + dst] = v;
@@ -655,8 +709,8 @@ spmm_smfmac_kernel(const SpmmArgs a) {
     return;
   }
 #pragma unroll
-  for (int j = 0; j < BT; ++j) {
-    const int64_t tok = t0 + wt * TW + j * 32 + tokl;
+  for (int j = 0; j < BE; ++j) {
+    const int64_t tok = t_wave + j * 32 + tokl;
     if (tok >= a.T) continue;
 #pragma unroll
     for (int i = 0; i < AT; ++i) {
@@ -676,25 +730,42 @@ bool spmm_smfmac_applicable(const void* X, int64_t ldx, const Dims& d) {
   return has_packed(d.V, d.M) && d.in % 8 == 0 && ldx % 8 == 0 && ((uintptr_t)X & 15) == 0;
 }
 
-template <int V, int TW, int WR, int WT, int NCW, int NBUF, bool DUAL, bool FUSED>
+template <int V, int TW, int WR, int KG, int NCW, int NBUF, bool DUAL, bool FUSED, bool BOXES>
 static int launch_cfg2(const SpmmArgs& a, hipStream_t st) {
-  size_t lds = (size_t)NBUF * a.image_bytes;
-  const size_t ep = (size_t)WR * WT * TW * (V * 2 + 8);     // epilogue transposition, per wave [TW][V] fp16
+  size_t lds = (size_t)KG * NBUF * a.image_bytes;
+  // epilogue: per wave [TW][V] fp16, or the exchange of half the accumulators between two groups
+  const size_t ep = KG == 1 ? (size_t)WR * TW * (V * 2 + 8) : (size_t)2 * WR * TW * V * 2;
   if (ep > lds) lds = ep;
-  auto kern = spmm_smfmac_kernel<V, TW, WR, WT, NCW, NBUF, DUAL, FUSED>;
+  auto kern = spmm_smfmac_kernel<V, TW, WR, KG, NCW, NBUF, DUAL, FUSED, BOXES>;
   if (int rc_lds = allow_big_lds((const void*)kern, "hipFuncSetAttribute(spmm_smfmac)")) return rc_lds;
-  dim3 grid((unsigned)((a.T + kTokTile - 1) / kTokTile), (unsigned)((a.R + WR - 1) / WR),
-            (unsigned)((a.S + a.ks_steps - 1) / a.ks_steps));
-  hipLaunchKernelGGL(kern, grid, dim3(64 * WR * WT), lds, st, a);
+  SpmmArgs b = a;
+  b.tiles = (unsigned)((a.T + kTokTile - 1) / kTokTile);
+  b.groups = (unsigned)((a.R + WR - 1) / WR);
+  dim3 grid(b.tiles, b.groups, (unsigned)((a.S + a.ks_steps - 1) / a.ks_steps));
+  if (a.order.kind == XcdOrder::kBoxes) {
+    if (b.tiles >= 1u << a.order.log_t && b.groups >= 8u >> a.order.log_t)
+      grid = dim3(8 * xcd_box_most(b.tiles, b.groups, a.order.log_t), 1, 1);
+    else b.order.kind = XcdOrder::kGrid;                   // (a box would be empty)
+  }
+  hipLaunchKernelGGL(kern, grid, dim3(64 * WR * KG), lds, st, b);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "spmm_smfmac_kernel"); return VNM_ERR_HIP; }
   return VNM_OK;
 }
 
-template <int V, int TW, int WR, int WT, int NCW, int NBUF, bool DUAL>
+template <int V, int TW, int WR, int KG, int NCW, int NBUF, bool DUAL, bool BOXES>
+static int launch_cfg3(const SpmmArgs& a, hipStream_t st) {
+  if (a.bias || a.perm_out) return launch_cfg2<V, TW, WR, KG, NCW, NBUF, DUAL, true, BOXES>(a, st);
+  return launch_cfg2<V, TW, WR, KG, NCW, NBUF, DUAL, false, BOXES>(a, st);
+}
+// (the numbering by boxes is an instantiation of its own: its code in front of the others cost them 1 %)
+template <int V, int TW, int WR, int KG, int NCW, int NBUF, bool DUAL>
 static int launch_cfg(const SpmmArgs& a, hipStream_t st) {
-  if (a.bias || a.perm_out) return launch_cfg2<V, TW, WR, WT, NCW, NBUF, DUAL, true>(a, st);
-  return launch_cfg2<V, TW, WR, WT, NCW, NBUF, DUAL, false>(a, st);
+  if constexpr (KG == 2) return launch_cfg3<V, TW, WR, KG, NCW, NBUF, DUAL, true>(a, st);
+  else if constexpr (WR == 8) {
+    if (a.order.kind == XcdOrder::kBoxes) return launch_cfg3<V, TW, WR, KG, NCW, NBUF, DUAL, true>(a, st);
+  }
+  return launch_cfg3<V, TW, WR, KG, NCW, NBUF, DUAL, false>(a, st);
 }
 
 // V = 64: pick the assembly loop by workgroup size (4 or 8 row blocks), by copies per wave
@@ -717,10 +788,24 @@ static int launch_v64_w4(const SpmmArgs& a, hipStream_t st) {
 // the deep loop (ring of 6; bias and permutation are the reduction's)
 static int launch_deep(const SpmmArgs& a, hipStream_t st) {
   switch ((a.image_bytes / 1024 + 3) / 4) {
-    case 3: return launch_cfg2<64, 128, 4, 1, 3, 6, false, false>(a, st);
-    case 4: return launch_cfg2<64, 128, 4, 1, 4, 6, false, false>(a, st);
-    case 5: return launch_cfg2<64, 128, 4, 1, 5, 6, false, false>(a, st);
-    case 6: return launch_cfg2<64, 128, 4, 1, 6, 6, false, false>(a, st);
+    case 3: return launch_cfg2<64, 128, 4, 1, 3, 6, false, false, false>(a, st);
+    case 4: return launch_cfg2<64, 128, 4, 1, 4, 6, false, false, false>(a, st);
+    case 5: return launch_cfg2<64, 128, 4, 1, 5, 6, false, false, false>(a, st);
+    case 6: return launch_cfg2<64, 128, 4, 1, 6, 6, false, false, false>(a, st);
+  }
+  return VNM_ERR_UNSUPPORTED;
+}
+// two groups of 4 waves on halves of K, the longest rings of which LDS holds two
+template <bool DUAL>
+static int launch_v64_kg(const SpmmArgs& a, hipStream_t st) {
+  switch (a.M) {
+    case 4: return launch_cfg<64, 128, 4, 2, 3, 4, DUAL>(a, st);
+    case 5:
+    case 6: return launch_cfg<64, 128, 4, 2, 4, 4, DUAL>(a, st);
+    case 7:
+    case 8: return launch_cfg<64, 128, 4, 2, 5, 4, DUAL>(a, st);
+    case 9: return launch_cfg<64, 128, 4, 2, 6, 3, DUAL>(a, st);
+    case 10: return launch_cfg<64, 128, 4, 2, 7, 3, DUAL>(a, st);
   }
   return VNM_ERR_UNSUPPORTED;
 }
@@ -881,14 +966,16 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
   const int y_elem = y_dtype == 0 ? 2 : 4;
   const bool post_permute = KS == 1 && f.perm_out && d.out * y_elem <= permute_rows_max_bytes();
   if (post_permute) a.perm_out = nullptr;
-  a.tiles_per_xcd = tiles_by_xcd(tiles, (a.R + 3) / 4, d.S, KS, weight_bytes, tiles * d.S * a.image_bytes, in_l2) &&
-                    tiles * a.R * d.S < (1ll << 31);
+  const int64_t last_piece = d.S - (int64_t)(KS - 1) * a.ks_steps;
+  const bool kg = kgroups(KS, base, d.S, d.M);
+  a.order = xcd_order(tiles, wide && !kg ? (a.R + 7) / 8 : (a.R + 3) / 4, d.S, KS, weight_bytes, tiles * d.S * a.image_bytes, kg, wide, in_l2);
+  if (tiles * a.R * d.S >= (1ll << 31)) a.order.kind = XcdOrder::kGrid;
   a.wide_store = (a.y_fp32 == 0) && (a.ldy % 8 == 0) && (((uintptr_t)a.Y & 15) == 0);
   a.vec_store = (a.ldy % 4 == 0) && (((uintptr_t)a.Y & (a.y_fp32 == 0 ? 7 : 15)) == 0);
   int rc = VNM_ERR_UNSUPPORTED;
   const bool ring4 = 4 * (size_t)a.image_bytes <= 150 * 1024;
-  const int64_t last_piece = d.S - (int64_t)(KS - 1) * a.ks_steps;
-  if (deep_loop(KS, base * KS, last_piece, a.R, d.S, d.M, packed_tables(d.V))) rc = launch_deep(a, st);
+  if (kg) rc = dual ? launch_v64_kg<true>(a, st) : launch_v64_kg<false>(a, st);
+  else if (deep_loop(KS, base * KS, last_piece, a.R, d.S, d.M, packed_tables(d.V))) rc = launch_deep(a, st);
   else if (!dual) {
     if (wide) rc = ring4 ? launch_v64_w8<4, false>(a, st) : launch_v64_w8<3, false>(a, st);
     else rc = deep ? launch_v64_w4<4, false>(a, st) : launch_v64_w4<3, false>(a, st);

@@ -135,3 +135,38 @@ def test_split_pieces(rule, T, pairs, steps, pieces):
 def test_refresh_pruning_steps(rule, V, M, R, S, k):
     assert rule("prune_ria_steps(%d, %d, %d, %d)" % (V, M, R, S)) == k
     assert rule("prune_ria_lds(%d, %d, %d)" % (V, M, k)) <= 64 * 1024
+
+
+@pytest.mark.parametrize("pieces,workgroups,steps,M,groups", [(1, 256, 103, 5, 1), (1, 257, 103, 5, 0), (2, 192, 103, 5, 0), (1, 144, 8, 5, 1),
+                                                              (1, 144, 7, 5, 0), (1, 192, 64, 10, 1), (1, 192, 64, 11, 0)])
+def test_two_wave_groups(rule, pieces, workgroups, steps, M, groups):
+    assert rule("kgroups(%d, %d, %d, %d)" % (pieces, workgroups, steps, M)) == groups
+
+
+# (tiles, groups, steps, pieces, MiB of weight and staged X, one generation, 8 row blocks per workgroup, parts in L2) -> kind
+# (0 grid order, 1 runs, 2 boxes) and parts of the token tiles
+@pytest.mark.parametrize("args,kind,log_t", [
+    ((16, 16, 103, 1, 17.6, 21.4, 1, 0, 0), 2, 2), ((3, 43, 103, 1, 47.0, 4.0, 1, 0, 0), 2, 0), ((1, 6, 103, 1, 6.0, 1.3, 1, 0, 0), 0, 0),
+    ((99, 6, 12, 1, 2.7, 23.0, 0, 1, 0), 2, 3), ((99, 6, 12, 1, 2.7, 23.0, 0, 0, 0), 0, 0), ((32, 8, 103, 1, 17.6, 43.0, 0, 1, 0), 0, 0),
+    ((9, 11, 276, 1, 47.0, 32.0, 0, 1, 0), 1, 0), ((6, 16, 103, 2, 17.6, 8.0, 0, 0, 0), 1, 0), ((1, 16, 103, 8, 17.6, 1.3, 0, 0, 1), 0, 0)])
+def test_xcd_order(rule, args, kind, log_t):
+    tiles, groups, steps, pieces, weight, staged, one, wide, in_l2 = args
+    call = "xcd_order(%d, %d, %d, %d, %d, %d, %d, %d, %d)" % (tiles, groups, steps, pieces, int(weight * MB), int(staged * MB), one, wide, in_l2)
+    assert rule(call + ".kind") == kind
+    if kind == 2:
+        assert rule(call + ".log_t") == log_t
+
+
+# the boxes cover every (token tile, group) once, and no XCD's box is larger than the launch provides for
+@pytest.mark.parametrize("tiles,groups,log_t", [(9, 16, 0), (9, 16, 1), (12, 13, 2), (17, 1, 3), (99, 6, 3), (8, 8, 3), (5, 4, 1)])
+def test_boxes_cover_the_launch(rule, tiles, groups, log_t):
+    most, seen = rule("xcd_box_most(%d, %d, %d)" % (tiles, groups, log_t)), []
+    for n in range(8 * most):
+        xcd, lg = n & 7, 3 - log_t
+        ct, cg = xcd & ((1 << log_t) - 1), xcd >> log_t
+        t_lo, g_lo = (ct * tiles) >> log_t, (cg * groups) >> lg
+        t_n, g_n = (((ct + 1) * tiles) >> log_t) - t_lo, (((cg + 1) * groups) >> lg) - g_lo
+        row = (n >> 3) // t_n
+        if row < g_n:
+            seen.append((t_lo + (n >> 3) - row * t_n, g_lo + row))
+    assert sorted(seen) == [(t, g) for t in range(tiles) for g in range(groups)]

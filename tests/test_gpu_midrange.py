@@ -62,3 +62,25 @@ def test_staged_product_epilogue(out, inn, T, V, M, ydt, which):
     if ydt == torch.float16:
         bound = bound + 2.0 ** -11 * want.abs() + 2.0 ** -24
     assert bool(((Y.double() - want).abs() <= bound).all())
+
+
+# two wave groups on halves of K, unsplit launches of up to 256 workgroups: 8 steps (4 each), 9 and other odd numbers (one
+# group waits a step for the other), every ring (M = 4 to 10), one and two column tables, ragged last row block and token
+# tile, 255 and 256 workgroups, boxes of unequal size; 270 workgroups and M = 11 (one group); and eight parts of the token
+# tiles (17, 47 and 23 of them, 8 row blocks per workgroup)
+KG = [(4096, 320, 1025, 64, 5), (4090, 360, 1100, 64, 5), (2056, 1632, 1500, 64, 4), (1100, 3000, 3000, 128, 7), (2050, 2040, 1300, 64, 6),
+      (4096, 1024, 2048, 32, 8), (4104, 1600, 1920, 32, 10), (5504, 680, 1000, 64, 9), (1000, 3080, 2600, 64, 8), (4360, 600, 1920, 64, 5),
+      (4096, 1408, 1500, 64, 11), (3080, 768, 2100, 64, 4), (2304, 1536, 6000, 64, 8), (5120, 1200, 2900, 32, 5)]
+
+
+@pytest.mark.parametrize("out,inn,T,V,M", KG)
+@pytest.mark.parametrize("ydt", [torch.float16, torch.float32])
+def test_two_wave_groups(out, inn, T, V, M, ydt):
+    test_staged_product(out, inn, T, V, M, ydt)
+
+
+@pytest.mark.parametrize("out,inn,T,V,M", [(2050, 2040, 1300, 64, 5), (4096, 2048, 2048, 32, 8), (2100, 1500 // 8 * 8, 2900, 64, 8)])
+@pytest.mark.parametrize("ydt", [torch.float16, torch.float32])
+@pytest.mark.parametrize("which", [("bias",), ("perm_out",), ("bias", "perm_out")])
+def test_two_wave_groups_epilogue(out, inn, T, V, M, ydt, which):
+    test_staged_product_epilogue(out, inn, T, V, M, ydt, which)
