@@ -52,10 +52,13 @@ __device__ __forceinline__ int64_t plain_src(const PlainArgs& a, int64_t c) {
 // along the columns, fall into different banks), so a wave reads the column a weight selects with one
 // conflict-free 4-byte read per lane.  Weights are decoded one block per lane (coalesced loads) and
 // handed to the whole wave with v_readlane: per (row, block) 8 vector instructions serve 128 tokens.
-// Bound by that instruction stream, half of it next to the multiply-adds.  1000 x 1030 at V = 16, M = 7,
-// 333 tokens, fp32 result: 25 us per call (spmm_generic_kernel: 219 us).  Sums run over the blocks in
+// Bound by that instruction stream: 10 vector and LDS instructions per (row, block), 4 of them multiply-adds, are half of
+// the time, the rest is moving X.  X reaches LDS two tokens at a time (4-byte stores; 2-byte ones, and offsets scaled by
+// the scalar unit per block, 25.4 -> 23.5 us on 1000 x 1030 at V = 16, M = 7, 333 tokens, fp32 result, where
+// spmm_generic_kernel takes 219; 4096 x 4096, M = 5, 200 tokens 217 -> 202).  Sums run over the blocks in
 // ascending order like that kernel's: the results are the same bits.
 constexpr int kPlainPitch = kPlainTok * 2 + 4;
+static_assert((kPlainCols + 255) * (kPlainPitch / 4) < 65536, "two offsets in a dword");
 
 // A chunk is at most kPlainCols columns: its 128 tokens then fit 16 (PAIR) or 32 registers per lane, which are
 // filled for the next chunk while the present one is multiplied.  PAIR: X moves two columns at a time.
@@ -81,7 +84,7 @@ spmm_plain_tokens_kernel(const PlainArgs a, int NB) {
   int64_t row_off[TU];                                // byte offsets of the wave's token rows, uniform
 #pragma unroll
   for (int u = 0; u < TU; ++u) {
-    const int64_t t = t0 + wave + 16 * u;
+    const int64_t t = t0 + 2 * (wave + 16 * (u >> 1)) + (u & 1);     // pairs of adjacent tokens
     row_off[u] = (t < a.T ? t : a.T - 1) * a.ldx * 2;
   }
   // chunk b0: this wave's weights, one block per lane, and 8 token rows of X, lanes along the columns
@@ -124,7 +127,7 @@ spmm_plain_tokens_kernel(const PlainArgs a, int NB) {
       const unsigned nib = odd ? byte[q] >> 4 : byte[q] & 15u;
       const unsigned c0 = base + ((k4 >> (8 * (nib & 3))) & 0xFFu), c1 = base + ((k4 >> (8 * (nib >> 2))) & 0xFFu);
       val[q] = pair[q];
-      offs[q] = c0 | (c1 << 16);
+      offs[q] = (c0 | (c1 << 16)) * (kPlainPitch / 4);      // in dwords: below 2^16 each
     }
     __syncthreads();                                  // the previous chunk has been read
 #pragma unroll
@@ -132,11 +135,12 @@ spmm_plain_tokens_kernel(const PlainArgs a, int NB) {
       const int c = (lane + 64 * k) * CW;
       if (c < ncol) {
 #pragma unroll
-        for (int u = 0; u < TU; ++u) {
-          unsigned char* d = smem + c * kPlainPitch + (wave + 16 * u) * 2;
-          const unsigned x = live[k] ? xr[k][u] : 0u;
-          *(unsigned short*)d = (unsigned short)x;
-          if constexpr (PAIR) *(unsigned short*)(d + kPlainPitch) = (unsigned short)(x >> 16);
+        for (int u = 0; u < TU; u += 2) {
+          // two tokens of a column per store
+          unsigned char* d = smem + c * kPlainPitch + (wave + 8 * u) * 4;
+          const unsigned x0 = live[k] ? xr[k][u] : 0u, x1 = live[k] ? xr[k][u + 1] : 0u;
+          *(unsigned*)d = __builtin_amdgcn_perm(x1, x0, 0x05040100u);
+          if constexpr (PAIR) *(unsigned*)(d + kPlainPitch) = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
         }
       }
     }
@@ -154,8 +158,8 @@ spmm_plain_tokens_kernel(const PlainArgs a, int NB) {
           for (int q = 0; q < RW; ++q) {
             const unsigned o = __builtin_amdgcn_readlane(offs[q], b + n);
             w[q][n] = __builtin_amdgcn_readlane(val[q], b + n);
-            x0[q][n] = *(const unsigned*)(xl + (o & 0xFFFFu) * kPlainPitch);
-            x1[q][n] = *(const unsigned*)(xl + (o >> 16) * kPlainPitch);
+            x0[q][n] = *(const unsigned*)(xl + (o & 0xFFFFu) * 4);
+            x1[q][n] = *(const unsigned*)(xl + (o >> 16) * 4);
           }
 #pragma unroll
         for (int n = 0; n < N; ++n)
