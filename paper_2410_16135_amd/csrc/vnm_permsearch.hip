@@ -189,9 +189,24 @@ out_precompute_kernel(const unsigned* __restrict__ rowM, PsDims d, const int* __
   Lrem[k * d.in + i] = s;
 }
 
+// The same after another slot: between two slots the sums change by the row that came into the block at the last slot and
+// the one at the present slot, which is lifted out.  Two rows read instead of V: 21 -> 3 us at V = 64 on 2048 columns.
+__global__ void __launch_bounds__(256)
+out_update_kernel(const unsigned* __restrict__ rowM, PsDims d, const int* __restrict__ member, int slot,
+                  int64_t* __restrict__ Lrem) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, k = blockIdx.y;
+  if (i >= d.in) return;
+  const int64_t in = rowM[(int64_t)member[k * d.V + slot - 1] * d.in + i], out = rowM[(int64_t)member[k * d.V + slot] * d.in + i];
+  Lrem[k * d.in + i] += in - out;
+}
+
 // gain[r][k] += over a chunk of NB column blocks: workgroup (k, chunk); the remainder rows of block
 // k over the chunk's columns sit in LDS; items (r, block of the chunk) are spread over the threads.
-__global__ void __launch_bounds__(256)
+// Bound by the gather from LDS, four words and a dozen instructions per (item, row): 512 threads, an item each on a 2048 x
+// 2048 matrix at V = 64, keep twice as many of them in flight as 256 with two: 53 -> 29 us per slot, with the columns' sums requested four at a
+// time and one instruction less in each comparison of four.
+constexpr int kGainThreads = 512;
+__global__ void __launch_bounds__(kGainThreads)
 out_gain_kernel(const unsigned* __restrict__ rowM, const int64_t* __restrict__ Lrem, PsDims d,
                 const int* __restrict__ member, int slot, int NB, int64_t* __restrict__ gain) {
   extern __shared__ unsigned lds_u[];
@@ -201,91 +216,141 @@ out_gain_kernel(const unsigned* __restrict__ rowM, const int64_t* __restrict__ L
   const int tid = threadIdx.x;
   const int64_t k = blockIdx.x;
   const int64_t col0 = (int64_t)blockIdx.y * W;
-  for (int e = tid; e < (V - 1) * W; e += 256) {
+  for (int e = tid; e < (V - 1) * W; e += kGainThreads) {
     const int pr = e / W, cc = e - pr * W;
     const int p = pr < slot ? pr : pr + 1;                 // remainder row pr is position p of the block
     const int64_t i = col0 + cc;
     rem[pr * P + cc] = i < d.in ? rowM[(int64_t)member[k * V + p] * d.in + i] : 0u;
   }
-  for (int64_t r = tid; r < d.Rf; r += 256) acc[r] = 0ull;
+  for (int64_t r = tid; r < d.Rf; r += kGainThreads) acc[r] = 0ull;
   __syncthreads();
-  const int64_t nblk = (d.B - (int64_t)blockIdx.y * NB) < NB ? (d.B - (int64_t)blockIdx.y * NB) : NB;
-  for (int64_t item = tid; item < d.Rf * nblk; item += 256) {
-    const int64_t r = item / nblk;
-    const int bl = (int)(item - r * nblk);
-    const int64_t crow = (int64_t)member[r * V + slot] * d.in;          // the lifted row of block r
+  const int nblk = (int)((d.B - (int64_t)blockIdx.y * NB) < NB ? (d.B - (int64_t)blockIdx.y * NB) : NB);
+  const int items = (int)d.Rf * nblk;                      // (Rf <= 8192, NB <= 16)
+  for (int item = tid; item < items; item += kGainThreads) {
+    const int r = item / nblk;
+    const int bl = item - r * nblk;
+    const unsigned* crow = rowM + (int64_t)member[(int64_t)r * V + slot] * d.in;   // the lifted row of block r
+    const int64_t* Lk = Lrem + k * d.in;
     // the four best columns of the block by (column sum descending, index ascending)
     int bc[4] = {0, 0, 0, 0};
     int64_t bL[4] = {-1, -1, -1, -1};
     unsigned cv[4] = {0, 0, 0, 0};
-    for (int c = 0; c < M; ++c) {
-      const int64_t i = col0 + bl * M + c;
-      const unsigned x = i < d.in ? rowM[crow + i] : 0u;
-      const int64_t L = (i < d.in ? Lrem[k * d.in + i] : 0) + x;
-      int at = 4;
-      while (at > 0 && L > bL[at - 1]) --at;
-      if (at < 4) {
-        for (int q = 3; q > at; --q) { bc[q] = bc[q - 1]; bL[q] = bL[q - 1]; cv[q] = cv[q - 1]; }
-        bc[at] = bl * M + c; bL[at] = L; cv[at] = x;
+    for (int c0 = 0; c0 < M; c0 += 4) {                    // four columns requested at a time
+      unsigned xs[4];
+      int64_t Ls[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int64_t i = col0 + bl * M + c0 + u;
+        const bool ok = c0 + u < M && i < d.in;
+        xs[u] = crow[ok ? i : 0];
+        Ls[u] = Lk[ok ? i : 0];
+        xs[u] = ok ? xs[u] : 0u;
+        Ls[u] = ok ? Ls[u] + xs[u] : (c0 + u < M ? 0 : -1);   // a column beyond the last scores 0, one that does not exist never enters
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int c = bl * M + c0 + u;
+        const int64_t L = Ls[u];
+        // inserted in front of the first that it beats
+        const bool g0 = L > bL[0], g1 = L > bL[1], g2 = L > bL[2], g3 = L > bL[3];
+        if (g3) {
+          bc[3] = g2 ? bc[2] : c; bL[3] = g2 ? bL[2] : L; cv[3] = g2 ? cv[2] : xs[u];
+          if (g2) { bc[2] = g1 ? bc[1] : c; bL[2] = g1 ? bL[1] : L; cv[2] = g1 ? cv[1] : xs[u]; }
+          if (g1) { bc[1] = g0 ? bc[0] : c; bL[1] = g0 ? bL[0] : L; cv[1] = g0 ? cv[0] : xs[u]; }
+          if (g0) { bc[0] = c; bL[0] = L; cv[0] = xs[u]; }
+        }
       }
     }
+    // the two largest of four: the second is the larger of the smaller winner and the losers
     auto top2 = [](unsigned x0, unsigned x1, unsigned x2, unsigned x3) -> unsigned long long {
-      const unsigned h01 = x0 > x1 ? x0 : x1, l01 = x0 > x1 ? x1 : x0;
-      const unsigned h23 = x2 > x3 ? x2 : x3, l23 = x2 > x3 ? x3 : x2;
-      const unsigned m1 = h01 > h23 ? h01 : h23;
-      const unsigned m2 = h01 > h23 ? (l01 > h23 ? l01 : h23) : (l23 > h01 ? l23 : h01);
+      const unsigned h01 = max(x0, x1), l01 = min(x0, x1), h23 = max(x2, x3), l23 = min(x2, x3);
+      const unsigned m1 = max(h01, h23), m2 = max(min(h01, h23), max(l01, l23));
       return (unsigned long long)m1 + m2;
     };
     unsigned long long s = top2(cv[0], cv[1], cv[2], cv[3]);
-    for (int pr = 0; pr < V - 1; ++pr) {
-      const unsigned* row = rem + pr * P;
-      s += top2(row[bc[0]], row[bc[1]], row[bc[2]], row[bc[3]]);
+    const unsigned *p0 = rem + bc[0], *p1 = rem + bc[1], *p2 = rem + bc[2], *p3 = rem + bc[3];
+    int pr = 0;
+    for (; pr + 4 <= V - 1; pr += 4) {
+      unsigned x[4][4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int o = (pr + u) * P;
+        x[u][0] = p0[o]; x[u][1] = p1[o]; x[u][2] = p2[o]; x[u][3] = p3[o];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s += top2(x[u][0], x[u][1], x[u][2], x[u][3]);
     }
+    for (; pr < V - 1; ++pr) s += top2(p0[pr * P], p1[pr * P], p2[pr * P], p3[pr * P]);
     atomicAdd(&acc[r], s);
   }
   __syncthreads();
-  for (int64_t r = tid; r < d.Rf; r += 256)
+  for (int64_t r = tid; r < d.Rf; r += kGainThreads)
     if (acc[r]) atomicAdd((unsigned long long*)&gain[r * d.Rf + k], acc[r]);
 }
 
-// Objective: one thread per (row block, column block) of the permuted matrix, ragged ones included.
-__global__ void __launch_bounds__(128)
+// Objective: a wave per (row block, column block) of the permuted matrix, ragged ones included; lane v takes the rows v,
+// v + 64 of the block.  A thread adds up its rows' scores per column, the wave their sums; every lane then knows the four
+// best columns.  Bound by the gather of single scores (a permutation of the columns leaves nothing contiguous): 2048 x 2048 at V = 64,
+// M = 5 294 us with a thread per (row block, column block), 61 now.
+__global__ void __launch_bounds__(256)
 retained_kernel(const float* __restrict__ S, PsDims d, const int* __restrict__ po, const int* __restrict__ pi,
                 unsigned long long* __restrict__ total) {
-  const int64_t id = (int64_t)blockIdx.x * 128 + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int64_t id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   unsigned long long mine = 0;
-  if (id < d.R * d.B) {
+  if (id < d.R * d.B) {                                     // uniform over the wave
     const int64_t r = id / d.B, b = id - r * d.B;
-    const int64_t o0 = r * d.V, o1 = o0 + d.V < d.out ? o0 + d.V : d.out;
-    int bc[4] = {0, 0, 0, 0};
+    const int64_t o0 = r * d.V;
+    const int rows = (int)(o0 + d.V < d.out ? d.V : d.out - o0);
+    const float* row[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) row[h] = S + (int64_t)po[o0 + (lane + 64 * h < rows ? lane + 64 * h : 0)] * d.lds;
     int64_t bL[4] = {-1, -1, -1, -1};
+    unsigned bx[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};       // this lane's scores in the best columns
     for (int c = 0; c < d.M; ++c) {
       const int64_t i = b * d.M + c;
-      int64_t L = 0;
+      unsigned x[2] = {0, 0};
       if (i < d.in) {
         const int64_t src = pi[i];
-        for (int64_t o = o0; o < o1; ++o) L += quantise(S[(int64_t)po[o] * d.lds + src], d.scale);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const unsigned q = quantise(row[h][src], d.scale);
+          x[h] = lane + 64 * h < rows ? q : 0u;
+        }
       }
-      int at = 4;
-      while (at > 0 && L > bL[at - 1]) --at;
-      if (at < 4) {
-        for (int q = 3; q > at; --q) { bc[q] = bc[q - 1]; bL[q] = bL[q - 1]; }
-        bc[at] = c; bL[at] = L;
+      int64_t L = (int64_t)x[0] + x[1];
+      for (int off = 32; off > 0; off >>= 1) L += __shfl_xor(L, off, 64);
+      // inserted in front of the first that it beats (sum descending, index ascending); moves down from the last place up
+      const bool g[4] = {L > bL[0], L > bL[1], L > bL[2], L > bL[3]};
+#pragma unroll
+      for (int k = 3; k >= 0; --k) {
+        const bool from_above = k > 0 && g[k > 0 ? k - 1 : 0];
+        const int64_t l = from_above ? bL[k > 0 ? k - 1 : 0] : L;
+        const unsigned y0 = from_above ? bx[0][k > 0 ? k - 1 : 0] : x[0], y1 = from_above ? bx[1][k > 0 ? k - 1 : 0] : x[1];
+        bL[k] = g[k] ? l : bL[k];
+        bx[0][k] = g[k] ? y0 : bx[0][k];
+        bx[1][k] = g[k] ? y1 : bx[1][k];
       }
     }
-    for (int64_t o = o0; o < o1; ++o) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
       unsigned m1 = 0, m2 = 0;
+#pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int64_t i = b * d.M + bc[q];
-        const unsigned x = i < d.in ? quantise(S[(int64_t)po[o] * d.lds + pi[i]], d.scale) : 0u;
+        const unsigned x = bx[h][q];
         if (x > m1) { m2 = m1; m1 = x; } else if (x > m2) m2 = x;
       }
       mine += (unsigned long long)m1 + m2;
     }
+    for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
   }
-  // wave reduction, then one atomic per wave
-  for (int off = 32; off > 0; off >>= 1) mine += __shfl_down(mine, off, 64);
-  if ((threadIdx.x & 63) == 0 && mine) atomicAdd(total, mine);
+  __shared__ unsigned long long part[4];
+  if (lane == 0) part[threadIdx.x >> 6] = mine;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned long long t = part[0] + part[1] + part[2] + part[3];
+    if (t) atomicAdd(total, t);
+  }
 }
 
 __global__ void fill_i64_kernel(int64_t* p, int64_t n, int64_t v) {
@@ -336,15 +401,17 @@ struct Ctx {
   template <typename T> T* at(int64_t off) const { return (T*)(ws + off); }
 };
 
-int upload(const Ctx& c, int64_t off, const int* host, int64_t n) {
+// wait = false: the caller does not change the host array before the stream has been waited for once more
+int upload(const Ctx& c, int64_t off, const int* host, int64_t n, bool wait = true) {
   if (int rc = check_hip(hipMemcpyAsync(c.ws + off, host, (size_t)n * 4, hipMemcpyHostToDevice, c.st), "hipMemcpyAsync")) return rc;
+  if (!wait) return VNM_OK;
   return check_hip(hipStreamSynchronize(c.st), "hipStreamSynchronize");   // the host vector may change next
 }
 
 int objective(const Ctx& c, int64_t* value) {
   const PsDims& d = c.d;
   hipLaunchKernelGGL(fill_i64_kernel, dim3(1), dim3(256), 0, c.st, c.at<int64_t>(c.l.total), (int64_t)1, (int64_t)0);
-  hipLaunchKernelGGL(retained_kernel, dim3((unsigned)((d.R * d.B + 127) / 128)), dim3(128), 0, c.st, c.S, d,
+  hipLaunchKernelGGL(retained_kernel, dim3((unsigned)((d.R * d.B + 3) / 4)), dim3(256), 0, c.st, c.S, d,
                      c.at<int>(c.l.po), c.at<int>(c.l.pi), c.at<unsigned long long>(c.l.total));
   if (int rc = check_hip(hipGetLastError(), "retained_kernel")) return rc;
   if (int rc = check_hip(hipMemcpyAsync(value, c.ws + c.l.total, 8, hipMemcpyDeviceToHost, c.st), "hipMemcpyAsync")) return rc;
@@ -382,9 +449,11 @@ int begin_output_step(const Ctx& c) {
   return check_hip(hipGetLastError(), "build_rowM_kernel");
 }
 
-int gain_output(const Ctx& c, int slot) {
+// follows: Lrem holds the sums of the slot before this one, whose assignment is in `member`
+int gain_output(const Ctx& c, int slot, bool follows) {
   const PsDims& d = c.d;
-  hipLaunchKernelGGL(out_precompute_kernel, dim3((unsigned)((d.in + 255) / 256), (unsigned)d.Rf), dim3(256), 0, c.st,
+  auto sums = follows ? out_update_kernel : out_precompute_kernel;
+  hipLaunchKernelGGL(sums, dim3((unsigned)((d.in + 255) / 256), (unsigned)d.Rf), dim3(256), 0, c.st,
                      c.at<unsigned>(c.l.mat), d, c.at<int>(c.l.member), slot, c.at<int64_t>(c.l.Lrem));
   const int64_t n2 = d.Rf * d.Rf;
   hipLaunchKernelGGL(fill_i64_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, c.st, c.at<int64_t>(c.l.gain), n2,
@@ -395,7 +464,7 @@ int gain_output(const Ctx& c, int slot) {
   const size_t rem_words = (((size_t)(d.V - 1) * ((size_t)(NB * d.M) | 1)) + 1) & ~(size_t)1;
   const size_t lds = rem_words * 4 + (size_t)d.Rf * 8;
   if (int rc = allow_big_lds((const void*)out_gain_kernel, "hipFuncSetAttribute(out_gain)")) return rc;
-  hipLaunchKernelGGL(out_gain_kernel, dim3((unsigned)d.Rf, (unsigned)((d.B + NB - 1) / NB)), dim3(256), lds, c.st,
+  hipLaunchKernelGGL(out_gain_kernel, dim3((unsigned)d.Rf, (unsigned)((d.B + NB - 1) / NB)), dim3(kGainThreads), lds, c.st,
                      c.at<unsigned>(c.l.mat), c.at<int64_t>(c.l.Lrem), d, c.at<int>(c.l.member), slot, NB,
                      c.at<int64_t>(c.l.gain));
   return check_hip(hipGetLastError(), "out_gain_kernel");
@@ -490,7 +559,7 @@ extern "C" int vnm_permutation_gain(const void* S, int64_t out, int64_t in, int6
     }
     if (int rc = upload(c, c.l.member, po.data(), d.Rf * d.V)) return rc;
     if (int rc = begin_output_step(c)) return rc;
-    if (int rc = gain_output(c, slot)) return rc;
+    if (int rc = gain_output(c, slot, false)) return rc;
     return fetch_gain(c, d.Rf, (int64_t*)gain);
   } catch (...) { return VNM_ERR_WORKSPACE; }
 }
@@ -528,7 +597,8 @@ extern "C" int vnm_permutation_search(const void* S, int64_t out, int64_t in, in
           if (int rc = vnm_lsa_max(gain.data(), (int)d.Bf, assign.data(), &tot)) return rc;
           for (int64_t b = 0; b < d.Bf; ++b) lifted[(size_t)b] = pi[b * M + slot];
           for (int64_t b = 0; b < d.Bf; ++b) pi[(int64_t)assign[(size_t)b] * M + slot] = lifted[(size_t)b];
-          if (int rc = upload(c, c.l.member, pi, d.Bf * d.M)) return rc;
+          if (slot + 1 < M)          // (the next slot's gains are waited for before pi changes again)
+            if (int rc = upload(c, c.l.member, pi, d.Bf * d.M, false)) return rc;
         }
         if (int rc = upload(c, c.l.pi, pi, in)) return rc;
       }
@@ -538,13 +608,14 @@ extern "C" int vnm_permutation_search(const void* S, int64_t out, int64_t in, in
         if (int rc = upload(c, c.l.member, po, d.Rf * d.V)) return rc;
         if (int rc = begin_output_step(c)) return rc;
         for (int slot = 0; slot < V; ++slot) {
-          if (int rc = gain_output(c, slot)) return rc;
+          if (int rc = gain_output(c, slot, slot > 0)) return rc;
           if (int rc = fetch_gain(c, d.Rf, gain.data())) return rc;
           int64_t tot = 0;
           if (int rc = vnm_lsa_max(gain.data(), (int)d.Rf, assign.data(), &tot)) return rc;
           for (int64_t r = 0; r < d.Rf; ++r) lifted[(size_t)r] = po[r * V + slot];
           for (int64_t r = 0; r < d.Rf; ++r) po[(int64_t)assign[(size_t)r] * V + slot] = lifted[(size_t)r];
-          if (int rc = upload(c, c.l.member, po, d.Rf * d.V)) return rc;
+          if (slot + 1 < V)
+            if (int rc = upload(c, c.l.member, po, d.Rf * d.V, false)) return rc;
         }
         if (int rc = upload(c, c.l.po, po, out)) return rc;
       }

@@ -225,3 +225,26 @@ def test_argument_errors():
     assert lib.vnm_retained_score(S.data_ptr(), 32, 40, 40, 16, 2, 5, 1.0, bad.ctypes.data, None,
                                   tot.ctypes.data_as(ctypes.POINTER(ctypes.c_int64)), ws.data_ptr(), ws.numel(),
                                   None) == 2
+
+
+# The search against its own definition, slot by slot: every gain matrix computed from scratch (vnm_permutation_gain), solved
+# by the same solver.  The search itself carries the column sums from one output slot to the next; V from the smallest to
+# the largest, more and fewer column blocks than a workgroup takes, ragged last blocks, M no multiple of four.
+@pytest.mark.parametrize("out,inn,V,M", [(64, 9, 16, 5), (130, 43, 16, 7), (300, 100, 64, 5), (256, 330, 128, 8), (70, 400, 32, 4)])
+def test_search_is_its_single_steps(out, inn, V, M):
+    import ctypes
+    rng = np.random.default_rng(out + inn)
+    S = _dev(_scores(rng, out, inn, "outliers"))
+    lib = vnm.load_library()
+    po, pi = np.arange(out, dtype=np.int32), np.arange(inn, dtype=np.int32)
+    for which, n, per, perm in ((0, inn // M, M, pi), (1, out // V, V, po)):
+        for slot in range(per if n >= 2 else 0):
+            gain = np.ascontiguousarray(vnm.vnm_permutation_gain(S, V, M, SCALE, which, slot, po, pi))
+            assign, tot = np.empty(n, dtype=np.int32), ctypes.c_int64(0)
+            assert lib.vnm_lsa_max(gain.ctypes.data, n, assign.ctypes.data, ctypes.byref(tot)) == 0
+            lifted = perm[slot:n * per:per].copy()
+            for b in range(n):
+                perm[assign[b] * per + slot] = lifted[b]
+    got_out, got_in, history = vnm.vnm_permutation_search(S, V, M, SCALE, iterations=1)
+    assert np.array_equal(got_out, po) and np.array_equal(got_in, pi)
+    assert history[-1] == vnm.vnm_retained_score(S, V, M, SCALE, po, pi)
