@@ -15,7 +15,7 @@
 //   * the 2-bit positions of a lane's two values in a block become one byte selector, and one
 //     V_PERM_B32 picks the two matching halfwords of X out of the block's four; one V_DOT2_F32_F16
 //     adds the two products to the lane's fp32 sum.
-// One workgroup owns one 32-row tile and all of K; each of its waves takes a contiguous range of K steps
+// One workgroup owns one 32-row tile (or half of one) and all of K; each of its waves takes a contiguous range of K steps
 // with a ring of steps of weights requested ahead, and the waves add their sums through LDS at the end.
 #include "vnm_internal.h"
 
@@ -37,30 +37,39 @@ struct GemvArgs {
 // NTOK: token rows computed (1, 2 or 4; rows beyond T count as zero and are not stored).
 // DUAL: the 64-row block carries one column table per 32-row tile (V = 32 patterns).
 // WAVES: waves per workgroup; RING: K steps of weights a wave requests ahead.
-template <int NTOK, bool DUAL, int WAVES, int RING>
+// HALF: a workgroup has half a tile (16 rows) and a lane one of two adjacent K steps -- still 16 bytes per lane in runs of
+// 256 --, so that a step of the code is a pair of K steps.  For layers whose tiles would leave half of the compute units
+// idle (gemv_half).
+template <int NTOK, bool DUAL, int WAVES, int RING, bool HALF>
 __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int NT = DUAL ? 2 : 1;
   constexpr int THREADS = 64 * WAVES;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const unsigned rp = blockIdx.x >> 1;             // 64-row block of the packed copy
-  const unsigned at = blockIdx.x & 1;              // its 32-row tile
-  const unsigned S = (unsigned)a.S;
+  constexpr int KS = HALF ? 2 : 1;                 // K steps of a step of this code
+  const unsigned unit = HALF ? blockIdx.x >> 1 : blockIdx.x;
+  const unsigned rh = HALF ? blockIdx.x & 1 : 0;   // half of the tile
+  const unsigned rp = unit >> 1;                   // 64-row block of the packed copy
+  const unsigned at = unit & 1;                    // its 32-row tile
+  const unsigned SK = (unsigned)a.S, S = (SK + KS - 1) / KS;
   const int M = a.M;
   const int in = (int)a.in;
   const int xpitch = in * 2 + 128;                 // bytes per token row of X in LDS
   unsigned char* xlds = smem;
-  // this wave's strips: [ring slot][token][32 halfwords]
-  unsigned char* xg = smem + (size_t)NTOK * xpitch + (size_t)wave * (RING * NTOK * 64);
-  float* red = (float*)(smem + (size_t)NTOK * xpitch + (size_t)WAVES * RING * NTOK * 64);
+  // this wave's strips: [ring slot][token][KS][32 halfwords]
+  unsigned char* xg = smem + (size_t)NTOK * xpitch + (size_t)wave * (RING * NTOK * KS * 64);
+  float* red = (float*)(smem + (size_t)NTOK * xpitch + (size_t)WAVES * RING * NTOK * KS * 64);
 
   // entry j of a strip is kept column kq of block 4 hj + g of the step; its offset inside the step's
   // 8 M raw columns is byte 2 hj + (g & 1) of dword ((g >> 1) * 4 + kq) (per table) of the column table
   const int j = lane & 31, hj = j >> 4, gj = (j >> 2) & 3, kqj = j & 3;
   const int pcb_off = ((((gj >> 1) * 4 + kqj) * NT + (DUAL ? at : 0)) << 2) + 2 * hj + (gj & 1);
   const int tokhalf = lane >> 5;                   // gather: lanes 0..31 take tokens 0, 2; lanes 32..63 tokens 1, 3
-  const int hA = lane >> 5;                        // multiply: half of the K step
+                                                   // (HALF: K steps 0 and 1 of every token)
+  const int hA = HALF ? (lane >> 4) & 1 : lane >> 5;     // multiply: half of the K step
+  const unsigned sp = HALF ? lane >> 5 : 0;              // its K step of the pair
+  const unsigned op = HALF ? hA * 32 + rh * 16 + (lane & 15) : lane;   // its operand's place in the packed copy
 
   struct Slot { uint4 w; unsigned idx, pcb; };
   // this wave's K steps: a contiguous range
@@ -70,13 +79,15 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
   // Loads beyond the range are still issued (the count of loads in flight is the same on every path),
   // but every lane then reads lane 0's operand of step 0 of the tile: one cache line, not eight.
   auto load_pcb = [&](Slot& o, unsigned s) {
-    s = s < s1 ? s : 0;
-    o.pcb = a.pcol[(rp * S + s) * (32u * NT) + pcb_off];
+    s = s < s1 ? s * KS + sp : 0;
+    s = HALF && s >= SK ? 0 : s;
+    o.pcb = a.pcol[(rp * SK + s) * (32u * NT) + pcb_off];
   };
   auto load_w = [&](Slot& o, unsigned s) {
-    const unsigned l = s < s1 ? lane : 0;
-    s = s < s1 ? s : 0;
-    const unsigned rs = rp * S + s;
+    const unsigned l = s < s1 ? op : 0;
+    s = s < s1 ? s * KS + sp : 0;
+    s = HALF && s >= SK ? 0 : s;                   // (the pair's second step may not exist: its strip is zero)
+    const unsigned rs = rp * SK + s;
     o.idx = *(const unsigned short*)(a.pidx + (((rs * 64 + l) * 2 + at) * 2u));
     o.w = *(const uint4*)(a.pa + (((rs * 2 + at) * 64 + l) * 16u));
   };
@@ -126,17 +137,17 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
   // first, then all stores (two LDS round trips per round).  Branch-free: a column beyond `in` or a
   // token beyond T reads X[0][0] and stores zero; with one token both halves of the wave do the same.
   // A slot beyond the wave's range holds step 0's column table: its strip is filled and never used.
-  constexpr int NIT = (NTOK + 1) / 2;
-  const int tg0 = tokhalf < NTOK ? tokhalf : NTOK - 1;          // token of this lane in gather pass 0
+  constexpr int NIT = HALF ? NTOK : (NTOK + 1) / 2;
+  const int tg0 = HALF ? 0 : tokhalf < NTOK ? tokhalf : NTOK - 1;          // token of this lane in gather pass 0
   auto gather_round = [&](unsigned sb) {
     unsigned short v[RING][NIT];
 #pragma unroll
     for (int i = 0; i < RING; ++i) {
-      const unsigned s = sb + i < s1 ? sb + i : 0;
-      const int col = (int)s * 8 * M + (int)ring[i].pcb;
+      const unsigned s = sb + i < s1 ? (sb + i) * KS + sp : 0;
+      const int col = (int)s * 8 * M + (int)ring[i].pcb;         // (a step beyond the last: beyond `in`)
 #pragma unroll
       for (int it = 0; it < NIT; ++it) {
-        const int t = it == 0 ? tg0 : 2 * it + tokhalf;
+        const int t = HALF ? it : it == 0 ? tg0 : 2 * it + tokhalf;
         const bool ok = t < a.T && col < in;
         const unsigned short x = *(const unsigned short*)(xlds + (ok ? t * xpitch + col * 2 : 0));
         v[i][it] = ok ? x : (unsigned short)0;
@@ -146,8 +157,8 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
     for (int i = 0; i < RING; ++i)
 #pragma unroll
       for (int it = 0; it < NIT; ++it) {
-        const int t = it == 0 ? tg0 : 2 * it + tokhalf;
-        *(unsigned short*)(xg + (i * NTOK + t) * 64 + j * 2) = v[i][it];
+        const int t = HALF ? it : it == 0 ? tg0 : 2 * it + tokhalf;
+        *(unsigned short*)(xg + ((i * NTOK + t) * KS + sp) * 64 + j * 2) = v[i][it];
       }
   };
   auto multiply = [&](const Slot& o, int slot) {
@@ -163,7 +174,7 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
     const unsigned wv[4] = {o.w.x, o.w.y, o.w.z, o.w.w};
 #pragma unroll
     for (int t = 0; t < NTOK; ++t) {
-      const unsigned char* strip = xg + (slot * NTOK + t) * 64 + hA * 32;
+      const unsigned char* strip = xg + ((slot * NTOK + t) * KS + sp) * 64 + hA * 32;
       const uint4 x0 = *(const uint4*)strip, x1 = *(const uint4*)(strip + 16);
       const unsigned xd[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
@@ -201,15 +212,16 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
 #pragma unroll
   for (int t = 0; t < NTOK; ++t) red[(wave * NTOK + t) * 64 + lane] = acc[t];
   __syncthreads();
-  for (int e = tid; e < 32 * NTOK; e += THREADS) {
-    const int tok = e >> 5, i = e & 31;
-    const int64_t o = (int64_t)rp * 64 + at * 32 + i;
+  constexpr int ROWS = HALF ? 16 : 32;
+  for (int e = tid; e < ROWS * NTOK; e += THREADS) {
+    const int tok = e / ROWS, i = e % ROWS;
+    const int64_t o = (int64_t)rp * 64 + at * 32 + rh * 16 + i;
     if (tok < a.T && o < a.out) {
       float sum = 0.f;
 #pragma unroll
       for (int w = 0; w < WAVES; ++w) {
-        sum += red[(w * NTOK + tok) * 64 + i];
-        sum += red[(w * NTOK + tok) * 64 + 32 + i];
+#pragma unroll
+        for (int g = 0; g < 64 / ROWS; ++g) sum += red[(w * NTOK + tok) * 64 + g * ROWS + i];
       }
       if (a.bias) sum += (float)a.bias[o];
       const int64_t dst = a.perm_out ? (int64_t)a.perm_out[o] : o;          // Eq. 6, P_o^T
@@ -222,8 +234,8 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
 
 int64_t gemv_max_tokens() { return 4; }
 
-static size_t gemv_lds(int ntok, int64_t in, int waves, int ring) {
-  return (size_t)ntok * ((size_t)in * 2 + 128) + (size_t)waves * ring * ntok * 64 + (size_t)waves * ntok * 64 * 4;
+static size_t gemv_lds(int ntok, int64_t in, int waves, int ring) {       // (with room for pairs of steps)
+  return (size_t)ntok * ((size_t)in * 2 + 128) + (size_t)waves * ring * ntok * 128 + (size_t)waves * ntok * 64 * 4;
 }
 
 static int gemv_ntok(int64_t T) { return T <= 1 ? 1 : (T <= 2 ? 2 : 4); }
@@ -235,6 +247,14 @@ static int gemv_ntok(int64_t T) { return T <= 1 ? 1 : (T <= 2 ? 2 : 4); }
 // measured slower (ring 2 / 4 / 8, 4096 x 4096, one token: 7.0 / 7.2 / 8.1 us).
 constexpr int kGvRing = 2;
 static int gemv_waves(const Dims& d) { return 2 * packed_row_blocks(d) > 256 ? 8 : 16; }
+
+// Half tiles while they are at most one workgroup per compute unit.  8 waves where a pass of them holds a row of X and K is
+// short, else 16.  Weights from HBM, one token, us: whole tiles (16 waves) / half tiles with 16 waves / with 8:
+// 4096 x 4096, M = 5 7.2 / 6.3 / 6.5, M = 8 (64 steps) 4.9 / 5.1 / 4.6; 4096 x 11008, M = 5 14.1 / 11.9 / 12.4; 1024 x 8192, M = 5
+// 7.5 / 5.9 / 6.9; 2048 x 5504, M = 12 (58 steps) 4.2 / 3.9 / 4.2; 2048 x 2048, M = 5 4.2 / 3.9 / 3.7; 128 x 128 2.7 / 2.9 / 2.3;
+// 64 x 11008, M = 8 6.9 / 5.1 / 5.7.  4100 x 4096 (65 row blocks) keeps whole tiles.
+static bool gemv_half(const Dims& d) { return 4 * packed_row_blocks(d) <= 256; }
+static bool gemv_half_short(const Dims& d) { return d.in <= 8 * 64 * 8 && d.S <= 80; }
 
 bool spmm_gemv_applicable(int64_t T, int64_t ldx, const Dims& d) {
   if (T < 1 || T > gemv_max_tokens() || !has_packed(d.V, d.M) || d.in % 8) return false;
@@ -249,11 +269,11 @@ bool spmm_gemv_applicable(int64_t T, int64_t ldx, const Dims& d) {
   return gemv_lds(gemv_ntok(T), d.in, gemv_waves(d), kGvRing) <= 150 * 1024;
 }
 
-template <int NTOK, bool DUAL, int WAVES>
+template <int NTOK, bool DUAL, int WAVES, bool HALF>
 static int launch_gemv_cfg(const GemvArgs& a, int64_t Rp, hipStream_t st) {
-  auto kern = spmm_gemv_kernel<NTOK, DUAL, WAVES, kGvRing>;
+  auto kern = spmm_gemv_kernel<NTOK, DUAL, WAVES, kGvRing, HALF>;
   if (int rc_lds = allow_big_lds((const void*)kern, "hipFuncSetAttribute(spmm_gemv)")) return rc_lds;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(2 * Rp)), dim3(64 * WAVES), gemv_lds(NTOK, a.in, WAVES, kGvRing), st, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((HALF ? 4 : 2) * Rp)), dim3(64 * WAVES), gemv_lds(NTOK, a.in, WAVES, kGvRing), st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "spmm_gemv_kernel"); return VNM_ERR_HIP; }
   return VNM_OK;
@@ -262,7 +282,9 @@ static int launch_gemv_cfg(const GemvArgs& a, int64_t Rp, hipStream_t st) {
 template <int NTOK, bool DUAL>
 static int launch_gemv_shape(const GemvArgs& a, const Dims& d, hipStream_t st) {
   const int64_t Rp = packed_row_blocks(d);
-  return gemv_waves(d) == 8 ? launch_gemv_cfg<NTOK, DUAL, 8>(a, Rp, st) : launch_gemv_cfg<NTOK, DUAL, 16>(a, Rp, st);
+  if (gemv_half(d))
+    return gemv_half_short(d) ? launch_gemv_cfg<NTOK, DUAL, 8, true>(a, Rp, st) : launch_gemv_cfg<NTOK, DUAL, 16, true>(a, Rp, st);
+  return gemv_waves(d) == 8 ? launch_gemv_cfg<NTOK, DUAL, 8, false>(a, Rp, st) : launch_gemv_cfg<NTOK, DUAL, 16, false>(a, Rp, st);
 }
 
 // X: 16-byte aligned, ldx a multiple of 8 (what spmm_smfmac_applicable checks); spmm_gemv_applicable(T, ldx, d) holds

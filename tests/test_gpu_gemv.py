@@ -1,0 +1,35 @@
+"""Products of one to four tokens on the vector ALUs: whole and half tiles of the packed copy."""
+
+import pytest
+import torch
+
+import paper_2410_16135_amd as vnm
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+# half tiles with 8 waves and with 16 (a row of X longer than 4096, more than 80 steps), odd and even numbers of K steps, one
+# step, fewer pairs of steps than waves, rows that fill no half tile, no tile and no row block, one and two column tables;
+# 64 row blocks and 65 (whole tiles)
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("out,inn,V,M", [
+    (64, 8, 64, 4), (17, 40, 32, 5), (96, 80, 32, 5), (100, 1032, 64, 8), (130, 3320, 128, 5), (33, 4096, 64, 6), (250, 4104, 64, 16),
+    (70, 11008, 32, 7), (4096, 264, 64, 4), (4090, 512, 32, 8), (4097, 264, 64, 4)])
+def test_few_tokens(out, inn, V, M, T):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(out + inn)
+    c = vnm.vnm_prune_compress((torch.randn((out, inn), generator=g, device=DEV) * 0.02).half(), V, M)
+    X = torch.randn((T, inn), generator=g, device=DEV).half()
+    bias = torch.randn(out, generator=g, device=DEV).half()
+    po = torch.randperm(out, generator=g, device=DEV).to(torch.int32)
+    W = vnm.vnm_decompress(c).double()
+    want, mag = X.double() @ W.t(), X.double().abs() @ W.abs().t()
+    # 2 kept products per block and at most 64 partial sums, each addition rounded in fp32
+    bound = (2 * -(-inn // M) + 64) * 2.0 ** -24 * mag
+    Y = vnm.vnm_spmm(X, c, out_dtype=torch.float32)
+    assert bool(((Y.double() - want).abs() <= bound).all())
+    Z = vnm.vnm_spmm_fused(X, c, bias=bias, perm_out=po, out_dtype=torch.float32)
+    want_z = torch.empty_like(want).index_copy_(1, po.long(), want + bias.double())
+    bound_z = torch.empty_like(bound).index_copy_(1, po.long(), bound + 2.0 ** -23 * (mag + bias.double().abs()))
+    assert bool(((Z.double() - want_z).abs() <= bound_z).all())
