@@ -83,7 +83,8 @@ enum PruneBy { kAbs, kScored, kRia };
 // per kept candidate: fp64 operations are cheaper than an fp32 tile next to the weights, which takes twice their room and
 // leaves a third of the workgroups (or of the span) per compute unit.  4096 x 4096 at 64:2:5 with the mask: 49 us, against
 // 19 for writing the scores and 57 for kScored reading them; 12 of the 49 are the norms' scores, 6 the candidates'.
-template <PruneBy BY>
+// BATCH: rows of W a thread requests at a time (prune_batch)
+template <PruneBy BY, int BATCH>
 __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int V = a.V, M = a.M;
@@ -137,7 +138,7 @@ __global__ void __launch_bounds__(256) prune_pack_kernel(const PruneFastArgs a) 
     double acc[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.0;
-    constexpr int kBatch = 12;
+    constexpr int kBatch = BATCH;
     // rows of this tile that exist in W (none when the 8 columns lie beyond the last one)
     const int64_t rows_left = a.out - r * V;
     const int v_real = !col_ok || rows_left <= 0 ? 0 : (rows_left < V ? (int)rows_left : V);
@@ -507,9 +508,13 @@ int launch_prune_fast_scored(const void* W, int64_t ldw, const void* S, int64_t 
     a.pa = (uint4*)(p + pl.pa_off); a.pidx = (unsigned short*)(p + pl.pidx_off); a.pcol = (unsigned*)(p + pl.pcol_off);
   }
   const size_t lds = (size_t)prune_fast_lds(d.V, d.M, a.KSW, true);
-  if (int rc_lds = allow_big_lds((const void*)prune_pack_kernel<kScored>, "hipFuncSetAttribute(prune_pack scored)")) return rc_lds;
   dim3 grid((unsigned)((d.S + a.KSW - 1) / a.KSW), (unsigned)d.R);
-  hipLaunchKernelGGL(prune_pack_kernel<kScored>, grid, dim3(256), lds, st, a);
+  auto kern = prune_batch(d.V, a.G) == 4   ? prune_pack_kernel<kScored, 4>
+              : prune_batch(d.V, a.G) == 6 ? prune_pack_kernel<kScored, 6>
+              : prune_batch(d.V, a.G) == 8 ? prune_pack_kernel<kScored, 8>
+                                           : prune_pack_kernel<kScored, 12>;
+  if (int rc_lds = allow_big_lds((const void*)kern, "hipFuncSetAttribute(prune_pack scored)")) return rc_lds;
+  hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "prune_pack_kernel<scored>"); return VNM_ERR_HIP; }
   return VNM_OK;
@@ -537,9 +542,13 @@ int launch_prune_fast_ria(const void* W, int64_t ldw, const double* prep, const 
     a.pa = (uint4*)(p + pl.pa_off); a.pidx = (unsigned short*)(p + pl.pidx_off); a.pcol = (unsigned*)(p + pl.pcol_off);
   }
   const size_t lds = (size_t)prune_ria_lds(d.V, d.M, a.KSW);
-  if (int rc_lds = allow_big_lds((const void*)prune_pack_kernel<kRia>, "hipFuncSetAttribute(prune_pack ria)")) return rc_lds;
   dim3 grid((unsigned)((d.S + a.KSW - 1) / a.KSW), (unsigned)d.R);
-  hipLaunchKernelGGL(prune_pack_kernel<kRia>, grid, dim3(256), lds, st, a);
+  auto kern = prune_batch(d.V, a.G) == 4   ? prune_pack_kernel<kRia, 4>
+              : prune_batch(d.V, a.G) == 6 ? prune_pack_kernel<kRia, 6>
+              : prune_batch(d.V, a.G) == 8 ? prune_pack_kernel<kRia, 8>
+                                           : prune_pack_kernel<kRia, 12>;
+  if (int rc_lds = allow_big_lds((const void*)kern, "hipFuncSetAttribute(prune_pack ria)")) return rc_lds;
+  hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "prune_pack_kernel<ria>"); return VNM_ERR_HIP; }
   return VNM_OK;
@@ -562,12 +571,16 @@ int launch_prune_fast(const void* W, int64_t ldw, const Dims& d, void* values, v
     a.pa = (uint4*)(p + pl.pa_off); a.pidx = (unsigned short*)(p + pl.pidx_off); a.pcol = (unsigned*)(p + pl.pcol_off);
   }
   const size_t lds = (size_t)prune_fast_lds(d.V, d.M, a.KSW, false);
-  if (int rc_lds = allow_big_lds((const void*)prune_pack_kernel<kAbs>, "hipFuncSetAttribute(prune_pack)")) return rc_lds;
   // column spans along x: the workgroups that run together then read whole rows of W (every memory
   // channel in use) instead of one window of columns in many rows; on weights that come from HBM
   // 11008 x 4096 takes 62 us instead of 71, 4096 x 11008 66 instead of 71, 4096 x 4096 the same
   dim3 grid((unsigned)((d.S + a.KSW - 1) / a.KSW), (unsigned)d.R);
-  hipLaunchKernelGGL(prune_pack_kernel<kAbs>, grid, dim3(256), lds, st, a);
+  auto kern = prune_batch(d.V, a.G) == 4   ? prune_pack_kernel<kAbs, 4>
+              : prune_batch(d.V, a.G) == 6 ? prune_pack_kernel<kAbs, 6>
+              : prune_batch(d.V, a.G) == 8 ? prune_pack_kernel<kAbs, 8>
+                                           : prune_pack_kernel<kAbs, 12>;
+  if (int rc_lds = allow_big_lds((const void*)kern, "hipFuncSetAttribute(prune_pack)")) return rc_lds;
+  hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "prune_pack_kernel"); return VNM_ERR_HIP; }
   return VNM_OK;

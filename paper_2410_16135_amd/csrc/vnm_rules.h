@@ -2,6 +2,7 @@
 // compiled and checked on any host.
 #pragma once
 #include <stdint.h>
+#include <initializer_list>
 
 namespace vnm {
 
@@ -214,6 +215,16 @@ inline bool kgroups(int pieces, int64_t workgroups, int64_t steps, int M) {
 inline int64_t prune_fast_lds(int V, int M, int steps, bool scored) {
   const int64_t NC = (int64_t)steps * 8 * M, blocks = (int64_t)steps * 8;
   return V * (NC + 4) * 2 + NC * 8 + blocks * 4 + (scored ? V * (NC + 4) * 4 : 0);
+}
+// Rows of W a thread requests at a time, where `groups` threads share a column of V rows: the fewest that need no more trips
+// than 12, which used to be taken everywhere.  Requests beyond the last row are made all the same, and registers they would
+// take are workgroups less.  Pruning from HBM with 12 / with this, us: 4096 x 4096 at 64:2:5 (6 rows) 25.5 / 22.3, V = 64,
+// M = 12 (7) 21.0 / 18.0, 11008 x 4096 at V = 32, M = 4 (4) 59.1 / 50.7, 1000 x 1000 at V = 64, M = 8 (4) 7.1 / 6.6; always 8 would
+// lose where 11 rows then take two trips: 11008 x 4096 at 64:2:5 48.9 / 51.1.
+inline int prune_batch(int V, int groups) {
+  const int rows = (V + groups - 1) / groups, trips = (rows + 11) / 12;
+  for (const int b : {4, 6, 8}) if ((rows + b - 1) / b == trips) return b;
+  return 12;
 }
 // Pruning from scores.  As wide as three workgroups per compute unit allow: a wider span reads longer runs of a row,
 // another workgroup hides more of the dependent phases.  11008 x 4096 with at most 40 / 52 / 64 KiB of LDS, us:

@@ -170,3 +170,10 @@ def test_boxes_cover_the_launch(rule, tiles, groups, log_t):
         if row < g_n:
             seen.append((t_lo + (n >> 3) - row * t_n, g_lo + row))
     assert sorted(seen) == [(t, g) for t in range(tiles) for g in range(groups)]
+
+
+# rows per thread up to 4, 6, 8 and 12, and two and three trips
+@pytest.mark.parametrize("V,groups,batch", [(32, 8, 4), (64, 12, 6), (64, 8, 8), (64, 6, 12), (128, 16, 8), (64, 4, 8), (128, 6, 12), (128, 4, 12),
+                                            (32, 32, 4), (128, 1, 12)])
+def test_prune_batch(rule, V, groups, batch):
+    assert rule("prune_batch(%d, %d)" % (V, groups)) == batch
