@@ -156,10 +156,16 @@ inline unsigned xcd_box_most(int64_t tiles, int64_t groups, unsigned log_t) {
 // Boxes for two kinds of unsplit launches.
 // A single generation (two wave groups, below): the grid that makes an XCD fetch least without a second one.  4096 x 4096 at
 // M = 5, 16 tiles x 16 groups 45.4 -> 44.4 us against runs, 12 x 16 42.9 -> 42.7; M = 8 32.4 -> 30.9.
-// Otherwise 8 parts of the tiles (8 row blocks per workgroup only: the others carry no code for it), where runs and grid order make every XCD fetch most of X (the number of tiles not a
-// multiple of 8) and the weight is the smaller part: 3072 x 768 at M = 8 and 12608 tokens (99 tiles) 48 -> 40 us, 2304 x 1536 at
-// 6000 (47) 26.0 -> 20.3, 10174 x 2824 at 2888 (23 tiles, 3 MiB less per XCD) 147 -> 140.  Boxes in other shapes lose on more than one generation: 11008 x 4096 at V = 32, M = 5 and 2048 tokens
-// in 2 x 4 boxes 46.0 -> 49.1.
+// Otherwise 8 parts of the tiles (8 row blocks per workgroup only: the others carry no code for it), where runs and grid
+// order make every XCD fetch most of X (the number of tiles not a multiple of 8) and the weight is the smaller part.  Not
+// where the largest box, of one more tile than the others, takes a generation (32 workgroups per XCD) more than an even share
+// of the launch: 5832 x 3032 at M = 8 and 2324 tokens (19 tiles x 12 groups, 36 workgroups instead of 28.5) 43.8 us in runs, 61.1
+// in boxes; and only where an XCD fetches 1 MiB less, and 1 MiB more than that for every percent by which that box exceeds the even
+// share: 3702 x 792 at M = 5 and 2198 tokens (24 instead of 18 workgroups, 0.9 MiB) 40.1 and 46.4.  262 random launches with
+// 9 tiles or more, where a box saves 1 MiB at least: boxes everywhere 0.986 of the time without, up to 1.46; by this rule
+// 112 of them, 0.941, none above 1.02.  Staged product alone: 3072 x 768 at M = 8 and 12608 tokens (99 tiles) 48 -> 40 us,
+// 2304 x 1536 at 6000 (47) 26.0 -> 20.3.  Boxes in other shapes lose on more than one generation: 11008 x 4096 at V = 32, M = 5
+// and 2048 tokens in 2 x 4 boxes 46.0 -> 49.1.
 inline XcdOrder xcd_order(int64_t tiles, int64_t groups, int64_t steps, int pieces, int64_t weight_bytes, int64_t staged_bytes,
                           bool one_generation, bool wide, bool in_l2) {
   XcdOrder o{XcdOrder::kGrid, 0};
@@ -180,7 +186,10 @@ inline XcdOrder xcd_order(int64_t tiles, int64_t groups, int64_t steps, int piec
   if (pieces == 1 && tiles >= 16 && wide) {
     const int64_t residues = tiles % 8 == 0 ? 8 : tiles % 4 == 0 ? 4 : tiles % 2 == 0 ? 2 : 1;
     const double now = o.kind == XcdOrder::kRuns ? w / 8 + x : w + x / (double)residues;
-    if (now - (w + x / 8) >= 1048576.0) o = {XcdOrder::kBoxes, 3};
+    const double saved = (now - (w + x / 8)) / 1048576.0;
+    const int64_t most = xcd_box_most(tiles, groups, 3), even = (tiles * groups + 7) / 8;
+    const double excess = (double)most * 8.0 / (double)(tiles * groups) - 1.0;
+    if ((most + 31) / 32 <= (even + 31) / 32 && saved >= 1.0 + 100.0 * excess) o = {XcdOrder::kBoxes, 3};
   }
   return o;
 }

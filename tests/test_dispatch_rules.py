@@ -157,6 +157,16 @@ def test_xcd_order(rule, args, kind, log_t):
         assert rule(call + ".log_t") == log_t
 
 
+# boxes in an unsplit launch of more than one generation: only with no generation more than an even share of the launch takes
+# (the comments are runs or grid order / boxes, us), and where they save more the less even they are
+@pytest.mark.parametrize("args,kind", [
+    ((19, 12, 48, 1, 9.7, 17.8, 0, 1, 0), 1), ((18, 8, 20, 1, 2.5, 4.6, 0, 1, 0), 0),         # 43.8 / 61.1, 40.1 / 46.4
+    ((44, 22, 22, 1, 8.3, 12.3, 0, 1, 0), 0), ((47, 5, 24, 1, 2.0, 23.0, 0, 1, 0), 2)])       # 200 / 210; 26.0 / 20.3
+def test_boxes_only_where_they_are_even(rule, args, kind):
+    tiles, groups, steps, pieces, weight, staged, one, wide, in_l2 = args
+    assert rule("xcd_order(%d, %d, %d, %d, %d, %d, %d, %d, %d).kind" % (tiles, groups, steps, pieces, int(weight * MB), int(staged * MB), one, wide, in_l2)) == kind
+
+
 # the boxes cover every (token tile, group) once, and no XCD's box is larger than the launch provides for
 @pytest.mark.parametrize("tiles,groups,log_t", [(9, 16, 0), (9, 16, 1), (12, 13, 2), (17, 1, 3), (99, 6, 3), (8, 8, 3), (5, 4, 1)])
 def test_boxes_cover_the_launch(rule, tiles, groups, log_t):
