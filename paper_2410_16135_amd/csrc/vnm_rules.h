@@ -162,7 +162,7 @@ inline unsigned xcd_box_most(int64_t tiles, int64_t groups, unsigned log_t) {
 // of the launch: 5832 x 3032 at M = 8 and 2324 tokens (19 tiles x 12 groups, 36 workgroups instead of 28.5) 43.8 us in runs, 61.1
 // in boxes; and only where an XCD fetches 1 MiB less, and 1 MiB more than that for every percent by which that box exceeds the even
 // share: 3702 x 792 at M = 5 and 2198 tokens (24 instead of 18 workgroups, 0.9 MiB) 40.1 and 46.4.  262 random launches with
-// 9 tiles or more, where a box saves 1 MiB at least: boxes everywhere 0.986 of the time without, up to 1.46; by this rule
+// 17 tiles or more, where a box saves 1 MiB at least: boxes everywhere 0.986 of the time without, up to 1.46; by this rule
 // 112 of them, 0.941, none above 1.02.  Staged product alone: 3072 x 768 at M = 8 and 12608 tokens (99 tiles) 48 -> 40 us,
 // 2304 x 1536 at 6000 (47) 26.0 -> 20.3.  Boxes in other shapes lose on more than one generation: 11008 x 4096 at V = 32, M = 5
 // and 2048 tokens in 2 x 4 boxes 46.0 -> 49.1.
@@ -215,8 +215,15 @@ inline bool deep_loop(int pieces, int64_t workgroups, int64_t last_piece, int64_
 // (192) 60.9 / 42.7; 8192 x 4096 at 1024 63.4 / 46.0; 11008 x 4096 at 300 63.0 / 43.9; 5504 x 2048 at 1000 33.4 / 25.0.
 // Pieces of a split K keep the deep loop (4096 x 4096 at 700 tokens 33.0 against 34.3 with two groups; two groups instead of
 // the split 42).  LDS holds two rings up to M = 10.
-inline bool kgroups(int pieces, int64_t workgroups, int64_t steps, int M) {
-  return pieces == 1 && workgroups <= 256 && steps >= 8 && M <= 10;
+// Below 8 row blocks one group is a workgroup of 4 waves on as many compute units, and two take steps to make up for the
+// exchange at the end: 256 x 600 at 7455 tokens and M = 5 (15 steps) 9.5 us with one, 11.2 with two.  Two groups against one,
+// geometric mean and range over 350 random launches of that kind: 8-16 steps 1.08 (0.88-1.25), 17-31 1.00 (0.85-1.13), 32-55
+// 0.95 (0.85-1.06), more 0.88 (0.75-1.09); but at M = 8, where one group has a ring of three images and two have four each, 8-13
+// 1.07 (0.89-1.17), 14-23 0.92 (0.79-1.10), 24-55 0.82 (0.65-1.01), more 0.67.  340 launches of 8 row blocks and more: 8-16
+// steps 0.84, more 0.79 (0.58-1.13; above 1.05 the two where no box of workgroups fits an XCD, see above).
+inline bool kgroups(int pieces, int64_t workgroups, int64_t row_blocks, int64_t steps, int M) {
+  const int least = row_blocks >= 8 ? 8 : M == 8 ? 24 : 56;
+  return pieces == 1 && workgroups <= 256 && steps >= least && M <= 10;
 }
 
 // ---- pruning (vnm_prune_fast.hip): K steps of 8 column blocks that a workgroup takes at a time

@@ -967,7 +967,7 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
   const bool post_permute = KS == 1 && f.perm_out && d.out * y_elem <= permute_rows_max_bytes();
   if (post_permute) a.perm_out = nullptr;
   const int64_t last_piece = d.S - (int64_t)(KS - 1) * a.ks_steps;
-  const bool kg = kgroups(KS, base, d.S, d.M);
+  const bool kg = kgroups(KS, base, a.R, d.S, d.M);
   a.order = xcd_order(tiles, wide && !kg ? (a.R + 7) / 8 : (a.R + 3) / 4, d.S, KS, weight_bytes, tiles * d.S * a.image_bytes, kg, wide, in_l2);
   if (tiles * a.R * d.S >= (1ll << 31)) a.order.kind = XcdOrder::kGrid;
   a.wide_store = (a.y_fp32 == 0) && (a.ldy % 8 == 0) && (((uintptr_t)a.Y & 15) == 0);

@@ -137,10 +137,13 @@ def test_refresh_pruning_steps(rule, V, M, R, S, k):
     assert rule("prune_ria_lds(%d, %d, %d)" % (V, M, k)) <= 64 * 1024
 
 
-@pytest.mark.parametrize("pieces,workgroups,steps,M,groups", [(1, 256, 103, 5, 1), (1, 257, 103, 5, 0), (2, 192, 103, 5, 0), (1, 144, 8, 5, 1),
-                                                              (1, 144, 7, 5, 0), (1, 192, 64, 10, 1), (1, 192, 64, 11, 0)])
-def test_two_wave_groups(rule, pieces, workgroups, steps, M, groups):
-    assert rule("kgroups(%d, %d, %d, %d)" % (pieces, workgroups, steps, M)) == groups
+# 8 steps at least, below 8 row blocks 56, or 24 at M = 8
+@pytest.mark.parametrize("pieces,workgroups,blocks,steps,M,groups", [
+    (1, 256, 64, 103, 5, 1), (1, 257, 64, 103, 5, 0), (2, 192, 64, 103, 5, 0), (1, 144, 64, 8, 5, 1), (1, 144, 8, 8, 5, 1), (1, 144, 64, 7, 5, 0),
+    (1, 192, 64, 64, 10, 1), (1, 192, 64, 64, 11, 0), (1, 59, 4, 15, 5, 0), (1, 19, 4, 16, 7, 0), (1, 144, 7, 55, 5, 0), (1, 144, 7, 56, 5, 1),
+    (1, 21, 1, 23, 8, 0), (1, 21, 1, 24, 8, 1)])
+def test_two_wave_groups(rule, pieces, workgroups, blocks, steps, M, groups):
+    assert rule("kgroups(%d, %d, %d, %d, %d)" % (pieces, workgroups, blocks, steps, M)) == groups
 
 
 # (tiles, groups, steps, pieces, MiB of weight and staged X, one generation, 8 row blocks per workgroup, parts in L2) -> kind
