@@ -142,11 +142,11 @@ inline bool tiles_by_xcd(int64_t tiles, int64_t groups, int64_t steps, int piece
   return pieces > 1 ? saved >= (4 << 20) && steps / pieces >= 10 : saved >= (8 << 20);
 }
 
-// The numberings: grid order, runs (the XCD order above), and boxes: the XCDs form a grid of 2^log_t parts of the token
+// The numberings: grid order, runs (the XCD order above), boxes: the XCDs form a grid of 2^log_t parts of the token
 // tiles x 8 / 2^log_t parts of the groups, each takes one box, token tiles fastest; boxes differ by at most one in each
-// direction, the launch is 8 of the largest.
+// direction, the launch is 8 of the largest; and columns: runs with the groups fastest, every XCD then has a share of the tiles.
 struct XcdOrder {
-  enum Kind { kGrid, kRuns, kBoxes } kind;
+  enum Kind { kGrid, kRuns, kBoxes, kColumns } kind;
   unsigned log_t;
 };
 inline unsigned xcd_box_most(int64_t tiles, int64_t groups, unsigned log_t) {
@@ -155,7 +155,10 @@ inline unsigned xcd_box_most(int64_t tiles, int64_t groups, unsigned log_t) {
 }
 // Boxes for two kinds of unsplit launches.
 // A single generation (two wave groups, below): the grid that makes an XCD fetch least without a second one.  4096 x 4096 at
-// M = 5, 16 tiles x 16 groups 45.4 -> 44.4 us against runs, 12 x 16 42.9 -> 42.7; M = 8 32.4 -> 30.9.
+// M = 5, 16 tiles x 16 groups 45.4 -> 44.4 us against runs, 12 x 16 42.9 -> 42.7; M = 8 32.4 -> 30.9.  Where no grid of boxes
+// does without a second one, columns if they fetch less than grid order: 660 x 2968 at V = 128, M = 8 and 10442 tokens (82 tiles
+// x 3 groups) 45.8 us in grid order, 27.6 in columns, 34.2 with one wave group; 90 random launches of that kind against one wave
+// group 0.907 (0.74-1.34) in grid order, 0.827 (0.68-1.03) by this rule.
 // Otherwise 8 parts of the tiles (8 row blocks per workgroup only: the others carry no code for it), where runs and grid
 // order make every XCD fetch most of X (the number of tiles not a multiple of 8) and the weight is the smaller part.  Not
 // where the largest box, of one more tile than the others, takes a generation (32 workgroups per XCD) more than an even share
@@ -179,6 +182,11 @@ inline XcdOrder xcd_order(int64_t tiles, int64_t groups, int64_t steps, int piec
       if (tiles < xt || groups < xg || (xcd_box_most(tiles, groups, l) > 32 && share <= 32)) continue;
       const double bytes = w * (double)((groups + xg - 1) / xg) / (double)groups + x * (double)((tiles + xt - 1) / xt) / (double)tiles;
       if (bytes < best) { best = bytes; o = {XcdOrder::kBoxes, l}; }
+    }
+    if (o.kind == XcdOrder::kGrid && share >= groups) {
+      const int64_t residues = tiles % 8 == 0 ? 8 : tiles % 4 == 0 ? 4 : tiles % 2 == 0 ? 2 : 1;
+      const double columns = w + x * (double)(share / groups + 2) / (double)tiles;
+      if (columns < (tiles < 8 ? (double)tiles / 8 : 1.0) * w + x / (double)residues) o.kind = XcdOrder::kColumns;
     }
     return o;
   }
@@ -220,7 +228,7 @@ inline bool deep_loop(int pieces, int64_t workgroups, int64_t last_piece, int64_
 // geometric mean and range over 350 random launches of that kind: 8-16 steps 1.08 (0.88-1.25), 17-31 1.00 (0.85-1.13), 32-55
 // 0.95 (0.85-1.06), more 0.88 (0.75-1.09); but at M = 8, where one group has a ring of three images and two have four each, 8-13
 // 1.07 (0.89-1.17), 14-23 0.92 (0.79-1.10), 24-55 0.82 (0.65-1.01), more 0.67.  340 launches of 8 row blocks and more: 8-16
-// steps 0.84, more 0.79 (0.58-1.13; above 1.05 the two where no box of workgroups fits an XCD, see above).
+// steps 0.84, more 0.79.
 inline bool kgroups(int pieces, int64_t workgroups, int64_t row_blocks, int64_t steps, int M) {
   const int least = row_blocks >= 8 ? 8 : M == 8 ? 24 : 56;
   return pieces == 1 && workgroups <= 256 && steps >= least && M <= 10;

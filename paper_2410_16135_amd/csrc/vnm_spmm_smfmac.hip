@@ -475,6 +475,12 @@ spmm_smfmac_kernel(const SpmmArgs a) {
     tile_id = t_lo + i - row * t_n;
     group_id = g_lo + row;
     piece_id = 0;
+  } else if (KG == 2 && a.order.kind == XcdOrder::kColumns) {
+    const unsigned n = blockIdx.x + gridDim.x * blockIdx.y;
+    const unsigned total = a.tiles * a.groups, xcd = n & 7, each = total >> 3, rest = total & 7;
+    const unsigned id = xcd * each + (xcd < rest ? xcd : rest) + (n >> 3);
+    tile_id = scalar(id / a.groups);
+    group_id = id - tile_id * a.groups;
   }
   const int64_t r = (int64_t)group_id * WR + wr;
   const bool r_valid = r < a.R;

@@ -170,6 +170,24 @@ def test_boxes_only_where_they_are_even(rule, args, kind):
     assert rule("xcd_order(%d, %d, %d, %d, %d, %d, %d, %d, %d).kind" % (tiles, groups, steps, pieces, int(weight * MB), int(staged * MB), one, wide, in_l2)) == kind
 
 
+# two wave groups where every grid of boxes gives an XCD more than 32 workgroups: columns, unless grid order fetches less
+# (the comments are grid order / columns, us)
+@pytest.mark.parametrize("tiles,groups,steps,weight,staged,kind", [
+    (82, 3, 47, 1.1, 75.0, 3), (33, 7, 47, 4.1, 24.2, 3),           # 45.8 / 27.6, 36.0 / 24.9
+    (49, 5, 59, 2.2, 56.5, 3), (12, 21, 24, 4.5, 4.5, 0), (16, 16, 103, 17.6, 21.4, 2)])
+def test_columns_where_no_box_fits(rule, tiles, groups, steps, weight, staged, kind):
+    assert rule("xcd_order(%d, %d, %d, 1, %d, %d, 1, 0, 0).kind" % (tiles, groups, steps, int(weight * MB), int(staged * MB))) == kind
+
+
+# the columns cover every (token tile, group) once, an XCD at most one workgroup more than another
+@pytest.mark.parametrize("tiles,groups", [(82, 3), (49, 5), (13, 17), (8, 31), (3, 85)])
+def test_columns_cover_the_launch(tiles, groups):
+    total = tiles * groups
+    each, rest = total >> 3, total & 7
+    ids = [(n & 7) * each + min(n & 7, rest) + (n >> 3) for n in range(total)]
+    assert sorted((i // groups, i % groups) for i in ids) == [(t, g) for t in range(tiles) for g in range(groups)]
+
+
 # the boxes cover every (token tile, group) once, and no XCD's box is larger than the launch provides for
 @pytest.mark.parametrize("tiles,groups,log_t", [(9, 16, 0), (9, 16, 1), (12, 13, 2), (17, 1, 3), (99, 6, 3), (8, 8, 3), (5, 4, 1)])
 def test_boxes_cover_the_launch(rule, tiles, groups, log_t):

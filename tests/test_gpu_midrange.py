@@ -84,3 +84,10 @@ def test_two_wave_groups(out, inn, T, V, M, ydt):
 @pytest.mark.parametrize("which", [("bias",), ("perm_out",), ("bias", "perm_out")])
 def test_two_wave_groups_epilogue(out, inn, T, V, M, ydt, which):
     test_staged_product_epilogue(out, inn, T, V, M, ydt, which)
+
+
+# two wave groups numbered by columns: 49 tiles x 5 groups and 11 x 22, where no box of workgroups fits an XCD
+@pytest.mark.parametrize("out,inn,T,V,M", [(1037, 520, 6171, 32, 8), (5400, 520, 1300, 64, 8), (5400, 328, 1300, 128, 5)])
+@pytest.mark.parametrize("ydt", [torch.float16, torch.float32])
+def test_two_wave_groups_in_columns(out, inn, T, V, M, ydt):
+    test_staged_product(out, inn, T, V, M, ydt)
