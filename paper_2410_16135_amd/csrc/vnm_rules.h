@@ -86,17 +86,23 @@ inline bool plain_scalar_faster(int64_t T, int64_t out, int64_t B, int M) {
 // ---- pieces of K of the staged product, for T <= 2048 tokens and `pairs` (token tile, 256 channels) pairs, before the
 // limits that scratch and 4 steps per piece set.
 // Up to 256 tokens about 200 workgroups measured best.  Beyond that the partial products (pieces x T x out floats
-// written, then read by the reduction) weigh in: 256 workgroups while that fills the compute units in one generation,
-// and a split in two only where K is long enough to pay for the reduction; exactly 128 pairs (powers of two in tokens
-// and channels) need more of it than 127.  Two pieces against one, in this order at
-// 26 / 43 / 52 / 64 / 103 / 205 steps (V = 64; M = 5 but M = 12 for 43 and M = 8 for 64): 96 pairs 1.12 / 0.96 / 0.91 / 0.87 /
-// 0.75 / 0.64, 112 pairs 1.12 / 1.01 / 0.93 / 0.99 / 0.78 / 0.67, 125 pairs 1.20 / 0.98 / 0.97 / 0.85 / 0.81 / 0.70, 128
-// pairs 1.20 / 1.06 / 1.01 / 1.01 / 0.85 / 0.72.  One pair more and they take a second generation: 129 pairs 1.36 / 1.44 /
-// 1.16 / 1.04 / 1.02 / 0.66, 160 pairs 1.44 / 1.46 / 1.21 / 1.15 / 1.08 / 0.96.
-inline int64_t split_pieces(int64_t T, int64_t pairs, int64_t steps) {
-  if (T <= 256) return (200 + pairs / 2) / pairs;
-  if (pairs <= 85) return 256 / pairs;
-  return steps >= (pairs < 128 ? 40 : pairs == 128 ? 96 : 192) ? 2 : 1;
+// written, then read by the reduction) weigh in: 256 workgroups while that fills the compute units in one generation, and two
+// pieces up to 128 pairs.  Either way only where K is long enough to pay for the reduction: by the columns of X (8 * M * steps) and
+// the results (T * out, in units of 2^15, a pair of 128 tokens).  Staged product with these pieces against one, which is the kernel with two
+// wave groups where that one runs (1030 random layers, 64 to 12000 x 500 to 14000, M 4 to 16, 65 to 2048 tokens, weights from
+// HBM; geometric mean and range) above the line and below it:
+//   results up to 7    0.55 (0.15-1.30)                          22 to 78    0.68 (0.32-1.18)   1.30 (0.80-1.88)
+//              7 to 14 0.67 (0.20-1.25)   1.14 (0.88-1.32)       78 to 120   0.84 (0.57-1.32)   1.14 (0.86-1.62)
+//             14 to 22 0.72 (0.28-1.36)   1.21 (0.79-1.54)       120 to 128  0.92 (0.70-1.30)   1.02 (0.94-1.24)
+// Beyond 128 pairs two pieces take a second generation, 0.94 to 1.28 at 200 to 280 steps; M > 10, where one piece has one wave
+// group, keeps the line it had (129 pairs: 1.02 at 103 steps, 0.66 at 205; 160 pairs 1.08 and 0.96).
+inline int64_t split_pieces(int64_t T, int64_t out, int64_t pairs, int64_t steps, int M) {
+  const int64_t results = (T * out + 32767) / 32768, length = steps * M;
+  if (pairs > 128) return M > 10 && T > 256 && steps >= 192 ? 2 : 1;
+  const int64_t least = results <= 7 ? 0 : results <= 14 ? 128 : results <= 22 ? 240
+                      : results <= 78 ? (T <= 256 ? 300 : 380) : results <= 120 ? 500 : 600;
+  if (length < least) return 1;
+  return T <= 256 ? (200 + pairs / 2) / pairs : pairs <= 85 ? 256 / pairs : 2;
 }
 
 // ---- reduction of a product whose K dimension is split (vnm_spmm_smfmac.hip, vnm_spmm_skinny.hip)

@@ -950,7 +950,7 @@ int launch_spmm_smfmac(const void* Xs, int64_t T, const void* packed, const Dims
   int KS = 1;
   const int64_t base = tiles * ((a.R + 3) / 4);
   if (scratch && T <= kSplitKMaxTokens && base < 192) {
-    int64_t ks = split_pieces(T, base, d.S);
+    int64_t ks = split_pieces(T, d.out, base, d.S, d.M);
     if (ks > 16) ks = 16;
     if (ks > d.S / 4) ks = d.S / 4;                                   // at least 4 K steps each
     while (ks > 1 && ks * T * d.out * 4 > scratch_bytes) --ks;

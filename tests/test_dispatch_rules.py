@@ -121,12 +121,14 @@ def test_sizes_of_the_plain_kernels(rule, T, out, inn, fit):
     assert rule("plain_sizes_fit(%d, %d, %d, 4)" % (T, out, inn)) == fit
 
 
-# two pieces against one, as measured: 128 pairs 0.85 at 103 steps, 1.20 at 26; 129 pairs 1.02 and 0.66 at 205
-@pytest.mark.parametrize("T,pairs,steps,pieces", [
-    (100, 43, 103, 5), (256, 32, 43, 6), (300, 48, 103, 5), (300, 85, 26, 3), (700, 86, 39, 1), (700, 86, 40, 2), (900, 112, 26, 1),
-    (1000, 127, 40, 2), (1000, 128, 96, 2), (1000, 128, 95, 1), (1000, 129, 103, 1), (1000, 129, 191, 1), (1000, 191, 192, 2)])
-def test_split_pieces(rule, T, pairs, steps, pieces):
-    assert rule("split_pieces(%d, %d, %d)" % (T, pairs, steps)) == pieces
+# on both sides of the line by results (T * out) and columns of X (steps * M), and the pieces above it
+@pytest.mark.parametrize("T,out,pairs,steps,M,pieces", [
+    (300, 1200, 15, 31, 4, 1), (300, 1200, 15, 32, 4, 17), (600, 1024, 20, 47, 5, 1), (600, 1024, 20, 48, 5, 12),
+    (250, 8000, 64, 59, 5, 1), (250, 8000, 64, 60, 5, 3), (700, 3000, 72, 75, 5, 1), (700, 3000, 72, 76, 5, 3),
+    (700, 4096, 96, 103, 5, 2), (1000, 3500, 112, 99, 5, 1), (1000, 3500, 112, 100, 5, 2), (2000, 2048, 128, 119, 5, 1), (2000, 2048, 128, 120, 5, 2),
+    (1000, 4100, 136, 300, 5, 1), (1000, 4100, 136, 191, 12, 1), (1000, 4100, 136, 192, 12, 2), (100, 2048, 8, 10, 5, 25)])
+def test_split_pieces(rule, T, out, pairs, steps, M, pieces):
+    assert rule("split_pieces(%d, %d, %d, %d, %d)" % (T, out, pairs, steps, M)) == pieces
 
 
 # K steps of a workgroup of the pruning inside a mask refresh (V, M, row blocks, steps)

@@ -11,9 +11,8 @@ DEV = "cuda:0"
 
 
 # weight larger than X (tiles of a row group together) and smaller, numbers of workgroups that 8 does not divide,
-# exactly 128 (tile, row group) pairs with and without enough K steps, out not a multiple of 4 (scalar reduction),
-# one token past a tile; the deep K loop at its largest M and the next; 8 and 7 steps unsplit; 8 and 7 in the last of
-# two pieces, where 8 are the fewest the deep loop takes at M = 8, 48 and 47 at M = 4; every number of copies per wave
+# exactly 128 (tile, row group) pairs, out not a multiple of 4 (scalar reduction), one token past a tile; short pieces of K;
+# 8 and 7 steps unsplit; two pieces in the deep loop at M = 7 and 9; every number of copies per wave
 @pytest.mark.parametrize("out,inn,T,V,M", [
     (4096, 1024, 257, 64, 4), (1100, 2048, 385, 64, 4), (640, 4096, 129, 128, 5), (4096, 3840, 1024, 64, 5),
     (1030, 3080, 700, 32, 5), (513, 4096, 300, 64, 8), (2048, 768, 2048, 64, 8), (1026, 8192, 260, 64, 16),
@@ -34,6 +33,16 @@ def test_staged_product(out, inn, T, V, M, ydt):
     if ydt == torch.float16:
         bound = bound + 2.0 ** -11 * want.abs() + 2.0 ** -24
     assert bool(((Y.double() - want).abs() <= bound).all())
+
+
+# a split K at the edges of the deep loop: 8 and 7 steps in the last of ten pieces at M = 8, 48 and 47 in the last of two at
+# M = 6, its largest M and the next, two column tables; and one step less than a split takes (results of 22 to 78, up to 22)
+@pytest.mark.parametrize("out,inn,T,V,M", [
+    (2048, 5120, 300, 64, 8), (2048, 5056, 300, 64, 8), (1536, 4608, 2000, 64, 6), (1536, 4560, 2000, 64, 6), (1540, 7200, 900, 64, 9),
+    (1540, 7200, 900, 64, 10), (2048, 5000, 700, 32, 5), (1030, 3040, 900, 64, 4), (1030, 3008, 900, 64, 4), (1100, 1920, 500, 64, 8), (1100, 1856, 500, 64, 8)])
+@pytest.mark.parametrize("ydt", [torch.float16, torch.float32])
+def test_staged_product_split(out, inn, T, V, M, ydt):
+    test_staged_product(out, inn, T, V, M, ydt)
 
 
 # the reduction's epilogue, four results per thread and one: bias and output permutation after the deep loop (M = 8, 9)
@@ -77,6 +86,14 @@ KG = [(4096, 320, 1025, 64, 5), (4090, 360, 1100, 64, 5), (2056, 1632, 1500, 64,
 @pytest.mark.parametrize("ydt", [torch.float16, torch.float32])
 def test_two_wave_groups(out, inn, T, V, M, ydt):
     test_staged_product(out, inn, T, V, M, ydt)
+
+
+# the same after pieces of K long enough to be split: the deep loop (M = 8, 9) and the shorter one
+@pytest.mark.parametrize("out,inn,T,V,M", [(1030, 8192, 900, 64, 8), (1540, 7200, 900, 64, 9), (2048, 5000, 700, 32, 5), (8192, 3000, 100, 64, 8)])
+@pytest.mark.parametrize("ydt", [torch.float16, torch.float32])
+@pytest.mark.parametrize("which", [("bias",), ("perm_out",), ("bias", "perm_out")])
+def test_split_epilogue(out, inn, T, V, M, ydt, which):
+    test_staged_product_epilogue(out, inn, T, V, M, ydt, which)
 
 
 @pytest.mark.parametrize("out,inn,T,V,M", [(2050, 2040, 1300, 64, 5), (4096, 2048, 2048, 32, 8), (2100, 1500 // 8 * 8, 2900, 64, 8)])
