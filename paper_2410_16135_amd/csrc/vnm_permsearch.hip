@@ -288,52 +288,58 @@ out_gain_kernel(const unsigned* __restrict__ rowM, const int64_t* __restrict__ L
     if (acc[r]) atomicAdd((unsigned long long*)&gain[r * d.Rf + k], acc[r]);
 }
 
-// Objective: a wave per (row block, column block) of the permuted matrix, ragged ones included; lane v takes the rows v,
-// v + 64 of the block.  A thread adds up its rows' scores per column, the wave their sums; every lane then knows the four
-// best columns.  Bound by the gather of single scores (a permutation of the columns leaves nothing contiguous): 2048 x 2048 at V = 64,
-// M = 5 294 us with a thread per (row block, column block), 61 now.
+// Objective: L lanes per (row block, column block) of the permuted matrix, ragged ones included; lane v takes row v of the
+// block, and row v + 64 where V is 128 (H = 2).  A lane adds up its rows' scores per column, the L lanes their sums; each of them
+// then knows the four best columns.  Bound by the gather of single scores (a permutation of the columns leaves nothing
+// contiguous), so no lane may be left without a row, and on large matrices by the one atomic per workgroup, so at most
+// kRetainedGroups of them walk the blocks.  Whole call, of which 55 us are the uploads and the wait, with a thread per block / a wave
+// per block / now: 2048 x 2048 at V = 64, M = 5 185 / 101 / 81 us, V = 16, M = 4 119 / 254 / 76; 4096 x 4096 at V = 64, M = 5 367 / 222 /
+// 124, V = 32, M = 4 215 / 454 / 113, V = 16, M = 4 178 / 848 / 114 (2048 workgroups 111, 4096 124).
+constexpr int64_t kRetainedGroups = 1024;
+template <int L, int H>
 __global__ void __launch_bounds__(256)
 retained_kernel(const float* __restrict__ S, PsDims d, const int* __restrict__ po, const int* __restrict__ pi,
                 unsigned long long* __restrict__ total) {
-  const int lane = threadIdx.x & 63;
-  const int64_t id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & (L - 1);
   unsigned long long mine = 0;
-  if (id < d.R * d.B) {                                     // uniform over the wave
+  // (the bounds are uniform over the L lanes)
+  for (int64_t id = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L; id < d.R * d.B; id += (int64_t)gridDim.x * (256 / L)) {
     const int64_t r = id / d.B, b = id - r * d.B;
     const int64_t o0 = r * d.V;
     const int rows = (int)(o0 + d.V < d.out ? d.V : d.out - o0);
-    const float* row[2];
+    const float* row[H];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) row[h] = S + (int64_t)po[o0 + (lane + 64 * h < rows ? lane + 64 * h : 0)] * d.lds;
+    for (int h = 0; h < H; ++h) row[h] = S + (int64_t)po[o0 + (lane + L * h < rows ? lane + L * h : 0)] * d.lds;
     int64_t bL[4] = {-1, -1, -1, -1};
-    unsigned bx[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};       // this lane's scores in the best columns
+    unsigned bx[H][4] = {};                                 // this lane's scores in the best columns
     for (int c = 0; c < d.M; ++c) {
       const int64_t i = b * d.M + c;
-      unsigned x[2] = {0, 0};
+      unsigned x[H] = {};
       if (i < d.in) {
         const int64_t src = pi[i];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < H; ++h) {
           const unsigned q = quantise(row[h][src], d.scale);
-          x[h] = lane + 64 * h < rows ? q : 0u;
+          x[h] = lane + L * h < rows ? q : 0u;
         }
       }
-      int64_t L = (int64_t)x[0] + x[1];
-      for (int off = 32; off > 0; off >>= 1) L += __shfl_xor(L, off, 64);
+      int64_t sum = 0;
+#pragma unroll
+      for (int h = 0; h < H; ++h) sum += x[h];
+#pragma unroll
+      for (int off = L / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
       // inserted in front of the first that it beats (sum descending, index ascending); moves down from the last place up
-      const bool g[4] = {L > bL[0], L > bL[1], L > bL[2], L > bL[3]};
+      const bool g[4] = {sum > bL[0], sum > bL[1], sum > bL[2], sum > bL[3]};
 #pragma unroll
       for (int k = 3; k >= 0; --k) {
         const bool from_above = k > 0 && g[k > 0 ? k - 1 : 0];
-        const int64_t l = from_above ? bL[k > 0 ? k - 1 : 0] : L;
-        const unsigned y0 = from_above ? bx[0][k > 0 ? k - 1 : 0] : x[0], y1 = from_above ? bx[1][k > 0 ? k - 1 : 0] : x[1];
-        bL[k] = g[k] ? l : bL[k];
-        bx[0][k] = g[k] ? y0 : bx[0][k];
-        bx[1][k] = g[k] ? y1 : bx[1][k];
+        bL[k] = g[k] ? (from_above ? bL[k > 0 ? k - 1 : 0] : sum) : bL[k];
+#pragma unroll
+        for (int h = 0; h < H; ++h) bx[h][k] = g[k] ? (from_above ? bx[h][k > 0 ? k - 1 : 0] : x[h]) : bx[h][k];
       }
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < H; ++h) {
       unsigned m1 = 0, m2 = 0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -342,10 +348,10 @@ retained_kernel(const float* __restrict__ S, PsDims d, const int* __restrict__ p
       }
       mine += (unsigned long long)m1 + m2;
     }
-    for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
   }
+  for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
   __shared__ unsigned long long part[4];
-  if (lane == 0) part[threadIdx.x >> 6] = mine;
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mine;
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned long long t = part[0] + part[1] + part[2] + part[3];
@@ -411,8 +417,10 @@ int upload(const Ctx& c, int64_t off, const int* host, int64_t n, bool wait = tr
 int objective(const Ctx& c, int64_t* value) {
   const PsDims& d = c.d;
   hipLaunchKernelGGL(fill_i64_kernel, dim3(1), dim3(256), 0, c.st, c.at<int64_t>(c.l.total), (int64_t)1, (int64_t)0);
-  hipLaunchKernelGGL(retained_kernel, dim3((unsigned)((d.R * d.B + 3) / 4)), dim3(256), 0, c.st, c.S, d,
-                     c.at<int>(c.l.po), c.at<int>(c.l.pi), c.at<unsigned long long>(c.l.total));
+  auto retained = d.V == 16 ? retained_kernel<16, 1> : d.V == 32 ? retained_kernel<32, 1> : d.V == 64 ? retained_kernel<64, 1> : retained_kernel<64, 2>;
+  const int64_t groups = (d.R * d.B * (d.V < 64 ? d.V : 64) + 255) / 256;
+  hipLaunchKernelGGL(retained, dim3((unsigned)(groups < kRetainedGroups ? groups : kRetainedGroups)), dim3(256), 0, c.st, c.S, d, c.at<int>(c.l.po),
+                     c.at<int>(c.l.pi), c.at<unsigned long long>(c.l.total));
   if (int rc = check_hip(hipGetLastError(), "retained_kernel")) return rc;
   if (int rc = check_hip(hipMemcpyAsync(value, c.ws + c.l.total, 8, hipMemcpyDeviceToHost, c.st), "hipMemcpyAsync")) return rc;
   return check_hip(hipStreamSynchronize(c.st), "hipStreamSynchronize");

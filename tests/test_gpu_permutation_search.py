@@ -248,3 +248,15 @@ def test_search_is_its_single_steps(out, inn, V, M):
     got_out, got_in, history = vnm.vnm_permutation_search(S, V, M, SCALE, iterations=1)
     assert np.array_equal(got_out, po) and np.array_equal(got_in, pi)
     assert history[-1] == vnm.vnm_retained_score(S, V, M, SCALE, po, pi)
+
+
+# the objective with 16, 32 and 64 lanes per (row block, column block) and with two rows per lane, more of these than one pass of the
+# launch takes, ragged last blocks of both kinds
+@pytest.mark.parametrize("out,inn,V,M", [(2041, 1103, 16, 4), (1000, 2003, 32, 5), (2050, 900, 64, 7), (4100, 700, 128, 4), (16, 7, 16, 5)])
+def test_objective_of_every_block_height(out, inn, V, M):
+    rng = np.random.default_rng(V)
+    S = _scores(rng, out, inn, "outliers")
+    po, pi = rng.permutation(out).astype(np.int32), rng.permutation(inn).astype(np.int32)
+    Sq = orc.quantise_scores(S, SCALE)
+    assert vnm.vnm_retained_score(_dev(S), V, M, SCALE, po, pi) == orc.permutation_objective(Sq, V, M, po, pi)
+    assert vnm.vnm_retained_score(_dev(S), V, M, SCALE) == orc.retained_score(Sq, V, M)
