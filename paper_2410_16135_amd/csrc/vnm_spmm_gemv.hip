@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
   auto load_w = [&](Slot& o, unsigned s) {
     const unsigned l = s < s1 ? op : 0;
     s = s < s1 ? s * KS + sp : 0;
-    s = HALF && s >= SK ? 0 : s;                   // (the pair's second step may not exist: its strip is zero)
+    s = HALF && s >= SK ? 0 : s;                   // (the pair's second step may not exist: set to zero below)
     const unsigned rs = rp * SK + s;
     o.idx = *(const unsigned short*)(a.pidx + (((rs * 64 + l) * 2 + at) * 2u));
     o.w = *(const uint4*)(a.pa + (((rs * 2 + at) * 64 + l) * 16u));
@@ -161,7 +161,9 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
         *(unsigned short*)(xg + ((i * NTOK + t) * KS + sp) * 64 + j * 2) = v[i][it];
       }
   };
-  auto multiply = [&](const Slot& o, int slot) {
+  // the step that an odd number of them leaves out of the last pair has the weights of another (load_w)
+  const unsigned last = HALF && (SK & 1) && sp ? 0u : ~0u;
+  auto multiply = [&](const Slot& o, int slot, unsigned keep) {
     const unsigned ix = o.idx;
     unsigned sel[4];
 #pragma unroll
@@ -171,7 +173,7 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
       const unsigned y = ix >> (4 * g);
       sel[g] = ((y | (y << 14)) & 0x00030003u) * 0x0202u + 0x01000100u;
     }
-    const unsigned wv[4] = {o.w.x, o.w.y, o.w.z, o.w.w};
+    const unsigned wv[4] = {HALF ? o.w.x & keep : o.w.x, HALF ? o.w.y & keep : o.w.y, HALF ? o.w.z & keep : o.w.z, HALF ? o.w.w & keep : o.w.w};
 #pragma unroll
     for (int t = 0; t < NTOK; ++t) {
       const unsigned char* strip = xg + ((slot * NTOK + t) * KS + sp) * 64 + hA * 32;
@@ -197,14 +199,14 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
       // another round follows: every slot is refilled as soon as it has been multiplied
 #pragma unroll
       for (int i = 0; i < RING; ++i) {
-        multiply(ring[i], i);
+        multiply(ring[i], i, ~0u);
         load(ring[i], sb + RING + i);
       }
     } else {
       // the last round requests nothing
 #pragma unroll
       for (int i = 0; i < RING; ++i)
-        if (sb + i < s1) multiply(ring[i], i);
+        if (sb + i < s1) multiply(ring[i], i, sb + i + 1 == S ? last : ~0u);
     }
     __builtin_amdgcn_wave_barrier();               // the next round's stores to the strips stay behind these reads
   }

@@ -33,3 +33,23 @@ def test_few_tokens(out, inn, V, M, T):
     want_z = torch.empty_like(want).index_copy_(1, po.long(), want + bias.double())
     bound_z = torch.empty_like(bound).index_copy_(1, po.long(), bound + 2.0 ** -23 * (mag + bias.double().abs()))
     assert bool(((Z.double() - want_z).abs() <= bound_z).all())
+
+
+# An odd number of K steps leaves half of the last pair of half tiles empty: nothing of it may enter the sums, an infinite weight
+# of the first step (whose operand stands in for the missing one) least of all.  One step, three, and one per wave and more.
+@pytest.mark.parametrize("T", [1, 2, 4])
+@pytest.mark.parametrize("out,steps,V,M", [(64, 1, 64, 4), (40, 3, 32, 8), (128, 17, 64, 5), (64, 33, 128, 8), (200, 101, 64, 5)])
+def test_infinite_weight_in_the_first_step(out, steps, V, M, T):
+    inn = steps * 8 * M
+    g = torch.Generator(device=DEV)
+    g.manual_seed(steps)
+    c = vnm.vnm_prune_compress((torch.randn((out, inn), generator=g, device=DEV) * 0.02).half(), V, M)
+    X = torch.rand((T, inn), generator=g, device=DEV).half() + 0.5               # positive
+    finite = vnm.vnm_spmm(X, c, out_dtype=torch.float32)
+    c.values.view(-1, 2 * -(-inn // M))[3:out:5, 0] = float("inf")
+    vnm.vnm_pack(c)
+    Y = vnm.vnm_spmm(X, c, out_dtype=torch.float32)
+    assert bool(torch.isposinf(Y[:, 3::5]).all())
+    rest = torch.ones(out, dtype=torch.bool, device=DEV)
+    rest[3::5] = False
+    assert torch.equal(Y[:, rest], finite[:, rest])
