@@ -18,6 +18,7 @@
 // One workgroup owns one 32-row tile (or half of one) and all of K; each of its waves takes a contiguous range of K steps
 // with a ring of steps of weights requested ahead, and the waves add their sums through LDS at the end.
 #include "vnm_internal.h"
+#include "vnm_rules.h"
 
 namespace vnm {
 
@@ -236,46 +237,21 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
 
 int64_t gemv_max_tokens() { return 4; }
 
-static size_t gemv_lds(int ntok, int64_t in, int waves, int ring) {       // (with room for pairs of steps)
-  return (size_t)ntok * ((size_t)in * 2 + 128) + (size_t)waves * ring * ntok * 128 + (size_t)waves * ntok * 64 * 4;
-}
-
 static int gemv_ntok(int64_t T) { return T <= 1 ? 1 : (T <= 2 ? 2 : 4); }
-
-// Workgroup shape, from timings of the Llama-2-7B layer shapes at 64:2:5 with the weights coming from
-// HBM.  More tiles than compute units: 8 waves, so that several workgroups share a unit and one's
-// start-up (X, the first weights) overlaps the others' streaming; otherwise 16 waves.  A ring of 2 steps
-// per wave is enough: the stream is kept going by the 16 to 32 waves of a unit, and deeper rings
-// measured slower (ring 2 / 4 / 8, 4096 x 4096, one token: 7.0 / 7.2 / 8.1 us).
-constexpr int kGvRing = 2;
-static int gemv_waves(const Dims& d) { return 2 * packed_row_blocks(d) > 256 ? 8 : 16; }
-
-// Half tiles while they are at most one workgroup per compute unit.  8 waves where a pass of them holds a row of X and K is
-// short, else 16.  Weights from HBM, one token, us: whole tiles (16 waves) / half tiles with 16 waves / with 8:
-// 4096 x 4096, M = 5 7.2 / 6.3 / 6.5, M = 8 (64 steps) 4.9 / 5.1 / 4.6; 4096 x 11008, M = 5 14.1 / 11.9 / 12.4; 1024 x 8192, M = 5
-// 7.5 / 5.9 / 6.9; 2048 x 5504, M = 12 (58 steps) 4.2 / 3.9 / 4.2; 2048 x 2048, M = 5 4.2 / 3.9 / 3.7; 128 x 128 2.7 / 2.9 / 2.3;
-// 64 x 11008, M = 8 6.9 / 5.1 / 5.7.  4100 x 4096 (65 row blocks) keeps whole tiles.
-static bool gemv_half(const Dims& d) { return 4 * packed_row_blocks(d) <= 256; }
-static bool gemv_half_short(const Dims& d) { return d.in <= 8 * 64 * 8 && d.S <= 80; }
 
 bool spmm_gemv_applicable(int64_t T, int64_t ldx, const Dims& d) {
   if (T < 1 || T > gemv_max_tokens() || !has_packed(d.V, d.M) || d.in % 8) return false;
   // 32-bit byte offsets: rows of X, the packed copy, raw column numbers
   if (T * ldx * 2 > 0x7FFFFFFF || packed_layout(d).total > 0x7FFFFFFF || d.S * 8 * d.M + 128 > 0x7FFFFFFF) return false;
   if (2 * packed_row_blocks(d) > 0x7FFFFFFF) return false;
-  // Three and four tokens: only where the tiles leave compute units idle and K is short.  Otherwise the
-  // vector ALUs become the limit and the matrix-core few-token kernel is faster (device time per call
-  // at four tokens, 64:2:5, weights from HBM, this kernel / that one: 4096 x 4096, 103 K steps, 8.0 / 10.6 us;
-  // 11008 x 4096, 344 tiles, 13.2 / 12.7 us; 4096 x 11008, 276 K steps, 16.4 / 13.8 us)
-  if (T > 2 && (2 * packed_row_blocks(d) > 256 || d.S > 224)) return false;
-  return gemv_lds(gemv_ntok(T), d.in, gemv_waves(d), kGvRing) <= 150 * 1024;
+  return gemv_takes(gemv_ntok(T), packed_row_blocks(d), d.in, d.S);
 }
 
 template <int NTOK, bool DUAL, int WAVES, bool HALF>
 static int launch_gemv_cfg(const GemvArgs& a, int64_t Rp, hipStream_t st) {
-  auto kern = spmm_gemv_kernel<NTOK, DUAL, WAVES, kGvRing, HALF>;
+  auto kern = spmm_gemv_kernel<NTOK, DUAL, WAVES, kGemvRing, HALF>;
   if (int rc_lds = allow_big_lds((const void*)kern, "hipFuncSetAttribute(spmm_gemv)")) return rc_lds;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((HALF ? 4 : 2) * Rp)), dim3(64 * WAVES), gemv_lds(NTOK, a.in, WAVES, kGvRing), st, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((HALF ? 4 : 2) * Rp)), dim3(64 * WAVES), (size_t)gemv_lds(NTOK, a.in, WAVES, HALF), st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_hip_error(e, "spmm_gemv_kernel"); return VNM_ERR_HIP; }
   return VNM_OK;
@@ -284,9 +260,9 @@ static int launch_gemv_cfg(const GemvArgs& a, int64_t Rp, hipStream_t st) {
 template <int NTOK, bool DUAL>
 static int launch_gemv_shape(const GemvArgs& a, const Dims& d, hipStream_t st) {
   const int64_t Rp = packed_row_blocks(d);
-  if (gemv_half(d))
-    return gemv_half_short(d) ? launch_gemv_cfg<NTOK, DUAL, 8, true>(a, Rp, st) : launch_gemv_cfg<NTOK, DUAL, 16, true>(a, Rp, st);
-  return gemv_waves(d) == 8 ? launch_gemv_cfg<NTOK, DUAL, 8, false>(a, Rp, st) : launch_gemv_cfg<NTOK, DUAL, 16, false>(a, Rp, st);
+  const bool eight = gemv_waves(NTOK, Rp, d.in, d.S) == 8;
+  if (gemv_half(NTOK, Rp, d.in)) return eight ? launch_gemv_cfg<NTOK, DUAL, 8, true>(a, Rp, st) : launch_gemv_cfg<NTOK, DUAL, 16, true>(a, Rp, st);
+  return eight ? launch_gemv_cfg<NTOK, DUAL, 8, false>(a, Rp, st) : launch_gemv_cfg<NTOK, DUAL, 16, false>(a, Rp, st);
 }
 
 // X: 16-byte aligned, ldx a multiple of 8 (what spmm_smfmac_applicable checks); spmm_gemv_applicable(T, ldx, d) holds

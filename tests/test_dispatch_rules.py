@@ -121,6 +121,21 @@ def test_sizes_of_the_plain_kernels(rule, T, out, inn, fit):
     assert rule("plain_sizes_fit(%d, %d, %d, 4)" % (T, out, inn)) == fit
 
 
+# one to four tokens: the widest rows that whole tiles hold (16 waves up to 128 row blocks, then 8; up to 32 row blocks half
+# tiles only), the widest that half tiles hold, three and four tokens up to 128 row blocks and 224 steps
+@pytest.mark.parametrize("tokens,blocks,inn,steps,half,waves,takes", [
+    (1, 65, 73664, 576, 0, 16, 1), (1, 65, 73672, 576, 0, 16, 0), (1, 129, 75200, 576, 0, 8, 1), (1, 129, 75208, 576, 0, 8, 0),
+    (2, 100, 35264, 276, 0, 16, 1), (2, 100, 35272, 276, 0, 16, 0), (4, 128, 16064, 126, 0, 16, 1), (4, 128, 16072, 126, 0, 16, 0),
+    (1, 64, 72640, 568, 1, 16, 1), (1, 64, 72648, 568, 0, 16, 1), (1, 33, 73664, 576, 0, 16, 1), (1, 32, 72648, 568, 1, 16, 0), (1, 32, 72640, 568, 1, 16, 1),
+    (4, 64, 15040, 118, 1, 16, 1), (4, 64, 15048, 118, 0, 16, 1), (4, 20, 15048, 118, 1, 16, 0),
+    (4, 129, 512, 8, 0, 8, 0), (4, 128, 8192, 224, 0, 16, 1), (4, 128, 8192, 225, 0, 16, 0), (2, 128, 8192, 225, 0, 16, 1),
+    (1, 64, 4096, 80, 1, 8, 1), (1, 64, 4096, 81, 1, 16, 1), (1, 64, 4104, 65, 1, 16, 1)])
+def test_one_to_four_tokens(rule, tokens, blocks, inn, steps, half, waves, takes):
+    assert rule("gemv_half(%d, %d, %d)" % (tokens, blocks, inn)) == half
+    assert rule("gemv_waves(%d, %d, %d, %d)" % (tokens, blocks, inn, steps)) == waves
+    assert rule("gemv_takes(%d, %d, %d, %d)" % (tokens, blocks, inn, steps)) == takes
+
+
 # on both sides of the line by results (T * out) and columns of X (steps * M), and the pieces above it
 @pytest.mark.parametrize("T,out,pairs,steps,M,pieces", [
     (300, 1200, 15, 31, 4, 1), (300, 1200, 15, 32, 4, 17), (600, 1024, 20, 47, 5, 1), (600, 1024, 20, 48, 5, 12),

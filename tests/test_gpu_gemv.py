@@ -53,3 +53,10 @@ def test_infinite_weight_in_the_first_step(out, steps, V, M, T):
     rest = torch.ones(out, dtype=torch.bool, device=DEV)
     rest[3::5] = False
     assert torch.equal(Y[:, rest], finite[:, rest])
+
+
+# rows of X at the edge of what LDS holds: the widest on half tiles, then whole tiles on 33 row blocks
+@pytest.mark.parametrize("out,inn,V,M,T", [(70, 72640, 64, 16, 1), (2080, 72648, 64, 16, 1), (2080, 73664, 32, 16, 1), (2080, 34248, 64, 16, 2),
+                                           (2080, 15040, 32, 16, 3), (2080, 15048, 64, 16, 4), (2080, 16064, 64, 12, 4)])
+def test_few_tokens_on_wide_layers(out, inn, V, M, T):
+    test_few_tokens(out, inn, V, M, T)
