@@ -92,15 +92,15 @@ inline bool plain_scalar_faster(int64_t T, int64_t out, int64_t B, int M) {
 // wave groups where that one runs (1030 random layers, 64 to 12000 x 500 to 14000, M 4 to 16, 65 to 2048 tokens, weights from
 // HBM; geometric mean and range) above the line and below it:
 //   results up to 7    0.55 (0.15-1.30)                          22 to 78    0.68 (0.32-1.18)   1.30 (0.80-1.88)
-//              7 to 14 0.67 (0.20-1.25)   1.14 (0.88-1.32)       78 to 120   0.84 (0.57-1.32)   1.14 (0.86-1.62)
-//             14 to 22 0.72 (0.28-1.36)   1.21 (0.79-1.54)       120 to 128  0.92 (0.70-1.30)   1.02 (0.94-1.24)
+//              7 to 14 0.67 (0.20-1.25)   1.14 (0.88-1.32)       78 to 128   0.83 (0.57-1.32)   1.14 (0.86-1.62)
+//             14 to 22 0.72 (0.28-1.36)   1.21 (0.79-1.54)
 // Beyond 128 pairs two pieces take a second generation, 0.94 to 1.28 at 200 to 280 steps; M > 10, where one piece has one wave
 // group, keeps the line it had (129 pairs: 1.02 at 103 steps, 0.66 at 205; 160 pairs 1.08 and 0.96).
 inline int64_t split_pieces(int64_t T, int64_t out, int64_t pairs, int64_t steps, int M) {
   const int64_t results = (T * out + 32767) / 32768, length = steps * M;
   if (pairs > 128) return M > 10 && T > 256 && steps >= 192 ? 2 : 1;
   const int64_t least = results <= 7 ? 0 : results <= 14 ? 128 : results <= 22 ? 240
-                      : results <= 78 ? (T <= 256 ? 300 : 380) : results <= 120 ? 500 : 600;
+                      : results <= 78 ? (T <= 256 ? 300 : 380) : T <= 600 ? 420 : T <= 1500 ? 500 : 660;
   if (length < least) return 1;
   return T <= 256 ? (200 + pairs / 2) / pairs : pairs <= 85 ? 256 / pairs : 2;
 }

@@ -140,7 +140,8 @@ def test_one_to_four_tokens(rule, tokens, blocks, inn, steps, half, waves, takes
 @pytest.mark.parametrize("T,out,pairs,steps,M,pieces", [
     (300, 1200, 15, 31, 4, 1), (300, 1200, 15, 32, 4, 17), (600, 1024, 20, 47, 5, 1), (600, 1024, 20, 48, 5, 12),
     (250, 8000, 64, 59, 5, 1), (250, 8000, 64, 60, 5, 3), (700, 3000, 72, 75, 5, 1), (700, 3000, 72, 76, 5, 3),
-    (700, 4096, 96, 103, 5, 2), (1000, 3500, 112, 99, 5, 1), (1000, 3500, 112, 100, 5, 2), (2000, 2048, 128, 119, 5, 1), (2000, 2048, 128, 120, 5, 2),
+    (700, 4096, 96, 103, 5, 2), (500, 6000, 96, 83, 5, 1), (500, 6000, 96, 84, 5, 2), (1000, 3500, 112, 99, 5, 1), (1000, 3500, 112, 100, 5, 2),
+    (1024, 4096, 128, 103, 5, 2), (2000, 2048, 128, 131, 5, 1), (2000, 2048, 128, 132, 5, 2),
     (1000, 4100, 136, 300, 5, 1), (1000, 4100, 136, 191, 12, 1), (1000, 4100, 136, 192, 12, 2), (100, 2048, 8, 10, 5, 25)])
 def test_split_pieces(rule, T, out, pairs, steps, M, pieces):
     assert rule("split_pieces(%d, %d, %d, %d, %d)" % (T, out, pairs, steps, M)) == pieces
