@@ -581,9 +581,12 @@ spmm_smfmac_kernel(const SpmmArgs a) {
   unsigned char* ep = smem + (size_t)wave_id * TE * (V * 2 + 8);       // its private region of LDS
   const int64_t t_wave = t0 + kg * TE;
   if constexpr (KG == 2) {
-    // A step has one barrier, so the group with a step less has one to add.  Each wave then hands the sums of the other
-    // group's half of the tokens over: 16 KiB per wave, [16-byte piece][lane].
+    // A step has one barrier, so the group with a step less has one to add: the stores below may not pass it, the other group
+    // still reads its ring (the builtin alone does not order memory, and the loop's clobber ends with the loop).  Each wave then
+    // hands the sums of the other group's half of the tokens over: 16 KiB per wave, [16-byte piece][lane].
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if (S < SG) __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     constexpr int XB = AT * BE * 16 * 64 * 4;
     float* mine = (float*)(smem + (size_t)wave_id * XB);
     const unsigned char* theirs = smem + (size_t)(wave_id ^ WR) * XB;
