@@ -284,10 +284,12 @@ inline int64_t prune_fast_lds(int V, int M, int steps, bool scored) {
   return V * (NC + 4) * 2 + NC * 8 + blocks * 4 + (scored ? V * (NC + 4) * 4 : 0);
 }
 // Rows of W a thread requests at a time, where `groups` threads share a column of V rows: the fewest that need no more trips
-// than 12, which used to be taken everywhere.  Requests beyond the last row are made all the same, and registers they would
-// take are workgroups less.  Pruning from HBM with 12 / with this, us: 4096 x 4096 at 64:2:5 (6 rows) 25.5 / 22.3, V = 64,
-// M = 12 (7) 21.0 / 18.0, 11008 x 4096 at V = 32, M = 4 (4) 59.1 / 50.7, 1000 x 1000 at V = 64, M = 8 (4) 7.1 / 6.6; always 8 would
-// lose where 11 rows then take two trips: 11008 x 4096 at 64:2:5 48.9 / 51.1.
+// than 12, which used to be taken everywhere.  Requests beyond the last row are made all the same, and from |w| alone (62, 67, 80
+// and 109 registers at 4, 6, 8 and 12) the registers are workgroups less; with scores (95 and, computed on the fly, 143 at any
+// number: another phase needs them) it is the requests only.  From HBM, us, with 12 / with this: from |w| 4096 x 4096 at 64:2:5
+// (6 rows) 25.5 / 22.3, V = 64, M = 12 (7) 21.0 / 18.0, 11008 x 4096 at V = 32, M = 4 (4) 59.1 / 50.7, 1000 x 1000 at V = 64, M = 8 (4)
+// 7.1 / 6.6, and always 8 would lose where 11 rows then take two trips: 11008 x 4096 at 64:2:5 48.9 / 51.1; from scores 120 sizes 1.04
+// times this with 12 (up to 1.10), 1.01 with 6; a refresh 1.016 and 1.003 (215 sizes).
 inline int prune_batch(int V, int groups) {
   const int rows = (V + groups - 1) / groups, trips = (rows + 11) / 12;
   for (const int b : {4, 6, 8}) if ((rows + b - 1) / b == trips) return b;
