@@ -242,14 +242,14 @@ def vnm_pack(c: Compressed, N: int = 2) -> Compressed:
     return c
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)      # (typed: 16.0 is refused, also after 16)
 def _spmm_workspace_bytes(T: int, out: int, inn: int, V: int, N: int, M: int) -> int:
     b = ctypes.c_int64(0)
     _check(load_library().vnm_spmm_workspace_bytes(T, out, inn, V, N, M, ctypes.byref(b)), "vnm_spmm_workspace_bytes")
     return b.value
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)      # (typed: 16.0 is refused, also after 16)
 def _spmm_fused_workspace_bytes(T: int, out: int, inn: int, V: int, N: int, M: int, with_perm_in: int) -> int:
     b = ctypes.c_int64(0)
     _check(load_library().vnm_spmm_fused_workspace_bytes(T, out, inn, V, N, M, with_perm_in, ctypes.byref(b)),
@@ -522,7 +522,7 @@ def vnm_spmm_kernel_choice(T: int, c: Compressed, workspace_bytes: int, N: int =
     return ch.value
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)      # (typed: 16.0 is refused, also after 16)
 def vnm_spmm_scratch_bytes(T: int, out: int) -> int:
     b = ctypes.c_int64(0)
     _check(load_library().vnm_spmm_scratch_bytes(T, out, ctypes.byref(b)), "vnm_spmm_scratch_bytes")

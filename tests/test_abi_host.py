@@ -148,3 +148,13 @@ def test_bench_refuses_more_than_one_gpu():
                          timeout=120)
     assert res.returncode != 0
     assert "single-GPU" in res.stderr + res.stdout
+
+
+def test_cached_size_queries_refuse_what_is_no_integer():
+    # the answers for equal integers are kept: a float equal to one of them is refused all the same
+    c = vnm.Compressed(None, None, None, None, 4096, 4096, 64, 5)
+    for query in (lambda T: vnm.vnm_spmm_scratch_bytes(T, 11008), lambda T: vnm.vnm_spmm_workspace_bytes(T, c)):
+        assert query(16) > 0
+        for T in (16.0, "16", None):
+            with pytest.raises((ctypes.ArgumentError, TypeError)):
+                query(T)
