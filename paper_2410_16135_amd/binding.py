@@ -479,21 +479,23 @@ def vnm_refresh_mask(W, B, A, scale: float, V: int, M: int, act=None, N: int = 2
     lib = load_library()
     b = ctypes.c_int64(0)
     _check(lib.vnm_refresh_mask_workspace_bytes(out, inn, V, N, M, ctypes.byref(b)), "vnm_refresh_mask_workspace_bytes")
+    merged, c = torch.empty_like(W), None
     if b.value > 0:                     # three kernels without a score matrix, where sizes and alignment allow them
-        merged = torch.empty_like(W)
         values, meta, colidx, packed = _alloc(vnm_query_sizes(out, inn, V, M, N), W.device)
         mask = torch.empty((out, inn), dtype=torch.uint8, device=W.device)
+        c = Compressed(values, meta, colidx, packed, out, inn, V, M, mask)
         ws = torch.empty(b.value, dtype=torch.uint8, device=W.device)
         status = lib.vnm_refresh_mask(
             _ptr(W), out, inn, W.stride(0), _ptr(B), B.stride(0) if r else 0, _ptr(A), A.stride(0) if r else inn, r,
             float(scale), _ptr(act), V, N, M, _ptr(merged), merged.stride(0), _ptr(values), _ptr(meta), _ptr(colidx),
             _ptr(mask), _ptr(packed), _ptr(ws), ws.numel(), _stream(W))
         if status == 0:
-            return Compressed(values, meta, colidx, packed, out, inn, V, M, mask)
+            return c
+        del ws
         if status != 3:                 # rows that are not 16-byte aligned are the single steps' business
             _check(status, "vnm_refresh_mask")
-    merged = vnm_lora_merge(W, B, A, scale)
-    return vnm_prune_compress_scored(merged, vnm_ria_scores(merged, act), V, M, N, want_mask=True)
+    vnm_lora_merge(W, B, A, scale, merged)
+    return vnm_prune_compress_scored(merged, vnm_ria_scores(merged, act), V, M, N, want_mask=True, out=c)
 
 
 def vnm_stage_x(X, M: int, staged=None):

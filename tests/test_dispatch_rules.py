@@ -155,6 +155,15 @@ def test_refresh_pruning_steps(rule, V, M, R, S, k):
     assert rule("prune_ria_lds(%d, %d, %d)" % (V, M, k)) <= 64 * 1024
 
 
+def test_refresh_cases_reach_every_span(rule):
+    from test_gpu_lora_merge import SPANS
+    for out, inn, V, M, steps, batch in SPANS:
+        R, S = -(-out // V), -(-(-(-inn // M)) // 8)
+        assert rule("prune_ria_steps(%d, %d, %d, %d)" % (V, M, R, S)) == steps, (out, inn, V, M)
+        assert rule("prune_batch(%d, %d)" % (V, min(256 // (steps * M), V))) == batch, (out, inn, V, M)
+    assert {s[4] for s in SPANS} == {1, 2, 4, 8} and {s[5] for s in SPANS} == {4, 6, 8, 12}
+
+
 # 8 steps at least, below 8 row blocks 56, or 24 at M = 8
 @pytest.mark.parametrize("pieces,workgroups,blocks,steps,M,groups", [
     (1, 256, 64, 103, 5, 1), (1, 257, 64, 103, 5, 0), (2, 192, 64, 103, 5, 0), (1, 144, 64, 8, 5, 1), (1, 144, 8, 8, 5, 1), (1, 144, 64, 7, 5, 0),
