@@ -583,6 +583,13 @@ extern "C" int vnm_permutation_search(const void* S, int64_t out, int64_t in, in
   const PsDims& d = c.d;
   int* po = (int*)perm_out;
   int* pi = (int*)perm_in;
+  // Uploads from po and pi may still be under way where a call fails in front of the wait that the next gains end with: the arrays
+  // are the caller's again once this function returns.
+  struct Drain {
+    hipStream_t st;
+    bool armed;
+    ~Drain() { if (armed) (void)hipStreamSynchronize(st); }
+  } drain{c.st, true};
   try {
     for (int64_t i = 0; i < out; ++i) po[i] = (int)i;
     for (int64_t i = 0; i < in; ++i) pi[i] = (int)i;
@@ -630,5 +637,6 @@ extern "C" int vnm_permutation_search(const void* S, int64_t out, int64_t in, in
       if (int rc = objective(c, &history[h++])) return rc;
     }
   } catch (...) { return VNM_ERR_WORKSPACE; }
+  drain.armed = false;                 // (the last objective has waited)
   return VNM_OK;
 }

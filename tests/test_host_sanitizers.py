@@ -30,3 +30,19 @@ def test_host_code_is_clean_under_asan_and_ubsan(tmp_path):
     assert run.returncode == 0, (run.stdout + run.stderr)[-3000:]
     assert "host_check ok" in run.stdout
     shutil.rmtree(tmp_path, ignore_errors=True)
+
+
+def test_search_leaves_no_copy_behind_when_a_launch_fails(tmp_path):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not found")
+    csrc = os.path.join(ROOT, "paper_2410_16135_amd", "csrc")
+    exe = str(tmp_path / "search_errors")
+    # (the device code that the host pass refers to does not exist and is never asked for)
+    cmd = [hipcc, "--cuda-host-only", "-O1", "-std=c++17", "-Wl,--unresolved-symbols=ignore-all", "-I", os.path.join(ROOT, "include"), "-I", csrc,
+           os.path.join(csrc, "vnm_permsearch.hip"), os.path.join(csrc, "vnm_lsa.hip"),
+           os.path.join(ROOT, "tests", "host_sanitize", "search_errors.cpp"), "-o", exe]
+    res = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert res.returncode == 0, res.stderr[-3000:]
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert run.returncode == 0 and "search_errors ok" in run.stdout, (run.stdout + run.stderr)[-3000:]
