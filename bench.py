@@ -619,7 +619,7 @@ def main():
                  "dense_equiv_frac_of_fp16_peak": dense_equiv / spmm_ms / 1e9 / PEAK_FP16_DENSE_TFLOPS,
                  "dense_fp16_gemm_ms": dense_total, "speedup_vs_dense_fp16": dense_total / spmm_ms,
                  "speedup_vs_torch_matmul": sum(torch_ms.values()) / spmm_ms,
-                 "target": "> 1.3x per layer (north star)",
+                 "target": "> 1.3x per layer",
                  "per_layer_speedup": {r["layer"]: r["speedup_vs_dense_fp16"] for r in layer_rows},
                  "weakest_layer": {"layer": weakest["layer"], "speedup_vs_dense_fp16": weakest["speedup_vs_dense_fp16"]},
                  "block": {"groups": groups, "group_ms": [round(g, 4) for g in group_ms], "ms": block_ms,
@@ -740,11 +740,13 @@ def main():
             vnm.vnm_ria_scores(Wm, act, S=S)
             vnm.vnm_prune_compress_scored(Wm, S, L.V, L.M, out=cs)
         t_refresh = timed(refresh, n=20, warm=20)
+        t_one = timed(lambda: vnm.vnm_refresh_mask(Wd, Bl, Al, 2.0, L.V, L.M, act=act), n=20, warm=20)
         result["mask_refresh"] = {
             "layer": L.name, "lora_rank": r_lora, "merge_ms": t_merge, "merge_gbps": 2 * w_bytes / t_merge / 1e6,
-            "merge_ria_prune_ms": t_refresh,
-            "note": "vnm_lora_merge alone, and merge + RIA scores + pruning from scores (one mask update of one "
-                    "layer); HIP-event means"}
+            "merge_ria_prune_ms": t_refresh, "refresh_mask_ms": t_one,
+            "note": "vnm_lora_merge alone; merge + RIA scores + pruning from scores in three calls without the mask; "
+                    "vnm_refresh_mask, which does the three in one call and writes the mask and its outputs into new "
+                    "tensors (one mask update of one layer); HIP-event means"}
         vnm.vnm_ria_scores(Wd, act, S=S)          # the search below uses the scores of the unmerged weight
         # channel-permutation search (Eqs. 7-9) on the first layer's RIA scores, one alternation
         sc = float(2 ** 30) / float(S.max().item())

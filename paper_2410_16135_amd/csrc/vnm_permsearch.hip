@@ -203,8 +203,8 @@ out_update_kernel(const unsigned* __restrict__ rowM, PsDims d, const int* __rest
 // gain[r][k] += over a chunk of NB column blocks: workgroup (k, chunk); the remainder rows of block
 // k over the chunk's columns sit in LDS; items (r, block of the chunk) are spread over the threads.
 // Bound by the gather from LDS, four words and a dozen instructions per (item, row): 512 threads, an item each on a 2048 x
-// 2048 matrix at V = 64, keep twice as many of them in flight as 256 with two: 53 -> 29 us per slot, with the columns' sums requested four at a
-// time and one instruction less in each comparison of four.
+// 2048 matrix at V = 64, keep twice as many of them in flight as 256 with two: 53 -> 29 us per slot, with the columns'
+// sums requested four at a time and one instruction less in each comparison of four.
 constexpr int kGainThreads = 512;
 __global__ void __launch_bounds__(kGainThreads)
 out_gain_kernel(const unsigned* __restrict__ rowM, const int64_t* __restrict__ Lrem, PsDims d,
@@ -289,12 +289,13 @@ out_gain_kernel(const unsigned* __restrict__ rowM, const int64_t* __restrict__ L
 }
 
 // Objective: L lanes per (row block, column block) of the permuted matrix, ragged ones included; lane v takes row v of the
-// block, and row v + 64 where V is 128 (H = 2).  A lane adds up its rows' scores per column, the L lanes their sums; each of them
-// then knows the four best columns.  Bound by the gather of single scores (a permutation of the columns leaves nothing
-// contiguous), so no lane may be left without a row, and on large matrices by the one atomic per workgroup, so at most
-// kRetainedGroups of them walk the blocks.  Whole call, of which 55 us are the uploads and the wait, with a thread per block / a wave
-// per block / now: 2048 x 2048 at V = 64, M = 5 185 / 101 / 81 us, V = 16, M = 4 119 / 254 / 76; 4096 x 4096 at V = 64, M = 5 367 / 222 /
-// 124, V = 32, M = 4 215 / 454 / 113, V = 16, M = 4 178 / 848 / 114 (2048 workgroups 111, 4096 124).
+// block, and row v + 64 where V is 128 (H = 2).  A lane adds up its rows' scores per column, the L lanes their sums;
+// each of them then knows the four best columns.  Bound by the gather of single scores (a permutation of the columns
+// leaves nothing contiguous), so no lane may be left without a row, and on large matrices by the one atomic per
+// workgroup, so at most kRetainedGroups of them walk the blocks.  Whole call, of which 55 us are the uploads and the
+// wait, with a thread per block / a wave per block / now: 2048 x 2048 at V = 64, M = 5 185 / 101 / 81 us, V = 16, M = 4
+// 119 / 254 / 76; 4096 x 4096 at V = 64, M = 5 367 / 222 / 124, V = 32, M = 4 215 / 454 / 113, V = 16, M = 4 178 / 848 /
+// 114 (2048 workgroups 111, 4096 124).
 constexpr int64_t kRetainedGroups = 1024;
 template <int L, int H>
 __global__ void __launch_bounds__(256)
@@ -583,8 +584,8 @@ extern "C" int vnm_permutation_search(const void* S, int64_t out, int64_t in, in
   const PsDims& d = c.d;
   int* po = (int*)perm_out;
   int* pi = (int*)perm_in;
-  // Uploads from po and pi may still be under way where a call fails in front of the wait that the next gains end with: the arrays
-  // are the caller's again once this function returns.
+  // Uploads from po and pi may still be under way where a call fails in front of the wait that the next gains end with:
+  // the arrays are the caller's again once this function returns.
   struct Drain {
     hipStream_t st;
     bool armed;

@@ -87,15 +87,15 @@ inline bool plain_scalar_faster(int64_t T, int64_t out, int64_t B, int M) {
 // limits that scratch and 4 steps per piece set.
 // Up to 256 tokens about 200 workgroups measured best.  Beyond that the partial products (pieces x T x out floats
 // written, then read by the reduction) weigh in: 256 workgroups while that fills the compute units in one generation, and two
-// pieces up to 128 pairs.  Either way only where K is long enough to pay for the reduction: by the columns of X (8 * M * steps) and
-// the results (T * out, in units of 2^15, a pair of 128 tokens).  Staged product with these pieces against one, which is the kernel with two
-// wave groups where that one runs (1030 random layers, 64 to 12000 x 500 to 14000, M 4 to 16, 65 to 2048 tokens, weights from
-// HBM; geometric mean and range) above the line and below it:
+// pieces up to 128 pairs.  Either way only where K is long enough to pay for the reduction: by the columns of X (8 * M *
+// steps) and the results (T * out, in units of 2^15, a pair of 128 tokens).  Staged product with these pieces against
+// one, which is the kernel with two wave groups where that one runs (1030 random layers, 64 to 12000 x 500 to 14000, M 4
+// to 16, 65 to 2048 tokens, weights from HBM; geometric mean and range) above the line and below it:
 //   results up to 7    0.55 (0.15-1.30)                          22 to 78    0.68 (0.32-1.18)   1.30 (0.80-1.88)
 //              7 to 14 0.67 (0.20-1.25)   1.14 (0.88-1.32)       78 to 128   0.83 (0.57-1.32)   1.14 (0.86-1.62)
 //             14 to 22 0.72 (0.28-1.36)   1.21 (0.79-1.54)
-// Beyond 128 pairs two pieces take a second generation, 0.94 to 1.28 at 200 to 280 steps; M > 10, where one piece has one wave
-// group, keeps the line it had (129 pairs: 1.02 at 103 steps, 0.66 at 205; 160 pairs 1.08 and 0.96).
+// Beyond 128 pairs two pieces take a second generation, 0.94 to 1.28 at 200 to 280 steps; M > 10, where one piece has
+// one wave group, keeps the line it had (129 pairs: 1.02 at 103 steps, 0.66 at 205; 160 pairs 1.08 and 0.96).
 inline int64_t split_pieces(int64_t T, int64_t out, int64_t pairs, int64_t steps, int M) {
   const int64_t results = (T * out + 32767) / 32768, length = steps * M;
   if (pairs > 128) return M > 10 && T > 256 && steps >= 192 ? 2 : 1;
@@ -150,7 +150,8 @@ inline bool tiles_by_xcd(int64_t tiles, int64_t groups, int64_t steps, int piece
 
 // The numberings: grid order, runs (the XCD order above), boxes: the XCDs form a grid of 2^log_t parts of the token
 // tiles x 8 / 2^log_t parts of the groups, each takes one box, token tiles fastest; boxes differ by at most one in each
-// direction, the launch is 8 of the largest; and columns: runs with the groups fastest, every XCD then has a share of the tiles.
+// direction, the launch is 8 of the largest; and columns: runs with the groups fastest, every XCD then has a share of
+// the tiles.
 struct XcdOrder {
   enum Kind { kGrid, kRuns, kBoxes, kColumns } kind;
   unsigned log_t;
@@ -162,19 +163,20 @@ inline unsigned xcd_box_most(int64_t tiles, int64_t groups, unsigned log_t) {
 // Boxes for two kinds of unsplit launches.
 // A single generation (two wave groups, below): the grid that makes an XCD fetch least without a second one.  4096 x 4096 at
 // M = 5, 16 tiles x 16 groups 45.4 -> 44.4 us against runs, 12 x 16 42.9 -> 42.7; M = 8 32.4 -> 30.9.  Where no grid of boxes
-// does without a second one, columns if they fetch less than grid order: 660 x 2968 at V = 128, M = 8 and 10442 tokens (82 tiles
-// x 3 groups) 45.8 us in grid order, 27.6 in columns, 34.2 with one wave group; 90 random launches of that kind against one wave
-// group 0.907 (0.74-1.34) in grid order, 0.827 (0.68-1.03) by this rule.
+// does without a second one, columns if they fetch less than grid order: 660 x 2968 at V = 128, M = 8 and 10442 tokens
+// (82 tiles x 3 groups) 45.8 us in grid order, 27.6 in columns, 34.2 with one wave group; 90 random launches of that
+// kind against one wave group 0.907 (0.74-1.34) in grid order, 0.827 (0.68-1.03) by this rule.
 // Otherwise 8 parts of the tiles (8 row blocks per workgroup only: the others carry no code for it), where runs and grid
 // order make every XCD fetch most of X (the number of tiles not a multiple of 8) and the weight is the smaller part.  Not
 // where the largest box, of one more tile than the others, takes a generation (32 workgroups per XCD) more than an even share
-// of the launch: 5832 x 3032 at M = 8 and 2324 tokens (19 tiles x 12 groups, 36 workgroups instead of 28.5) 43.8 us in runs, 61.1
-// in boxes; and only where an XCD fetches 1 MiB less, and 1 MiB more than that for every percent by which that box exceeds the even
-// share: 3702 x 792 at M = 5 and 2198 tokens (24 instead of 18 workgroups, 0.9 MiB) 40.1 and 46.4.  262 random launches with
-// 17 tiles or more, where a box saves 1 MiB at least: boxes everywhere 0.986 of the time without, up to 1.46; by this rule
-// 112 of them, 0.941, none above 1.02.  Staged product alone: 3072 x 768 at M = 8 and 12608 tokens (99 tiles) 48 -> 40 us,
-// 2304 x 1536 at 6000 (47) 26.0 -> 20.3.  Boxes in other shapes lose on more than one generation: 11008 x 4096 at V = 32, M = 5
-// and 2048 tokens in 2 x 4 boxes 46.0 -> 49.1.
+// of the launch: 5832 x 3032 at M = 8 and 2324 tokens (19 tiles x 12 groups, 36 workgroups instead of 28.5) 43.8 us in
+// runs, 61.1 in boxes; and only where an XCD fetches 1 MiB less, and 1 MiB more than that for every percent by which
+// that box exceeds the even share: 3702 x 792 at M = 5 and 2198 tokens (24 instead of 18 workgroups, 0.9 MiB) 40.1 and
+// 46.4.  262 random launches with 17 tiles or more, where a box saves 1 MiB at least: boxes everywhere 0.986 of the time
+// without, up to 1.46; by this rule 112 of them, 0.941, none above 1.02.  vnm_spmm_staged: 3072 x 768 at M = 8 and 12608
+// tokens (99 tiles) 48 -> 40 us (vnm_spmm runs the resident kernel there), 2304 x 1536 at 6000 (47) 26.0 -> 20.3.  Boxes
+// in other shapes lose on more than one generation: 11008 x 4096 at V = 32, M = 5 and 2048 tokens in 2 x 4 boxes 46.0 ->
+// 49.1.
 inline XcdOrder xcd_order(int64_t tiles, int64_t groups, int64_t steps, int pieces, int64_t weight_bytes, int64_t staged_bytes,
                           bool one_generation, bool wide, bool in_l2) {
   XcdOrder o{XcdOrder::kGrid, 0};
@@ -227,33 +229,35 @@ inline bool deep_loop(int pieces, int64_t workgroups, int64_t last_piece, int64_
 // measured slower (ring 2 / 4 / 8, 4096 x 4096, 64:2:5, one token: 7.0 / 7.2 / 8.1 us).
 constexpr int kGemvRing = 2;
 constexpr int64_t kGemvLds = 150 * 1024;
-// LDS: the rows of X, per wave a ring of strips of 32 halfwords per token (half tiles: 64, for pairs of steps), the waves' sums.
+// LDS: the rows of X, per wave a ring of strips of 32 halfwords per token (half tiles: 64, for pairs of steps), the
+// waves' sums.
 inline int64_t gemv_lds(int tokens, int64_t in, int waves, bool half) {
   return tokens * (in * 2 + 128) + (int64_t)waves * kGemvRing * tokens * (half ? 128 : 64) + (int64_t)waves * tokens * 64 * 4;
 }
 // Half tiles (16 rows per workgroup) while they are at most one workgroup per compute unit.  Weights from HBM, whole / half
-// tiles at 1 and at 4 tokens, us: 4096 x 4096, M = 5 7.1 / 6.2 and 8.1 / 7.1, M = 8 4.4 / 4.5 and 5.5 / 5.1; 4096 x 11008, M = 8 10.4 / 8.4 and
-// 12.1 / 10.6; 1024 x 8192, M = 5 7.6 / 6.0 and 10.4 / 8.5; 128 x 128 2.6 / 2.3 and 3.1 / 2.7; 64 x 11008, M = 8 6.9 / 5.2 and 9.6 / 7.7.
-// 4100 x 4096 (65 row blocks) keeps whole tiles.  Rows of X too long for half tiles but not for whole ones: whole tiles beyond
-// 32 row blocks, below that the few-token kernel (64 x 73600, M = 16, one token 17.3 us on whole tiles, 8.8 there; 4096 x 73600,
-// V = 32 30.6 and 50.2).
+// tiles at 1 and at 4 tokens, us: 4096 x 4096, M = 5 7.1 / 6.2 and 8.1 / 7.1, M = 8 4.4 / 4.5 and 5.5 / 5.1; 4096 x
+// 11008, M = 8 10.4 / 8.4 and 12.1 / 10.6; 1024 x 8192, M = 5 7.6 / 6.0 and 10.4 / 8.5; 128 x 128 2.6 / 2.3 and 3.1 /
+// 2.7; 64 x 11008, M = 8 6.9 / 5.2 and 9.6 / 7.7.
+// 4100 x 4096 (65 row blocks) keeps whole tiles.  Rows of X too long for half tiles but not for whole ones: whole tiles
+// beyond 32 row blocks, below that the few-token kernel (64 x 73600, M = 16, one token 17.3 us on whole tiles, 8.8
+// there; 4096 x 73600, V = 32 30.6 and 50.2).
 inline bool gemv_half(int tokens, int64_t row_blocks, int64_t in) {
   return row_blocks <= 64 && (row_blocks <= 32 || gemv_lds(tokens, in, 16, true) <= kGemvLds);
 }
-// Waves per workgroup.  Whole tiles: 8 where they are more than compute units, so that several workgroups share a unit and one's
-// start-up (X, the first weights) overlaps the others' streaming, otherwise 16.  Half tiles: 8 where a pass of them holds
-// a row of X and K is short, else 16.  With 16 / 8, one token, us: 4096 x 4096, M = 5 (103 steps) 6.3 / 6.5, M = 8 (64) 5.1 / 4.6; 4096 x
-// 11008, M = 5 11.9 / 12.4; 1024 x 8192, M = 5 5.9 / 6.9; 2048 x 5504, M = 12 (58 steps) 3.9 / 4.2; 2048 x 2048, M = 5 3.9 / 3.7; 128 x 128
-// 2.9 / 2.3.
+// Waves per workgroup.  Whole tiles: 8 where they are more than compute units, so that several workgroups share a unit
+// and one's start-up (X, the first weights) overlaps the others' streaming, otherwise 16.  Half tiles: 8 where a pass of
+// them holds a row of X and K is short, else 16.  With 16 / 8, one token, us: 4096 x 4096, M = 5 (103 steps) 6.3 / 6.5,
+// M = 8 (64) 5.1 / 4.6; 4096 x 11008, M = 5 11.9 / 12.4; 1024 x 8192, M = 5 5.9 / 6.9; 2048 x 5504, M = 12 (58 steps)
+// 3.9 / 4.2; 2048 x 2048, M = 5 3.9 / 3.7; 128 x 128 2.9 / 2.3.
 inline int gemv_waves(int tokens, int64_t row_blocks, int64_t in, int64_t steps) {
   if (gemv_half(tokens, row_blocks, in)) return in <= 8 * 64 * 8 && steps <= 80 ? 8 : 16;
   return 2 * row_blocks > 256 ? 8 : 16;
 }
 // Which layers it takes.  Three and four tokens: only where the tiles leave compute units idle and K is short.  Otherwise the
-// vector ALUs become the limit and the matrix-core few-token kernel is faster: 11008 x 4096 at 64:2:5 (344 tiles) and four tokens
-// 13.2 us against 12.7.  This kernel's time over that one's at 3 and 4 tokens, 160 random layers of up to 128 row blocks by K
-// steps: up to 80 0.32 to 0.81, 81 to 130 0.40 to 0.9 (1.02 at M = 16), 131 to 180 0.78 to 1.02, 181 to 224 0.90 to 1.11, 225 to 290
-// 0.51 to 1.24, more 0.97 to 1.43.
+// vector ALUs become the limit and the matrix-core few-token kernel is faster: 11008 x 4096 at 64:2:5 (344 tiles) and
+// four tokens 13.2 us against 12.7.  This kernel's time over that one's at 3 and 4 tokens, 160 random layers of up to
+// 128 row blocks by K steps: up to 80 0.32 to 0.81, 81 to 130 0.40 to 0.9 (1.02 at M = 16), 131 to 180 0.78 to 1.02, 181
+// to 224 0.90 to 1.11, 225 to 290 0.51 to 1.24, more 0.97 to 1.43.
 inline bool gemv_takes(int tokens, int64_t row_blocks, int64_t in, int64_t steps) {
   if (tokens > 2 && (2 * row_blocks > 256 || steps > 224)) return false;
   return gemv_lds(tokens, in, gemv_waves(tokens, row_blocks, in, steps), gemv_half(tokens, row_blocks, in)) <= kGemvLds;
@@ -269,9 +273,9 @@ inline bool gemv_takes(int tokens, int64_t row_blocks, int64_t in, int64_t steps
 // Below 8 row blocks one group is a workgroup of 4 waves on as many compute units, and two take steps to make up for the
 // exchange at the end: 256 x 600 at 7455 tokens and M = 5 (15 steps) 9.5 us with one, 11.2 with two.  Two groups against one,
 // geometric mean and range over 350 random launches of that kind: 8-16 steps 1.08 (0.88-1.25), 17-31 1.00 (0.85-1.13), 32-55
-// 0.95 (0.85-1.06), more 0.88 (0.75-1.09); but at M = 8, where one group has a ring of three images and two have four each, 8-13
-// 1.07 (0.89-1.17), 14-23 0.92 (0.79-1.10), 24-55 0.82 (0.65-1.01), more 0.67.  340 launches of 8 row blocks and more: 8-16
-// steps 0.84, more 0.79.
+// 0.95 (0.85-1.06), more 0.88 (0.75-1.09); but at M = 8, where one group has a ring of three images and two have four
+// each, 8-13 1.07 (0.89-1.17), 14-23 0.92 (0.79-1.10), 24-55 0.82 (0.65-1.01), more 0.67.  340 launches of 8 row blocks
+// and more: 8-16 steps 0.84, more 0.79.
 inline bool kgroups(int pieces, int64_t workgroups, int64_t row_blocks, int64_t steps, int M) {
   const int least = row_blocks >= 8 ? 8 : M == 8 ? 24 : 56;
   return pieces == 1 && workgroups <= 256 && steps >= least && M <= 10;
@@ -284,12 +288,13 @@ inline int64_t prune_fast_lds(int V, int M, int steps, bool scored) {
   return V * (NC + 4) * 2 + NC * 8 + blocks * 4 + (scored ? V * (NC + 4) * 4 : 0);
 }
 // Rows of W a thread requests at a time, where `groups` threads share a column of V rows: the fewest that need no more trips
-// than 12, which used to be taken everywhere.  Requests beyond the last row are made all the same, and from |w| alone (62, 67, 80
-// and 109 registers at 4, 6, 8 and 12) the registers are workgroups less; with scores (95 and, computed on the fly, 143 at any
-// number: another phase needs them) it is the requests only.  From HBM, us, with 12 / with this: from |w| 4096 x 4096 at 64:2:5
-// (6 rows) 25.5 / 22.3, V = 64, M = 12 (7) 21.0 / 18.0, 11008 x 4096 at V = 32, M = 4 (4) 59.1 / 50.7, 1000 x 1000 at V = 64, M = 8 (4)
-// 7.1 / 6.6, and always 8 would lose where 11 rows then take two trips: 11008 x 4096 at 64:2:5 48.9 / 51.1; from scores 120 sizes 1.04
-// times this with 12 (up to 1.10), 1.01 with 6; a refresh 1.016 and 1.003 (215 sizes).
+// than 12, which used to be taken everywhere.  Requests beyond the last row are made all the same, and from |w| alone
+// (62, 67, 80 and 109 registers at 4, 6, 8 and 12) the registers are workgroups less; with scores (95 and, computed on
+// the fly, 143 at any number: another phase needs them) it is the requests only.  From HBM, us, with 12 / with this:
+// from |w| 4096 x 4096 at 64:2:5 (6 rows) 25.5 / 22.3, V = 64, M = 12 (7) 21.0 / 18.0, 11008 x 4096 at V = 32, M = 4 (4)
+// 59.1 / 50.7, 1000 x 1000 at V = 64, M = 8 (4) 7.1 / 6.6, and always 8 would lose where 11 rows then take two trips:
+// 11008 x 4096 at 64:2:5 48.9 / 51.1; from scores 120 sizes 1.04 times this with 12 (up to 1.10), 1.01 with 6; a refresh
+// 1.016 and 1.003 (215 sizes).
 inline int prune_batch(int V, int groups) {
   const int rows = (V + groups - 1) / groups, trips = (rows + 11) / 12;
   for (const int b : {4, 6, 8}) if ((rows + b - 1) / b == trips) return b;
@@ -315,9 +320,9 @@ inline int64_t prune_ria_lds(int V, int M, int steps) {
   return V * (NC + 4) * 2 + NC * 8 + blocks * 4 + 3 * NC * 8 + 2 * V * 8 + 16;
 }
 // Whole refresh of 4096 x 4096, us, with 2 / 4 / 8 steps: V = 64, M = 5 98 / 82 / 91; V = 64, M = 8 75 / 69 / 85; V = 128,
-// M = 5 95 / 87 / 117; V = 64, M = 12 (80 KiB at 4) 72 / 80 / 102; V = 32, M = 8 (49 KiB at 8) 82 / 69 / 70 and on 2000 x 3000
-// 43 / 37 / 41; V = 32, M = 4 120 / 90 / 79.  Fewer where that leaves too few workgroups: 200 x 304 at V = 128, M = 8 with
-// 1 / 2 / 4 / 8 steps 32 / 34 / 36 / 55; 1000 x 1000 at V = 32, M = 8 25.0 / 24.3 / 24.4 / 30.2.
+// M = 5 95 / 87 / 117; V = 64, M = 12 (80 KiB at 4) 72 / 80 / 102; V = 32, M = 8 (49 KiB at 8) 82 / 69 / 70 and on 2000
+// x 3000 43 / 37 / 41; V = 32, M = 4 120 / 90 / 79.  Fewer where that leaves too few workgroups: 200 x 304 at V = 128, M
+// = 8 with 1 / 2 / 4 / 8 steps 32 / 34 / 36 / 55; 1000 x 1000 at V = 32, M = 8 25.0 / 24.3 / 24.4 / 30.2.
 inline int prune_ria_steps(int V, int M, int64_t row_blocks, int64_t steps) {
   int k = 8;
   while (k > 1 && (prune_ria_lds(V, M, k) > (k > 4 ? 40 : 50) * 1024 || (steps + k - 1) / k * row_blocks < (k > 4 ? 512 : 160))) k >>= 1;
