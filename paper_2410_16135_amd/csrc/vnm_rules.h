@@ -234,10 +234,12 @@ constexpr int64_t kGemvLds = 150 * 1024;
 inline int64_t gemv_lds(int tokens, int64_t in, int waves, bool half) {
   return tokens * (in * 2 + 128) + (int64_t)waves * kGemvRing * tokens * (half ? 128 : 64) + (int64_t)waves * tokens * 64 * 4;
 }
-// Half tiles (16 rows per workgroup) while they are at most one workgroup per compute unit.  Weights from HBM, whole / half
-// tiles at 1 and at 4 tokens, us: 4096 x 4096, M = 5 7.1 / 6.2 and 8.1 / 7.1, M = 8 4.4 / 4.5 and 5.5 / 5.1; 4096 x
-// 11008, M = 8 10.4 / 8.4 and 12.1 / 10.6; 1024 x 8192, M = 5 7.6 / 6.0 and 10.4 / 8.5; 128 x 128 2.6 / 2.3 and 3.1 /
-// 2.7; 64 x 11008, M = 8 6.9 / 5.2 and 9.6 / 7.7.
+// Half tiles (16 rows per workgroup) while they are at most one workgroup per compute unit.  Whole / half tiles at 1 and
+// at 4 tokens, us: weights from HBM 4096 x 4096, M = 5 7.3 / 6.2 and 8.9 / 7.4, M = 8 5.6 / 4.9 and 6.5 / 5.7; 4096 x
+// 11008, M = 8 11.8 / 8.4 and 13.5 / 10.7; 1024 x 8192, M = 5 10.2 / 7.2 and 11.9 / 9.2; 128 x 128 2.5 / 2.3 and 3.1 /
+// 2.7; 64 x 11008, M = 8 6.9 / 5.4 and 9.7 / 7.8; from the last-level cache 4096 x 4096, M = 5 6.6 / 6.1 and 8.3 / 7.4,
+// 4096 x 11008, M = 8 9.4 / 8.6 and 12.5 / 10.9.  23 layers at 1, 2 and 4 tokens: 0.82, 0.84 and 0.86 of the time from
+// HBM, 0.89, 0.89 and 0.88 from that cache.
 // 4100 x 4096 (65 row blocks) keeps whole tiles.  Rows of X too long for half tiles but not for whole ones: whole tiles
 // beyond 32 row blocks, below that the few-token kernel (64 x 73600, M = 16, one token 17.3 us on whole tiles, 8.8
 // there; 4096 x 73600, V = 32 30.6 and 50.2).
@@ -246,18 +248,19 @@ inline bool gemv_half(int tokens, int64_t row_blocks, int64_t in) {
 }
 // Waves per workgroup.  Whole tiles: 8 where they are more than compute units, so that several workgroups share a unit
 // and one's start-up (X, the first weights) overlaps the others' streaming, otherwise 16.  Half tiles: 8 where a pass of
-// them holds a row of X and K is short, else 16.  With 16 / 8, one token, us: 4096 x 4096, M = 5 (103 steps) 6.3 / 6.5,
-// M = 8 (64) 5.1 / 4.6; 4096 x 11008, M = 5 11.9 / 12.4; 1024 x 8192, M = 5 5.9 / 6.9; 2048 x 5504, M = 12 (58 steps)
-// 3.9 / 4.2; 2048 x 2048, M = 5 3.9 / 3.7; 128 x 128 2.9 / 2.3.
+// them holds a row of X and K is short, else 16.  With 16 / 8, one token, us (halves of a tile in grid order): 4096 x
+// 4096, M = 5 (103 steps) 6.3 / 6.5, M = 8 (64) 5.1 / 4.6; 4096 x 11008, M = 5 11.9 / 12.4; 1024 x 8192, M = 5 5.9 /
+// 6.9; 2048 x 5504, M = 12 (58 steps) 3.9 / 4.2; 2048 x 2048, M = 5 3.9 / 3.7; 128 x 128 2.9 / 2.3.
 inline int gemv_waves(int tokens, int64_t row_blocks, int64_t in, int64_t steps) {
   if (gemv_half(tokens, row_blocks, in)) return in <= 8 * 64 * 8 && steps <= 80 ? 8 : 16;
   return 2 * row_blocks > 256 ? 8 : 16;
 }
 // Which layers it takes.  Three and four tokens: only where the tiles leave compute units idle and K is short.  Otherwise the
 // vector ALUs become the limit and the matrix-core few-token kernel is faster: 11008 x 4096 at 64:2:5 (344 tiles) and
-// four tokens 13.2 us against 12.7.  This kernel's time over that one's at 3 and 4 tokens, 160 random layers of up to
-// 128 row blocks by K steps: up to 80 0.32 to 0.81, 81 to 130 0.40 to 0.9 (1.02 at M = 16), 131 to 180 0.78 to 1.02, 181
-// to 224 0.90 to 1.11, 225 to 290 0.51 to 1.24, more 0.97 to 1.43.
+// four tokens 13.2 us against 12.7.  This kernel's time over that one's at 3 and 4 tokens (halves of a tile in grid order,
+// up to 11 % slower than they run), 160 random layers of up to 128 row blocks by K steps: up to 80 0.32 to 0.81, 81 to
+// 130 0.40 to 0.9 (1.02 at M = 16), 131 to 180 0.78 to 1.02, 181 to 224 0.90 to 1.11, 225 to 290 0.51 to 1.24, more 0.97
+// to 1.43.
 inline bool gemv_takes(int tokens, int64_t row_blocks, int64_t in, int64_t steps) {
   if (tokens > 2 && (2 * row_blocks > 256 || steps > 224)) return false;
   return gemv_lds(tokens, in, gemv_waves(tokens, row_blocks, in, steps), gemv_half(tokens, row_blocks, in)) <= kGemvLds;

@@ -49,10 +49,17 @@ __global__ void __launch_bounds__(64 * WAVES) spmm_gemv_kernel(const GemvArgs a)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int KS = HALF ? 2 : 1;                 // K steps of a step of this code
-  const unsigned unit = HALF ? blockIdx.x >> 1 : blockIdx.x;
-  const unsigned rh = HALF ? blockIdx.x & 1 : 0;   // half of the tile
-  const unsigned rp = unit >> 1;                   // 64-row block of the packed copy
-  const unsigned at = unit & 1;                    // its 32-row tile
+  // Workgroup n runs on XCD n mod 8, each with an L2 of its own.  The four half tiles of a row block read the same lines of
+  // positions and columns: they run on one XCD, 8 row blocks at a time (the row blocks beyond a multiple of 8 in grid order).
+  // In grid order they fetched 1.4 times the weight, and large layers whose weights the last-level cache holds were slower than
+  // on whole tiles.  One token, us per call, whole tiles / half tiles in grid order / now: 4096 x 11008, M = 5 from that cache
+  // 12.7 / 13.8 / 11.8, from HBM 16.6 / 12.7 / 11.5; 4096 x 4096, M = 5 6.6 / 6.7 / 6.1 and 7.3 / 6.4 / 6.2.
+  const unsigned n = blockIdx.x;
+  const bool by_xcd = HALF && n < (gridDim.x & ~31u);
+  const unsigned part = !HALF ? n & 1 : by_xcd ? (n >> 3) & 3 : n & 3;
+  const unsigned rp = !HALF ? n >> 1 : by_xcd ? (n >> 5) * 8 + (n & 7) : n >> 2;   // 64-row block of the packed copy
+  const unsigned at = HALF ? part >> 1 : part;     // its 32-row tile
+  const unsigned rh = HALF ? part & 1 : 0;         // half of the tile
   const unsigned SK = (unsigned)a.S, S = (SK + KS - 1) / KS;
   const int M = a.M;
   const int in = (int)a.in;

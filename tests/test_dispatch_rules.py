@@ -235,3 +235,16 @@ def test_boxes_cover_the_launch(rule, tiles, groups, log_t):
                                             (32, 32, 4), (128, 1, 12)])
 def test_prune_batch(rule, V, groups, batch):
     assert rule("prune_batch(%d, %d)" % (V, groups)) == batch
+
+
+# half tiles of one to four tokens: every quarter of a row block once, the four of a block on one XCD (workgroup n mod 8)
+# except in the row blocks beyond a multiple of 8
+@pytest.mark.parametrize("blocks", [1, 7, 8, 9, 16, 29, 64])
+def test_half_tiles_cover_the_launch(blocks):
+    grid, seen = 4 * blocks, {}
+    for n in range(grid):
+        by_xcd = n < (grid & ~31)
+        rp, part = ((n >> 5) * 8 + (n & 7), (n >> 3) & 3) if by_xcd else (n >> 2, n & 3)
+        seen.setdefault(rp, {})[part] = n & 7
+    assert sorted(seen) == list(range(blocks)) and all(sorted(p) == [0, 1, 2, 3] for p in seen.values())
+    assert all(len(set(p.values())) == 1 for rp, p in seen.items() if rp < blocks // 8 * 8)

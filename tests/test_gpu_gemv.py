@@ -60,3 +60,10 @@ def test_infinite_weight_in_the_first_step(out, steps, V, M, T):
                                            (2080, 15040, 32, 16, 3), (2080, 15048, 64, 16, 4), (2080, 16064, 64, 12, 4)])
 def test_few_tokens_on_wide_layers(out, inn, V, M, T):
     test_few_tokens(out, inn, V, M, T)
+
+
+# half tiles are dealt out 8 row blocks at a time: 7, 8, 9, 15 and 21 of them, and 63
+@pytest.mark.parametrize("T", [1, 4])
+@pytest.mark.parametrize("out,inn,V,M", [(448, 264, 64, 4), (512, 264, 32, 4), (550, 520, 64, 8), (960, 264, 128, 5), (1300, 520, 32, 8), (4030, 264, 64, 4)])
+def test_order_of_half_tiles(out, inn, V, M, T):
+    test_few_tokens(out, inn, V, M, T)
