@@ -94,14 +94,21 @@ inline bool plain_scalar_faster(int64_t T, int64_t out, int64_t B, int M) {
 //   results up to 7    0.55 (0.15-1.30)                          22 to 78    0.68 (0.32-1.18)   1.30 (0.80-1.88)
 //              7 to 14 0.67 (0.20-1.25)   1.14 (0.88-1.32)       78 to 128   0.83 (0.57-1.32)   1.14 (0.86-1.62)
 //             14 to 22 0.72 (0.28-1.36)   1.21 (0.79-1.54)
-// Beyond 128 pairs two pieces take a second generation, 0.94 to 1.28 at 200 to 280 steps; M > 10, where one piece has
-// one wave group, keeps the line it had (129 pairs: 1.02 at 103 steps, 0.66 at 205; 160 pairs 1.08 and 0.96).
+// Beyond 128 pairs two pieces take a second generation, 0.94 to 1.28 at 200 to 280 steps; M > 10 keeps the line it had
+// (129 pairs: 1.02 at 103 steps, 0.66 at 205; 160 pairs 1.08 and 0.96).
+// M > 10: one piece has one wave group there, from 8 row blocks on on half of the compute units, and pieces pay earlier: 1205
+// x 1688 at M = 16 and 504 tokens (14 steps) 43 us in one piece, 34 in three; 705 wide at M = 12 and 354 tokens (9
+// steps) 1.33.
+// 198 random layers that the other line would not split (M 11 to 16, 8 to 102 units of results), all in pieces as before this
+// line 1, none 1.009 (weights from the last-level cache) and 1.027 (from HBM), up to 1.34; by this line 0.969 and 0.974,
+// up to 1.13, with the better of both every time 0.965.
 inline int64_t split_pieces(int64_t T, int64_t out, int64_t pairs, int64_t steps, int M) {
   const int64_t results = (T * out + 32767) / 32768, length = steps * M;
   if (pairs > 128) return M > 10 && T > 256 && steps >= 192 ? 2 : 1;
   const int64_t least = results <= 7 ? 0 : results <= 14 ? 128 : results <= 22 ? 240
                       : results <= 78 ? (T <= 256 ? 300 : 380) : T <= 600 ? 420 : T <= 1500 ? 500 : 660;
-  if (length < least) return 1;
+  const int64_t least_one_group = out <= 448 ? (results <= 14 ? 128 : 240) : results <= 34 ? 0 : results <= 50 ? 220 : 320;
+  if (length < (M > 10 && results <= 78 ? least_one_group : least)) return 1;
   return T <= 256 ? (200 + pairs / 2) / pairs : pairs <= 85 ? 256 / pairs : 2;
 }
 

@@ -142,6 +142,8 @@ def test_one_to_four_tokens(rule, tokens, blocks, inn, steps, half, waves, takes
     (250, 8000, 64, 59, 5, 1), (250, 8000, 64, 60, 5, 3), (700, 3000, 72, 75, 5, 1), (700, 3000, 72, 76, 5, 3),
     (700, 4096, 96, 103, 5, 2), (500, 6000, 96, 83, 5, 1), (500, 6000, 96, 84, 5, 2), (1000, 3500, 112, 99, 5, 1), (1000, 3500, 112, 100, 5, 2),
     (1024, 4096, 128, 103, 5, 2), (2000, 2048, 128, 131, 5, 1), (2000, 2048, 128, 132, 5, 2),
+    (504, 1205, 20, 14, 16, 12), (504, 1205, 20, 9, 12, 12), (800, 1407, 42, 18, 12, 1), (800, 1407, 42, 19, 12, 6), (842, 2000, 56, 26, 12, 1),
+    (842, 2000, 56, 27, 12, 4), (1100, 448, 18, 15, 16, 14), (1100, 448, 18, 14, 16, 1), (900, 3000, 96, 41, 12, 1), (900, 3000, 96, 42, 12, 2),
     (1000, 4100, 136, 300, 5, 1), (1000, 4100, 136, 191, 12, 1), (1000, 4100, 136, 192, 12, 2), (100, 2048, 8, 10, 5, 25)])
 def test_split_pieces(rule, T, out, pairs, steps, M, pieces):
     assert rule("split_pieces(%d, %d, %d, %d, %d)" % (T, out, pairs, steps, M)) == pieces
